@@ -174,7 +174,9 @@ static int upload_image(pfac_trie *t) {
     size_t o_dradd = align256(o_dchild + std::max<size_t>(I.dchild.size(), 1) * 4);
     size_t o_rlist = align256(o_dradd + std::max<size_t>(I.dradd.size(), 1) * 4);
     size_t o_ldag = align256(o_rlist + std::max<size_t>(I.rank_list.size(), 2) * 4);
-    size_t total = align256(o_ldag + std::max<size_t>(I.lvl_dag.size(), 2) * 4);
+    size_t o_gram = align256(o_ldag + std::max<size_t>(I.lvl_dag.size(), 2) * 4);
+    size_t o_gfp = align256(o_gram + I.gram.size() * 4);
+    size_t total = align256(o_gfp + I.gfp.size() * 2);
     auto t0 = std::chrono::steady_clock::now();
     // the new image is built beside the old one, which stays usable if this fails
     DeviceBuf fresh;
@@ -222,6 +224,10 @@ static int upload_image(pfac_trie *t) {
             if (!I.lvl_dag.empty())
                 CP(hipMemcpy(b + o_ldag, I.lvl_dag.data(), I.lvl_dag.size() * 4, hipMemcpyHostToDevice));
         }
+        if (!I.gram.empty())
+            CP(hipMemcpy(b + o_gram, I.gram.data(), I.gram.size() * 4, hipMemcpyHostToDevice));
+        if (!I.gfp.empty())
+            CP(hipMemcpy(b + o_gfp, I.gfp.data(), I.gfp.size() * 2, hipMemcpyHostToDevice));
         return hipSuccess;
     };
 #undef CP
@@ -270,6 +276,12 @@ static int upload_image(pfac_trie *t) {
     v.rank_list = (const uint2 *)(b + o_rlist);
     v.lvl_dag = (const uint2 *)(b + o_ldag);
     v.dag = I.dag;
+    v.gram = (const uint32_t *)(b + o_gram);
+    v.gfp = (const uint4 *)(b + o_gfp);
+    v.gram_s = I.gram_s;
+    v.gram_lw = I.gram_lw;
+    v.gfp_lb = I.gfp_lb;
+    v.min_len = (uint32_t)std::min<uint64_t>(t->crs.min_len, 0xffffffffu);
     v.fold_syms = I.fold_syms;
     v.K = I.K;
     v.b = I.b;
@@ -816,6 +828,12 @@ static ScanShape scan_shape(const pfac_trie *t, const pfac_tuning &tn, const voi
     return h;
 }
 
+// The gram kernel runs the launches whose kernel the library chooses (kernel
+// 3), where the image has a gram filter.
+static bool use_gram_kernel(const pfac_trie *t, uint64_t total) {
+    return t->tuning.kernel == 3 && t->img.gram_s && !t->img.trunc_depth && !t->img.dag && total >= kAutoSplitBytes;
+}
+
 static int enqueue_scan(const Launch &L, bool reserve) {
     const pfac_trie *t = L.t;
     const pfac_tuning tn = launch_tuning(t, L.total);
@@ -839,6 +857,11 @@ static int enqueue_scan(const Launch &L, bool reserve) {
 
     ScanArgs a = layout_for(t, tn, &waves);
     a.im = t->view;
+    const bool gram = wave_kernel && split && use_gram_kernel(t, L.total);
+    if (gram) {
+        waves = kGramWaves;
+        gram_lds_layout(a, waves);
+    }
     a.base = (const uint8_t *)(addr - shift);
     a.shift = shift;
     a.total = L.total;
@@ -846,7 +869,7 @@ static int enqueue_scan(const Launch &L, bool reserve) {
     a.n_texts = L.n_texts;
     a.text_id0 = L.text_id0;
     a.tile_first_text = L.offsets ? (const uint32_t *)w->tile_first.p : nullptr;
-    a.chunk_info = L.offsets && wave_kernel ? (const uint2 *)w->chunk_info.p : nullptr;
+    a.chunk_info = L.offsets && wave_kernel && !gram ? (const uint2 *)w->chunk_info.p : nullptr;
     a.n_plan = n_plan;
     a.plan_shift = (uint32_t)__builtin_ctz(plan_unit);
     a.n_tiles = n_tiles;
@@ -859,7 +882,12 @@ static int enqueue_scan(const Launch &L, bool reserve) {
     a.counts = L.counts;
     a.inline_stage = (pfac_match *)w->inline_stage.p;
     a.inline_cap = wave_kernel ? std::max(kInlineCap, kInlinePerChunk * tn.chunks_per_unit) : 0;
-    if (split) {
+    if (gram) {
+        // the candidate area (32 x 16 bytes a chunk) holds the matches past
+        // the LDS lists, 8 bytes each, in scan order and again in position order
+        a.spill = (uint2 *)w->cand.p;
+        a.spill_cap = a.group * kCandPerChunk;
+    } else if (split) {
         a.cand = (uint4 *)w->cand.p;
         a.cand_count = (uint32_t *)w->cand_count.p;
         a.cand_cap = a.group * kCandPerChunk;
@@ -870,7 +898,7 @@ static int enqueue_scan(const Launch &L, bool reserve) {
 
     a.n_sums = n_sums;
     // the split filter kernel clears the block sums and the cursor itself
-    if (!(split && n_tiles)) HIP_TRY(launch_reset(a.stage_cursor, a.blocksum, n_sums, L.s));
+    if (!(split && !gram && n_tiles)) HIP_TRY(launch_reset(a.stage_cursor, a.blocksum, n_sums, L.s));
     if (L.counts) HIP_TRY(launch_fill_u32(L.counts, L.total, 0, L.s));
     if (n_tiles) {
         if (L.offsets)
@@ -879,7 +907,12 @@ static int enqueue_scan(const Launch &L, bool reserve) {
         int per_cu = (int)tn.wg_per_cu;
         int occ;
         uint64_t want;
-        if (wave_kernel) {
+        if (gram) {
+            const int sl = (int)a.im.gram_s;
+            if (a.lds_total > 64 * 1024) HIP_TRY(grant_lds(20 + sl, a.lds_total, prepare_gram_kernel, sl));
+            occ = 1;
+            want = (n_tiles + waves - 1) / waves;
+        } else if (wave_kernel) {
             const int mode = wave_mode(a);
             if (a.lds_total > 64 * 1024) HIP_TRY(grant_lds(4 + mode, a.lds_total, prep_wave, mode));
             occ = max_wave_wg_per_cu(a, waves);
@@ -902,12 +935,14 @@ static int enqueue_scan(const Launch &L, bool reserve) {
         w->main_grid = grid;
         w->main_block = wave_kernel ? 64 * waves : kWG;
         w->main_lds = a.lds_total;
-        if (wave_kernel)
+        if (gram)
+            HIP_TRY(launch_scan_grams(a, waves, grid, L.s));
+        else if (wave_kernel)
             HIP_TRY(launch_scan_waves(a, waves, grid, L.s));
         else
             HIP_TRY(launch_scan(a, bpl, grid, L.s));
         if (w->ev_stop) HIP_TRY(hipEventRecordWithFlags(w->ev_stop, L.s, ev_flags));
-        if (split) HIP_TRY(launch_walk_units(a, L.s));
+        if (split && !gram) HIP_TRY(launch_walk_units(a, L.s));
     }
     FinishArgs f{};
     f.unit_count = a.unit_count;

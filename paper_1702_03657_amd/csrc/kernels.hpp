@@ -48,6 +48,9 @@ struct ImageView {
     uint32_t q16_lw, qfp_lb;          // four-symbol filter sizes (0 = none)
     uint32_t qa, qb, qalph, q16_mul;  // its symbol map, alphabet bytes and hash multiplier
     uint32_t top_nodes, top_rw;       // bitmapped top nodes: count, words per node
+    const uint32_t *gram;     // gram filter: bitmap words (2^gram_lw)
+    const uint4 *gfp;         // gram filter: buckets of 16 x 16-bit slots (2^gfp_lb; 0 = none)
+    uint32_t gram_s, gram_lw, gfp_lb, min_len;
 };
 
 struct ScanArgs {
@@ -93,6 +96,10 @@ struct ScanArgs {
     uint32_t *cand_count;
     uint32_t cand_cap;
     uint32_t n_sums;                  // split filter kernel: clears blocksum[0 .. n_sums) and the cursor
+    // gram kernel: matches of unit u past the LDS list, at spill[2 * u *
+    // spill_cap ..) in scan order, then spill_cap more in position order
+    uint2 *spill;
+    uint32_t spill_cap, pad2;
 };
 
 struct FinishArgs {
@@ -136,6 +143,14 @@ hipError_t prepare_wave_kernel(int mode, uint32_t lds_bytes);
 hipError_t launch_scan_waves(const ScanArgs &a, uint32_t waves, uint32_t grid, hipStream_t s);
 hipError_t launch_walk_units(const ScanArgs &a, hipStream_t s);
 int max_wave_wg_per_cu(const ScanArgs &a, uint32_t waves);
+
+// Gram kernel (images with a gram filter): filter, walks and emission of
+// every unit in one kernel.  The LDS layout for `waves` waves (the bitmap and
+// one area per wave), and the launch.
+constexpr uint32_t kGramWaves = 16;
+void gram_lds_layout(ScanArgs &a, uint32_t waves);
+hipError_t prepare_gram_kernel(int s, uint32_t lds_bytes);
+hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, uint32_t grid, hipStream_t s);
 
 // Largest resident workgroups per CU for this layout.
 int max_wg_per_cu(uint32_t bpl, uint32_t lds_bytes, int var);  // var: 0 level index, 1 top nodes, 2 DAG

@@ -1,0 +1,549 @@
+// Gram scan kernel for gfx950: filter, walks and emission of every output
+// unit in one kernel, for images with a gram filter (every pattern of four
+// bytes or more).
+//
+// The filter does not test every start position.  A pattern of S + 3 bytes or
+// more that starts at p covers the four-byte gram at the next multiple t of S
+// (t - p < S), so testing the grams at the multiples of S against the grams
+// at offsets 0 .. S-1 of every pattern drops no match.  With S = 4 those
+// grams are the text's aligned dwords, as the loads deliver them: 16 start
+// positions a lane cost four tests of ten VALU instructions instead of
+// sixteen of four and a second stage over many more survivors.
+//
+//   * a workgroup loads the bitmap (two hashed bits per gram, at most 128 KiB)
+//     into LDS; each wave owns units of G consecutive 1 KiB chunks of test
+//     positions and keeps a group of GC chunks of loads in flight;
+//   * every test that hits queues its gram and position at once: reading the
+//     gram again later would double the HBM traffic, since the text streams
+//     through L2 faster than the queue fills;
+//   * 64 queued grams at a time are checked against 16-bit slots in global
+//     memory (L2), which also give the offsets of a gram in its patterns, that
+//     is the starts;
+//   * starts are walked from their depth-K node; matches of a unit collect in
+//     LDS, past kGMatch in global memory, and are staged in (pos, id) order.
+// Unit u holds the starts from S - 1 before its first test position to S - 1
+// before its end, so no start is seen by two units.
+#include <hip/hip_runtime.h>
+
+#include "trie.hpp"
+#include "wave_common.hpp"
+
+namespace pfac {
+
+constexpr uint32_t kGQ = 144;     // grams in a wave's queue, 8 bytes each
+constexpr uint32_t kGC = 128;     // grams in its list of starts: 2 + 1 bytes each
+constexpr uint32_t kGMatch = 64;  // matches of a unit in LDS
+
+typedef __attribute__((address_space(3))) const uint32_t lds_word_t;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const u32x2 lds_pair_t;
+
+// The filter's hash of a gram: its 16-bit halves times two odd constants.
+__device__ __forceinline__ uint32_t gram_hash(uint32_t x) {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    union { uint32_t w; u16x2 h; } a, c;
+    a.w = x;
+    c.w = kGramC0 | kGramC1 << 16;
+    return __builtin_amdgcn_udot2(a.h, c.h, 0u, false);
+}
+
+// the lesser of each 16-bit half
+__device__ __forceinline__ uint32_t pk_min(uint32_t x, uint32_t y) {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    union { uint32_t w; u16x2 h; } a, b, r;
+    a.w = x;
+    b.w = y;
+    r.h = __builtin_elementwise_min(a.h, b.h);
+    return r.w;
+}
+
+// The kernel's arguments read again from the kernel argument segment: code
+// that runs once per unit takes them from there, so that they do not occupy
+// scalar registers (or spill) in the loop over the chunks.
+__device__ __forceinline__ const ScanArgs &again(const ScanArgs &a) {
+    auto *p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    (void)a;
+    return *(const ScanArgs *)(const void *)p;
+}
+
+// Wait for all loads of the wave: at the end of code that runs once per unit,
+// so that no load of it into a register that the chunk loop uses stays open
+// (the compiler would set the loop's waits for that path).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
+// The text holding frame position p: its index, start and end.  p lies in the
+// frame's valid range.
+struct TextSpan {
+    uint32_t tid;
+    uint64_t start, end;
+};
+
+__device__ __forceinline__ TextSpan text_span(const ScanArgs &a, uint64_t p) {
+    if (!a.offsets) return TextSpan{0u, a.shift, a.shift + a.total};
+    const uint64_t c = p >> a.plan_shift;
+    const uint32_t lo = a.tile_first_text[c];
+    const uint32_t hi = (c + 1 < a.n_plan ? a.tile_first_text[c + 1] : a.n_texts - 1) + 1;
+    const uint32_t tid = text_of(a.offsets, lo, hi, a.shift, p);
+    return TextSpan{tid, a.offsets[tid] + a.shift, a.offsets[tid + 1] + a.shift};
+}
+
+// Walk for the start p whose text ends at `end` (end - p >= the shortest
+// pattern), from the depth-K node of its first K symbols.
+__device__ __forceinline__ uint2 walk_start(const ImageView &im, const uint8_t *base, uint64_t p,
+                                            uint64_t end, uint64_t hi_valid) {
+    const uint32_t K = im.K;
+    uint32_t v = 0;
+    if (K) {
+        uint32_t code = 0, bad = 0;
+        for (uint32_t d = 0; d < K; d++) {
+            const uint32_t byte = base[p + d];
+            const uint32_t s = im.identity ? byte : (uint32_t)im.sym[byte];
+            bad |= im.identity ? 0u : (uint32_t)(s == 0xffu);
+            code = (code << im.b) | s;
+        }
+        if (bad) return make_uint2(0, 0);
+        const uint2 lv = ((const uint2 *)im.lvl)[code >> 5];
+        const uint32_t bit = code & 31u;
+        if (!((lv.x >> bit) & 1u)) return make_uint2(0, 0);
+        v = im.lvl_start + lv.y + (uint32_t)__builtin_popcount(lv.x & ((1u << bit) - 1u));
+    }
+    const uint64_t lim = end - p;
+    return walk_g(im, base, p, (uint32_t)umin64(lim, 0xffffffffull), v, K, hi_valid);
+}
+
+// A start's pattern list (0 ids: no match), for starts in any order.
+__device__ __forceinline__ uint2 scan_start(const ScanArgs &a, uint64_t p, const UnitText &ut, uint64_t ut_end) {
+    const uint64_t lo_valid = a.shift, hi_valid = a.shift + a.total;
+    if (p < lo_valid || p >= hi_valid) return make_uint2(0, 0);
+    const uint64_t end = ut.known ? ut_end : text_span(a, p).end;
+    if (end - p < a.im.min_len) return make_uint2(0, 0);
+    return walk_start(a.im, a.base, p, end, hi_valid);
+}
+
+// Reserve `total` records of unit u: its inline slots or the staging area.
+__device__ __forceinline__ void reserve_unit(const ScanArgs &a, uint64_t u, uint32_t total,
+                                             pfac_match *&dst, uint64_t &base, uint64_t &cap) {
+    const uint32_t lane = lane_id();
+    const bool in = total <= a.inline_cap;
+    unsigned long long b = 0;
+    if (lane == 0) {
+        if (!in) b = atomicAdd(a.stage_cursor, (unsigned long long)total);
+        a.unit_count[u] = total;
+        a.unit_off[u] = in ? ~0ull : b;
+        if (total) atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
+    }
+    base = __shfl(b, 0, 64);
+    dst = in ? a.inline_stage + u * a.inline_cap : a.stage;
+    cap = in ? a.inline_cap : a.stage_cap;
+}
+
+// Unit u again, 64 starts at a time in position order, when its matches
+// overflow both lists: one pass counts, the next emits.
+__device__ __forceinline__ void redo_unit(const ScanArgs &a, uint64_t u, uint64_t ubase, uint32_t n_starts,
+                                          const UnitText &ut, uint64_t ut_end) {
+    const uint32_t lane = lane_id();
+    pfac_match *dst = nullptr;
+    uint64_t base = 0, cap = 0;
+    uint32_t total = 0;
+    for (int pass = 0; pass < 2; pass++) {
+        for (uint32_t r = 0; r < n_starts; r += 64) {
+            const uint64_t p = ubase + r + lane;
+            uint2 ids = make_uint2(0, 0);
+            if (r + lane < n_starts) {
+                const uint2 h = scan_start(a, p, ut, ut_end);
+                if (h.y) ids = hit_list(a.im, h);
+            }
+            uint32_t t;
+            const uint32_t before = wave_excl_scan(ids.y, t);
+            if (pass == 0) {
+                total += t;
+            } else {
+                if (ids.y) emit(a, p, ids, dst, base + before, cap, ut);
+                base += t;
+            }
+        }
+        if (pass == 0) reserve_unit(a, u, total, dst, base, cap);
+    }
+}
+
+// Stage a unit whose matches went past mcap: entry i is wm[i] or
+// spill[i - mcap], in no order.  For each window of 8,192 positions the
+// entries in it are ranked by a bit map of its positions (256 words and 64
+// prefix words in LDS) and written in position order to `sorted` (global),
+// which a last pass emits.
+__device__ __forceinline__ void emit_spilled(const ScanArgs &a, uint64_t u, uint64_t ubase, const uint2 *wm,
+                                             uint32_t mcap, const uint2 *spill, uint2 *sorted, uint32_t mn,
+                                             uint32_t n_starts, uint32_t *map, uint32_t *pre, const UnitText &ut) {
+    const uint32_t lane = lane_id();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    // (two loads, not one through a pointer to either memory)
+    auto get = [&](uint32_t i) -> uint2 {
+        const u32x2 m = ((lds_pair_t *)wm)[min(i, mcap - 1)];
+        uint2 e = make_uint2(m.x, m.y);
+        if (i >= mcap) e = spill[i - mcap];
+        return e;
+    };
+    uint32_t done = 0, total = 0;
+    for (uint32_t w0 = 0; w0 < n_starts && done < mn; w0 += 8192) {
+        for (uint32_t i = lane; i < 256; i += 64) map[i] = 0;
+        wave_sync();
+        for (uint32_t r = 0; r < mn; r += 64) {
+            const uint32_t i = r + lane;
+            const uint32_t q = i < mn ? (get(i).x & 0xffffu) - w0 : ~0u;
+            if (q < 8192) atomicOr(&map[q >> 5], 1u << (q & 31u));
+        }
+        wave_sync();
+        const uint4 m4 = ((const uint4 *)map)[lane];
+        uint32_t all;
+        pre[lane] = wave_excl_scan((uint32_t)(__builtin_popcount(m4.x) + __builtin_popcount(m4.y) +
+                                              __builtin_popcount(m4.z) + __builtin_popcount(m4.w)), all);
+        wave_sync();
+        for (uint32_t r = 0; r < mn; r += 64) {
+            const uint32_t i = r + lane;
+            uint32_t n = 0;
+            if (i < mn) {
+                const uint2 e = get(i);
+                const uint32_t q = (e.x & 0xffffu) - w0, w = q >> 5;
+                if (q < 8192) {
+                    uint32_t rk = pre[w >> 2] + (uint32_t)__builtin_popcount(map[w] & ((1u << (q & 31u)) - 1u));
+                    for (uint32_t k = w & ~3u; k < w; k++) rk += (uint32_t)__builtin_popcount(map[k]);
+                    sorted[done + rk] = e;
+                    n = hit_list(a.im, make_uint2(e.y, e.x >> 16)).y;
+                }
+            }
+            uint32_t t;
+            wave_excl_scan(n, t);
+            total += t;
+        }
+        wave_sync();
+        done += all;
+    }
+    pfac_match *dst;
+    uint64_t base, cap;
+    reserve_unit(a, u, total, dst, base, cap);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    for (uint32_t r = 0; r < mn; r += 64) {
+        const uint32_t i = r + lane;
+        uint2 e = make_uint2(0, 0), ids = make_uint2(0, 0);
+        if (i < mn) {
+            e = sorted[i];
+            ids = hit_list(a.im, make_uint2(e.y, e.x >> 16));
+        }
+        uint32_t t;
+        const uint32_t before = wave_excl_scan(ids.y, t);
+        if (i < mn) emit(a, ubase + (e.x & 0xffffu), ids, dst, base + before, cap, ut);
+        base += t;
+    }
+}
+
+// S: the distance of test positions (im.gram_s).
+template <int S>
+__global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    constexpr uint32_t TL = 16 / S;            // tests per lane and chunk
+    constexpr uint32_t GC = S == 4 ? 4 : 2;    // chunks per group and in flight
+    const ImageView &im = a.im;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t waves = blockDim.x >> 6;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t lane = tid & 63;
+
+    // the bitmap by direct global-to-LDS loads, at LDS address 0
+    const uint32_t n_tab = (4u << im.gram_lw) / 16;
+    for (uint32_t b = wave * 64; b < n_tab; b += waves * 64)
+        if (b + lane < n_tab)
+            __builtin_amdgcn_global_load_lds((const void *)((const uint4 *)im.gram + b + lane),
+                                             (__attribute__((address_space(3))) void *)(lds + 16 * b), 16, 0, 0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+
+    uint8_t *wbase = lds + a.off_wave + wave * a.wave_bytes;
+    uint2 *wq = (uint2 *)wbase;                              // queue: (gram, unit position)
+    uint16_t *wc = (uint16_t *)(wbase + 8 * kGQ);            // starts: unit position of the gram ...
+    uint8_t *wcm = wbase + 8 * kGQ + 2 * kGC;                // ... and its offsets
+    uint2 *wm = (uint2 *)(wbase + 8 * kGQ + 3 * kGC);        // matches
+
+    const uint64_t hi_valid = a.shift + a.total;
+    const uint32_t n_u = (uint32_t)a.n_tiles, n_ch = (uint32_t)a.n_plan, G = a.group;
+    const uint32_t ustride = gridDim.x * waves;
+    const uint64_t blk_hi = (hi_valid - 1) & ~15ull;
+    const uint32_t lane16 = 16u * lane;
+    const uint32_t adr_mask = (4u << im.gram_lw) - 4u;
+    const uint32_t lb = im.gfp_lb;
+
+    // ---- loads: GC chunks of a unit from chunk g on; a slot past the unit's
+    // last chunk repeats it, lanes past the text's last 16-byte block repeat
+    // that, so every load is issued and every wait counts only later loads
+    struct Slot {
+        uint4 v;
+        uint32_t h;  // the dword after the lane's 16 bytes (S < 4)
+    };
+    struct Cur {
+        uint32_t u, g, n;  // unit, first chunk of the group, chunks of the unit
+    };
+    auto start_at = [&](uint32_t u) -> Cur { return Cur{u, 0u, u < n_u ? min(G, n_ch - u * G) : 0u}; };
+    auto advance = [&](Cur &c) {
+        c.g += GC;
+        if (c.g >= c.n) c = start_at(c.u + ustride);
+    };
+    auto load = [&](const Cur &c, uint32_t i) -> Slot {
+        uint64_t sb = ((uint64_t)c.u * G + c.g) * kChunk;
+        sb = sb < blk_hi ? sb : blk_hi;
+        const uint32_t lim = (uint32_t)umin64(blk_hi - sb, 0x7fffffffull);
+        const uint32_t last = c.n > c.g ? c.n - c.g - 1 : 0u;
+        const uint32_t o = lane16 + kChunk * min(i, last);
+        Slot s;
+        // (non-temporal: the text is read once, the tables of the walks stay in L2)
+        const u32x4 v = __builtin_nontemporal_load((const u32x4 *)(a.base + sb + min(o, lim)));
+        s.v = make_uint4(v.x, v.y, v.z, v.w);
+        s.h = S == 4 ? 0u : *(const uint32_t *)(a.base + sb + min(o + 16u, lim));
+        return s;
+    };
+    uint32_t qn = 0;  // grams queued (kept in scalar registers, as all counts)
+    // the filter's word of gram x (one 16-bit dot product: two shifts, two
+    // multiplies and an add fewer than 24-bit ones), and its bit 0 set if
+    // both bits of x are
+    auto lookup = [&](uint32_t x, uint32_t &h) -> uint32_t {
+        h = gram_hash(x);
+        return *(lds_word_t *)(uintptr_t)((h >> (kGramShift - 2)) & adr_mask);
+    };
+    auto test = [&](uint32_t ent, uint32_t h, uint32_t x) -> uint32_t { return (ent >> (h & 31u)) & (ent >> (x & 31u)) & 1u; };
+    // queue the grams x that hit, at unit positions pos; past the queue's end
+    // they are only counted
+    auto queue = [&](uint32_t hit, uint32_t x, uint32_t pos) {
+        const unsigned long long mk = __ballot(hit != 0);
+        if (mk == 0) return;
+        const uint32_t at = qn;
+        qn += (uint32_t)__popcll(mk);
+        if (qn <= kGQ && hit) wq[at + mbcnt(mk)] = make_uint2(x, pos);
+    };
+    // the TL tests of a lane's 16 positions from unit position pos on
+    auto tests = [&](const Slot &s, uint32_t pos) {
+        const uint32_t w[5] = {s.v.x, s.v.y, s.v.z, s.v.w, s.h};
+        uint32_t x[TL], h[TL], ent[TL];
+#pragma unroll
+        for (uint32_t j = 0; j < TL; j++) {
+            const uint32_t b = j * S;
+            x[j] = (b & 3) == 0 ? w[b >> 2] : __builtin_amdgcn_alignbyte(w[(b >> 2) + 1], w[b >> 2], b & 3);
+            ent[j] = lookup(x[j], h[j]);
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < TL; j++) queue(test(ent[j], h[j], x[j]), x[j], pos + j * S);
+    };
+
+    // the text of a batch unit that lies inside one: its starts need no search
+    auto unit_text = [&](uint32_t u, uint32_t n, uint64_t ulo, uint64_t &end) -> UnitText {
+        UnitText ut;
+        const ScanArgs &r = again(a);
+        if (!r.offsets) return ut;
+        const uint64_t c0 = (uint64_t)u * G, c1 = c0 + n;
+        if (c1 >= n_ch) return ut;
+        const uint32_t t0 = r.tile_first_text[c0];
+        if (t0 != r.tile_first_text[c1]) return ut;
+        ut.tid = t0;
+        ut.start = r.offsets[t0] + r.shift;
+        end = r.offsets[t0 + 1] + r.shift;
+        ut.known = ut.start + (S - 1) <= ulo;
+        return ut;
+    };
+
+    // ---- the unit being scanned
+    uint32_t cn = 0, mn = 0;  // grams with starts, matches
+    // The check of 64 queued grams is spread over two groups, so that its
+    // loads are not waited for: their slots are loaded after one group's tests
+    // and read after the next's.  (All loads of a wave return in order, so a
+    // load waited for at once also waits for the chunks in flight.)
+    uint32_t nb = 0, tb = 0, gb = 0;
+    uint4 fb0 = make_uint4(0, 0, 0, 0), fb1 = fb0;
+
+    // One step of the check.  It is inlined twice: after a group's tests,
+    // where the loads it waits for are older than the chunks in flight, and in
+    // the loop that empties the queue.
+    auto check = [&](uint32_t at_least) __attribute__((always_inline)) {
+        if (nb) {
+            // offsets in the slot with the gram's fingerprint
+            uint32_t om = (1u << S) - 1u;
+            if (lb) {
+                const uint32_t want = gb >> (20u - lb) << 4 & 0xfff0u, w2 = want << 16 | want;
+                uint32_t m = pk_min(fb0.x ^ w2, fb0.y ^ w2);
+                m = pk_min(m, pk_min(fb0.z ^ w2, fb0.w ^ w2));
+                m = pk_min(m, pk_min(fb1.x ^ w2, fb1.y ^ w2));
+                m = pk_min(m, pk_min(fb1.z ^ w2, fb1.w ^ w2));
+                m = min(m & 0xffffu, m >> 16);
+                om &= m < 16u ? m : 0u;  // (an empty slot may add offsets, which the walk refuses)
+            }
+            const bool pass = lane < nb && om != 0;
+            const unsigned long long mk = __ballot(pass);
+            if (pass) {
+                const uint32_t i = cn + mbcnt(mk);
+                wc[i] = (uint16_t)tb;
+                wcm[i] = (uint8_t)om;
+            }
+            cn += (uint32_t)__popcll(mk);
+            nb = 0;
+        }
+        if (qn >= at_least) {
+            // the last (up to) 64 grams of the queue
+            nb = min(qn, 64u);
+            qn -= nb;
+            const uint2 q = wq[min(qn + lane, kGQ - 1)];
+            tb = q.y;
+            gb = q.x * im.pfx4_mul;
+            if (lb) {
+                const uint4 *bk = im.gfp + (gb >> (32u - lb) << 1);
+                fb0 = bk[0];
+                fb1 = bk[1];
+            }
+        }
+    };
+
+    Cur cc = start_at(blockIdx.x * waves + wave);
+    Slot slot[GC];
+#pragma unroll
+    for (uint32_t i = 0; i < GC; i++) {
+        // in the order of use, as in the loop: the waits there are set for
+        // the path with the fewest later loads
+        slot[i] = load(cc, i);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    while (cc.n) {
+        Cur pc = cc;
+        advance(pc);
+        const uint64_t ulo = (uint64_t)cc.u * G * kChunk;  // frame position of the unit's first chunk
+        const uint64_t ubase = ulo - (S - 1);              // start of its range of starts
+        const uint32_t rem = cc.n - cc.g;
+        const bool last = rem <= GC;
+        const uint32_t gpos = cc.g * kChunk + lane16;
+        const uint32_t q0 = qn;
+#pragma unroll
+        for (uint32_t i = 0; i < GC; i++) {
+            if (i == 0 || i < rem) tests(slot[i], gpos + i * kChunk);
+            slot[i] = load(pc, i);
+        }
+        // the chunks of a group that overflows the queue are tested again
+        // below, one test at a time
+        uint32_t r_from = GC;
+        const uint32_t r_to = min(GC, rem);
+        if (qn > kGQ) {
+            qn = q0;
+            r_from = 0;
+        }
+        wave_sync();
+        check(64);
+        uint32_t ra = 0;  // next test of chunk r_from
+        UnitText ut;
+        uint64_t ut_end = 0;
+
+        if (last || r_from < r_to || qn >= 64 || cn > kGC - 64) {
+            // ---- empty the queue as far as the next group needs it, and wholly
+            // after the unit's last group
+            if (last) ut = unit_text(cc.u, cc.n, ulo, ut_end);
+            for (;;) {
+                if (r_from < r_to && qn + 64 <= kGQ) {
+                    const uint32_t pos = gpos + r_from * kChunk + ra;
+                    const uint8_t *ub = a.base + ulo;
+                    const uint32_t last4 = (uint32_t)umin64(blk_hi + 12 - ulo, 0x7fffffffull);
+                    const uint32_t t4 = min(pos & ~3u, last4);
+                    uint32_t x = *(const uint32_t *)(ub + t4), h;
+                    if (S < 4) x = __builtin_amdgcn_alignbyte(*(const uint32_t *)(ub + min(t4 + 4u, last4)), x, pos & 3u);
+                    const uint32_t ent = lookup(x, h);
+                    queue(test(ent, h, x), x, pos);
+                    wave_sync();
+                    ra += S;
+                    if (ra == 16) {
+                        ra = 0;
+                        r_from++;
+                    }
+                }
+                const bool done = r_from >= r_to && (last ? (nb | qn) == 0 : qn < 64);
+                if (cn > kGC - 64 || (last && done)) {
+                    // ---- walk the starts; matches go to LDS, past kGMatch to
+                    // global memory
+                    wave_sync();
+                    const ScanArgs &r = again(a);
+                    for (uint32_t c0 = 0; c0 < cn; c0 += 64) {
+                        const bool in = c0 + lane < cn;
+                        const uint32_t t = wc[min(c0 + lane, kGC - 1)] + (uint32_t)(S - 1);
+                        uint32_t om = in ? wcm[min(c0 + lane, kGC - 1)] : 0u;
+                        do {
+                            uint2 h = make_uint2(0, 0);
+                            uint32_t pr = 0;
+                            if (om) {
+                                const uint32_t b = (uint32_t)__builtin_ctz(om);
+                                om &= om - 1;
+                                pr = t - b;
+                                h = scan_start(r, ubase + pr, ut, ut_end);
+                            }
+                            const bool got = h.y != 0;
+                            const unsigned long long mk = __ballot(got);
+                            if (got) {
+                                const uint32_t s = mn + mbcnt(mk);
+                                const uint2 e = make_uint2(pr | (h.y << 16), h.x);
+                                if (s < kGMatch) wm[s] = e;
+                                else if (s - kGMatch < r.spill_cap) r.spill[2ull * cc.u * r.spill_cap + s - kGMatch] = e;
+                            }
+                            mn += (uint32_t)__popcll(mk);
+                        } while (__ballot(om != 0));
+                    }
+                    cn = 0;
+                    wave_sync();
+                }
+                if (done) break;
+                check(last && r_from >= r_to ? 1 : 64);
+            }
+
+            // ---- the unit's last group: its matches in (pos, id) order
+            if (last) {
+                const ScanArgs &r = again(a);
+                uint2 *spill = r.spill + 2ull * cc.u * r.spill_cap;
+                if (mn <= kGMatch)
+                    emit_unit(r, cc.u, ubase, wm, mn, (uint2 *)wbase, ut);
+                else if (mn <= r.spill_cap)
+                    emit_spilled(r, cc.u, ubase, wm, kGMatch, spill, spill + r.spill_cap, mn, cc.n * kChunk, (uint32_t *)wbase,
+                                 (uint32_t *)(wbase + 1024), ut);
+                else
+                    redo_unit(r, cc.u, ubase, cc.n * kChunk, ut, ut_end);
+                mn = 0;
+                wave_sync();
+            }
+            wait_loads();
+        }
+        cc = pc;
+    }
+}
+
+// ------------------------------------------------------------------ launchers
+
+static const void *gram_fn(int s) {
+    return s == 4 ? (const void *)scan_grams<4> : s == 2 ? (const void *)scan_grams<2> : (const void *)scan_grams<1>;
+}
+
+void gram_lds_layout(ScanArgs &a, uint32_t waves) {
+    a.off_wave = 4u << a.im.gram_lw;
+    // the queue's and the starts' place is also where a unit's matches are
+    // sorted (kGMatch entries, or 256 + 64 words)
+    static_assert(8 * kGMatch <= 8 * kGQ && 4 * (256 + 64) <= 8 * kGQ + 3 * kGC, "sort area");
+    a.wave_bytes = 8 * kGQ + 3 * kGC + 8 * kGMatch;
+    a.lds_total = a.off_wave + waves * a.wave_bytes;
+}
+
+hipError_t prepare_gram_kernel(int s, uint32_t lds_bytes) {
+    // the bitmap is addressed at LDS address 0: no static LDS in front of it
+    hipFuncAttributes attr;
+    hipError_t e = hipFuncGetAttributes(&attr, gram_fn(s));
+    if (e != hipSuccess) return e;
+    if (attr.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
+    return hipFuncSetAttribute(gram_fn(s), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+}
+
+hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, uint32_t grid, hipStream_t s) {
+    ScanArgs arg = a;
+    void *args[] = {(void *)&arg};
+    const hipError_t e = hipLaunchKernel(gram_fn((int)a.im.gram_s), dim3(grid), dim3(64 * waves), args, a.lds_total, s);
+    if (e != hipSuccess) return e;
+    return hipGetLastError();
+}
+
+}  // namespace pfac

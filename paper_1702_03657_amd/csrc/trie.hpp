@@ -135,6 +135,24 @@ struct DeviceImageHost {
     uint32_t qa = 0, qb = 0, qalph = 0;
     std::vector<uint32_t> q16;
     std::vector<uint16_t> qfp;
+    // Gram filter (every pattern of four bytes or more).  A pattern that
+    // starts at position p spells, at the next multiple t of S (0 <= t - p <
+    // S), a four-byte gram that lies inside it when it has S + 3 bytes or
+    // more; so only every S-th position of a text is tested, against the
+    // grams at offsets 0 .. S-1 of every pattern.  For a gram x (first byte
+    // lowest) h = (x mod 2^16) * kGramC0 + (x >> 16) * kGramC1 mod 2^32 (the
+    // middle bits of the products name the word: the top ones hardly see the
+    // low byte of each half, which text needs):
+    //  - gram: 2^gram_lw words; word (h >> kGramShift) mod 2^gram_lw has bits
+    //    h & 31 and x & 31 set;
+    //  - gfp: 2^gfp_lb buckets of 16 slots (0xffff: empty): for g = x * kPfx4Mul
+    //    bucket g >> (32 - gfp_lb) has one slot with the 12 bits of g below
+    //    those in its upper bits, and in its lower four the offsets o of the
+    //    grams that share them, as bits 1 << o (gfp_lb = 0: no slots).
+    uint32_t gram_s = 0;               // S: 4, 2 or 1 (0 = no gram filter)
+    uint32_t gram_lw = 0, gfp_lb = 0;
+    std::vector<uint32_t> gram;
+    std::vector<uint16_t> gfp;
 };
 
 // Multiplicative (Fibonacci) hashing, Knuth TAOCP vol. 3, 6.4: odd
@@ -143,6 +161,8 @@ constexpr uint32_t kQ16Mul = 0x9E3779u;     // 24-bit multiplier (one 24 x 24-bi
 constexpr uint32_t kPfx4Mul = 0x9E3779B1u;  // 32-bit multiplier
 constexpr uint32_t kPfx4M1 = 0x9E3779u;     // 24-bit multipliers of the prefix-4 filter
 constexpr uint32_t kPfx4M2 = 0x7F4A7Du;
+constexpr uint32_t kGramC0 = 0x9E37u, kGramC1 = 0xC2B3u;  // 16-bit multipliers of the gram filter
+constexpr uint32_t kGramShift = 10;                       // ... and the bits below its word index
 
 // Derives the device image from the CRS trie for a level index of at most
 // `index_bits` bits and a prefix filter of `fold_bits` (0, 8 or 16) bits per

@@ -585,10 +585,81 @@ static void build_dag(const CrsTrie &T, DeviceImageHost &I) {
     I.chain.assign(40, 0);
 }
 
+// Gram filter: the four-byte grams at offsets 0 .. S-1 of every pattern.  A
+// larger S tests fewer positions but puts S grams per pattern into a bitmap
+// that LDS bounds at 2^20 bits; past 2^18 grams a smaller S leaves fewer
+// false positives per byte (two bits a gram: 28% of the positions tested at
+// 400,000 grams, 10% at 200,000), and past 2^19 first grams none is built.
+static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
+    if (!T.k || T.min_len < 4) return;
+    auto level = [&](uint32_t d) { return T.level_start[d + 1] - T.level_start[d]; };
+    uint32_t S = T.min_len >= 7 ? 4 : T.min_len >= 5 ? 2 : 1;
+    uint64_t n = 0;
+    for (;; S /= 2) {
+        n = 0;
+        for (uint32_t o = 0; o < S; o++) n += level(o + 4);  // at most so many distinct grams at offset o
+        if (S == 1 || n <= (1u << 18)) break;
+    }
+    if (n > (1u << 19)) return;
+    // small alphabets: past a quarter of all grams the filter keeps too much
+    const double all = (double)I.alphabet * I.alphabet * I.alphabet * I.alphabet;
+    if (4.0 * (double)n > all) return;
+    uint32_t lg = 12;  // bits of the bitmap: 24 a gram, at most 2^20
+    while (lg < 20 && (1ull << lg) < 24 * n) lg++;
+    I.gram_s = S;
+    I.gram_lw = lg - 5;
+    I.gram.assign(1u << I.gram_lw, 0);
+    auto each_gram = [&](auto &&f) {
+        for (uint32_t o = 0; o < S; o++)
+            for (uint32_t v = T.level_start[o + 4]; v < T.level_start[o + 5]; v++) {
+                const uint8_t *p = T.pat_data.data() + T.pat_off[T.rep[v]] + o;
+                f((uint32_t)p[0] | (uint32_t)p[1] << 8 | (uint32_t)p[2] << 16 | (uint32_t)p[3] << 24, o);
+            }
+    };
+    each_gram([&](uint32_t x, uint32_t) {
+        const uint32_t h = (x & 0xffffu) * kGramC0 + (x >> 16) * kGramC1;
+        I.gram[(h >> kGramShift) & ((1u << I.gram_lw) - 1u)] |= (1u << (h & 31)) | (1u << (x & 31));
+    });
+    // buckets of 16 slots: about three grams each, more buckets while one overflows
+    uint32_t lb = 1;
+    while ((1ull << lb) * 3 < n) lb++;
+    bool put_all = false;
+    for (const uint32_t top = std::min(lb + 3, 20u); !put_all && lb <= top; lb++) {
+        I.gfp_lb = lb;
+        I.gfp.assign((size_t)16 << lb, 0xffffu);
+        std::vector<uint8_t> used_slots((size_t)1 << lb, 0);
+        put_all = true;
+        each_gram([&](uint32_t x, uint32_t o) {
+            const uint32_t g = x * kPfx4Mul;
+            uint16_t *bk = I.gfp.data() + ((size_t)(g >> (32 - lb)) << 4);
+            uint8_t &n_used = used_slots[g >> (32 - lb)];
+            const uint32_t fp = (g >> (20 - lb)) & 0xfffu;
+            uint32_t i = 0;
+            while (i < n_used && (uint32_t)(bk[i] >> 4) != fp) i++;
+            if (i == 16) {
+                put_all = false;
+                return;
+            }
+            if (i == n_used) {
+                bk[i] = (uint16_t)(fp << 4);
+                n_used++;
+            }
+            bk[i] = (uint16_t)(bk[i] | 1u << o);
+        });
+    }
+    if (!put_all) {  // every offset of a gram is walked
+        I.gfp_lb = 0;
+        I.gfp.clear();
+    }
+}
+
 void pack_image(const CrsTrie &T, uint32_t index_bits, uint32_t fold_bits, uint32_t trunc_depth,
                 uint32_t dag, DeviceImageHost &I) {
     pack_core(T, index_bits, fold_bits, dag ? 0u : trunc_depth, I);
-    if (dag) build_dag(T, I);
+    if (dag)
+        build_dag(T, I);
+    else if (!I.trunc_depth)
+        build_grams(T, I);
 }
 
 }  // namespace pfac

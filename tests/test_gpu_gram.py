@@ -1,0 +1,116 @@
+"""The gram kernel (launches whose kernel the library chooses, patterns of
+four bytes or more) against the oracle, record by record: each distance of
+test positions, texts at odd addresses whose ends fall inside a chunk, starts
+at every offset around a unit's edge, batches of tiny and empty texts, matches
+past the LDS list of a unit and past its list in global memory."""
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_1702_03657_amd as pf
+from tests.gpu_util import assert_same, gpu_scan, gpu_scan_batch, say
+
+pytestmark = pytest.mark.gpu
+
+MiB = 1 << 20
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    pf.load()
+
+
+def _patterns(rng, k, lo, hi, alphabet):
+    return [bytes(rng.choice(alphabet, int(rng.integers(lo, hi + 1))).astype(np.uint8)) for _ in range(k)]
+
+
+BYTES = np.arange(256)
+LOWER = np.arange(97, 123)
+
+
+# shortest pattern 4 tests every position, 5 and 6 every second, 7 and more
+# every fourth; 16 KiB units and 64 KiB units
+@pytest.mark.parametrize("lo,alphabet,n,pad", [
+    (4, BYTES, 8 * MiB + 1, 0), (5, BYTES, 8 * MiB + 1023, 1), (6, BYTES, 9 * MiB + 7, 13),
+    (7, BYTES, 8 * MiB, 15), (8, BYTES, 40 * MiB + 4093, 3), (4, LOWER, 8 * MiB + 77, 2), (7, LOWER, 9 * MiB, 9),
+])
+def test_one_text(lo, alphabet, n, pad):
+    rng = np.random.default_rng(lo * 100 + pad)
+    pats = _patterns(rng, 1500, lo, lo + 24, alphabet)
+    text = rng.choice(alphabet, n).astype(np.uint8)
+    for q in range(n // 3000):  # whole copies and copies cut short
+        p = np.frombuffer(pats[int(rng.integers(0, len(pats)))], dtype=np.uint8)
+        at = int(rng.integers(0, n - p.size))
+        m = p.size if q % 4 else int(rng.integers(1, p.size + 1))
+        text[at:at + m] = p[:m]
+    for at in (0, 1, 2, 3, 5, 6):  # both ends of the text
+        p = np.frombuffer(pats[at], dtype=np.uint8)
+        if at == 0:
+            text[:p.size] = p
+        elif at == 1:
+            text[n - p.size:] = p
+    for e in range(16, 4096, 16):  # starts around the edges of units
+        p = np.frombuffer(pats[e % len(pats)], dtype=np.uint8)
+        at = e * 1024 - pad + e // 16 % 8 - 4
+        if at + p.size <= n:
+            text[at:at + p.size] = p
+    want = oracle.bucketed(text, pats, threads=8)
+    say(f"gram lo={lo} n={n} pad={pad}: {want.n} matches")
+    got, counts = gpu_scan(pf.Trie(pats), text, pad_front=pad)
+    assert_same(got, want)
+    assert np.array_equal(counts, oracle.counts(n, want))
+
+
+@pytest.mark.parametrize("lo,most,graph", [(4, 40, 0), (5, 300, 3), (8, 3000, 0), (9, 70_000, 2)])
+def test_batch(lo, most, graph):
+    rng = np.random.default_rng(lo)
+    pats = _patterns(rng, 900, lo, lo + 20, np.arange(32, 48))
+    lens = []
+    while sum(lens) < 8 * MiB + 100:
+        lens += rng.integers(0, most, 4000).tolist() + [0, 0, 1, 2, 3]
+    lens = lens[:next(i for i, t in enumerate(np.cumsum(lens)) if t > 8 * MiB + 50) + 1]
+    offs = np.zeros(len(lens) + 1, dtype=np.uint64)
+    offs[1:] = np.cumsum(lens)
+    n = int(offs[-1])
+    text = rng.choice(np.arange(32, 48), n).astype(np.uint8)
+    for _ in range(n // 1000):
+        p = np.frombuffer(pats[int(rng.integers(0, len(pats)))], dtype=np.uint8)
+        at = int(rng.integers(0, n - p.size))
+        text[at:at + p.size] = p
+    want = oracle.bucketed(text, pats, offsets=offs, threads=8)
+    say(f"gram batch lo={lo}: {len(lens)} texts, {n} bytes, {want.n} matches")
+    got, cnt = gpu_scan_batch(pf.Trie(pats), text, offs, pad_front=lo, graph_replays=graph)
+    assert cnt == want.n
+    for g in (got if graph else [got]):
+        assert_same(g, want, with_text=True)
+
+
+@pytest.mark.parametrize("lo", [4, 5, 7])
+@pytest.mark.parametrize("density", ["spill", "redo", "nested"])
+def test_dense_matches(lo, density):
+    """Stretches of many matches in units that hold few elsewhere."""
+    rng = np.random.default_rng(lo)
+    n = 8 * MiB + 333
+    text = rng.integers(0, 200, n).astype(np.uint8)
+    if density == "nested":
+        pats = [b"\xff" * m for m in range(lo, lo + 9)] * 2 + [b"\xfe" * lo + b"\xff"]
+        for at in (5000, 2 * MiB + 1, n - 3000):
+            text[at:at + 2500] = 0xff
+    else:
+        pats = _patterns(rng, 40, lo, lo + 3, np.arange(200, 256))
+        step = 40 if density == "spill" else 11
+        for lo_at in (0, 3 * MiB + 1):  # past 80 matches a unit, past 32 a KiB
+            for q in range(3000):
+                p = np.frombuffer(pats[q % len(pats)], dtype=np.uint8)
+                at = lo_at + q * step
+                text[at:at + p.size] = p
+    want = oracle.bucketed(text, pats, threads=8)
+    say(f"gram dense {density} lo={lo}: {want.n} matches")
+    got, counts = gpu_scan(pf.Trie(pats), text)
+    assert_same(got, want)
+    assert np.array_equal(counts, oracle.counts(n, want))
