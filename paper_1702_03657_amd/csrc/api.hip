@@ -113,6 +113,9 @@ struct pfac_workspace {
     // launch shape of the last main scan kernel (grid, block, dynamic LDS):
     // graphs find its node by it
     uint32_t main_grid = 0, main_block = 0, main_lds = 0;
+    // A launch failed after the scan's kernels were (partly) queued: the
+    // staging cursor, which every finisher leaves at zero, may not be.
+    bool cursor_stale = false;
     // misc: [0] stage cursor, [1] running total, [2] per-launch count
     unsigned long long *cursor() { return (unsigned long long *)misc.p; }
     unsigned long long *running() { return (unsigned long long *)misc.p + 1; }
@@ -176,7 +179,9 @@ static int upload_image(pfac_trie *t) {
     size_t o_ldag = align256(o_rlist + std::max<size_t>(I.rank_list.size(), 2) * 4);
     size_t o_gram = align256(o_ldag + std::max<size_t>(I.lvl_dag.size(), 2) * 4);
     size_t o_gfp = align256(o_gram + I.gram.size() * 4);
-    size_t total = align256(o_gfp + I.gfp.size() * 2);
+    size_t o_grec = align256(o_gfp + I.gfp.size() * 2);
+    size_t o_gpat = align256(o_grec + I.grec.size() * 4);
+    size_t total = align256(o_gpat + I.gpat.size());
     auto t0 = std::chrono::steady_clock::now();
     // the new image is built beside the old one, which stays usable if this fails
     DeviceBuf fresh;
@@ -228,6 +233,10 @@ static int upload_image(pfac_trie *t) {
             CP(hipMemcpy(b + o_gram, I.gram.data(), I.gram.size() * 4, hipMemcpyHostToDevice));
         if (!I.gfp.empty())
             CP(hipMemcpy(b + o_gfp, I.gfp.data(), I.gfp.size() * 2, hipMemcpyHostToDevice));
+        if (!I.grec.empty())
+            CP(hipMemcpy(b + o_grec, I.grec.data(), I.grec.size() * 4, hipMemcpyHostToDevice));
+        if (!I.gpat.empty())
+            CP(hipMemcpy(b + o_gpat, I.gpat.data(), I.gpat.size(), hipMemcpyHostToDevice));
         return hipSuccess;
     };
 #undef CP
@@ -278,6 +287,8 @@ static int upload_image(pfac_trie *t) {
     v.dag = I.dag;
     v.gram = (const uint32_t *)(b + o_gram);
     v.gfp = (const uint4 *)(b + o_gfp);
+    v.grec = (const uint4 *)(b + o_grec);
+    v.gpat = b + o_gpat;
     v.gram_s = I.gram_s;
     v.gram_lw = I.gram_lw;
     v.gfp_lb = I.gfp_lb;
@@ -897,11 +908,18 @@ static int enqueue_scan(const Launch &L, bool reserve) {
     if (wave_kernel && n_plan >= (1ull << 31)) return PFAC_EINVAL;
 
     a.n_sums = n_sums;
-    // the split filter kernel clears the block sums and the cursor itself
-    if (!(split && !gram && n_tiles)) HIP_TRY(launch_reset(a.stage_cursor, a.blocksum, n_sums, L.s));
+    if (n_tiles <= kCountUnits) a.blocksum = nullptr;
+    // (the split filter kernel clears the block sums and the cursor itself)
+    if ((a.blocksum || w->cursor_stale) && !(split && !gram && n_tiles))
+        HIP_TRY(launch_reset(a.stage_cursor, a.blocksum, a.blocksum ? n_sums : 0, L.s));
+    w->cursor_stale = true;  // until the finisher is queued
     if (L.counts) HIP_TRY(launch_fill_u32(L.counts, L.total, 0, L.s));
     if (n_tiles) {
-        if (L.offsets)
+        // the gram kernel's plan: the text of each unit's first start
+        if (L.offsets && gram)
+            HIP_TRY(launch_plan(L.offsets, L.n_texts, shift + a.im.gram_s - 1, n_tiles, h.tile,
+                                (uint32_t *)w->tile_first.p, nullptr, L.s));
+        else if (L.offsets)
             HIP_TRY(launch_plan(L.offsets, L.n_texts, shift, n_plan, plan_unit,
                                 (uint32_t *)w->tile_first.p, (uint2 *)a.chunk_info, L.s));
         int per_cu = (int)tn.wg_per_cu;
@@ -958,7 +976,9 @@ static int enqueue_scan(const Launch &L, bool reserve) {
     f.base_dev = L.base_dev;
     f.inline_stage = a.inline_stage;
     f.inline_cap = a.inline_cap;
+    f.cursor = a.stage_cursor;
     HIP_TRY(launch_finish(f, L.s));
+    w->cursor_stale = false;
     return PFAC_OK;
 }
 
@@ -993,11 +1013,12 @@ static __device__ __align__(256) uint8_t scratch[kNoAllocScratch];
 constexpr int kMaxDevices = 256;
 static std::mutex g_scratch_mu;
 static uint8_t *g_scratch_dev[kMaxDevices] = {};
+static std::atomic<bool> g_scratch_stale[kMaxDevices];  // see pfac_workspace::cursor_stale
 
 // The scratch's device address on the current device, looked up once per
 // device with that device current.
-static int noalloc_scratch(uint8_t **out) {
-    int dev = 0;
+static int noalloc_scratch(uint8_t **out, int &dev) {
+    dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) return PFAC_EINVAL;
     std::lock_guard<std::mutex> lock(g_scratch_mu);
@@ -1022,7 +1043,8 @@ extern "C" int pfac_scan_noalloc(const pfac_trie *t, const uint8_t *text_dev, ui
     if (h.ws_units() > (1ull << 40) || capacity > (1ull << 40)) return PFAC_EINVAL;
     const WsSizes z = ws_sizes(h.ws_units(), capacity, h.split);
     uint8_t *base = nullptr;
-    int rc = noalloc_scratch(&base);
+    int dev = 0;
+    int rc = noalloc_scratch(&base, dev);
     if (rc != PFAC_OK) return rc;
     pfac_workspace w{};
     uint64_t off = 0;
@@ -1048,7 +1070,10 @@ extern "C" int pfac_scan_noalloc(const pfac_trie *t, const uint8_t *text_dev, ui
              nullptr, (hipStream_t)stream};
     // every buffer is in place: the scan allocates nothing (the DeviceBufs
     // are not owned and are dropped without release)
-    return enqueue_scan(L, false);
+    w.cursor_stale = g_scratch_stale[dev].load();
+    rc = enqueue_scan(L, false);
+    g_scratch_stale[dev].store(w.cursor_stale);
+    return rc;
 }
 
 extern "C" int pfac_scan_sync(const pfac_trie *t, pfac_workspace *w, const uint8_t *text_dev,
@@ -1233,6 +1258,7 @@ extern "C" int pfac_graph_create_batch(const pfac_trie *t, pfac_workspace *w,
     const bool timed = w && w->ev_start && w->ev_stop;
     for (int method = timed ? 0 : 2; method <= 2; method++) {
         g->ws->ev_start = g->ws->ev_stop = nullptr;
+        g->ws->cursor_stale = false;  // (a failed attempt ran nothing)
         g->n_start = g->n_stop = nullptr;
         rc = PFAC_OK;
         if (method < 2) {

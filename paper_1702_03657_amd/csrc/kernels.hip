@@ -295,7 +295,7 @@ __global__ __launch_bounds__(kWG) void scan_tiles(const ScanArgs a) {
                 const unsigned long long base = atomicAdd(a.stage_cursor, (unsigned long long)total);
                 a.unit_count[t] = total;
                 a.unit_off[t] = base;
-                atomicAdd(&a.blocksum[t >> kSumShift], (unsigned long long)total);
+                if (a.blocksum) atomicAdd(&a.blocksum[t >> kSumShift], (unsigned long long)total);
                 s_base = base;
             }
             __syncthreads();
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kWG) void scan_tiles(const ScanArgs a) {
                 const unsigned long long base = atomicAdd(a.stage_cursor, (unsigned long long)total);
                 a.unit_count[t] = total;
                 a.unit_off[t] = base;
-                atomicAdd(&a.blocksum[t >> kSumShift], (unsigned long long)total);
+                if (a.blocksum) atomicAdd(&a.blocksum[t >> kSumShift], (unsigned long long)total);
                 s_base = base;
             }
             __syncthreads();
@@ -348,30 +348,32 @@ __global__ __launch_bounds__(kWG) void scan_tiles(const ScanArgs a) {
 
 // ---------------------------------------------------------------- finisher
 
-// One workgroup per block-sum entry (1 << kSumShift units): the units'
-// records go to out[] in unit order.  The workgroup's first output slot is
-// the sum of the block sums before it; its first wave scans the units'
+// One workgroup per 1 << kSumShift units: the units' records go to out[] in
+// unit order.  The workgroup's first output slot is the sum of the counts (or
+// block sums) before it; its first wave scans the units'
 // counts, then every thread copies records, each finding its unit by binary
 // search over the unit starts.
 __global__ __launch_bounds__(kWG) void finish_tiles(const FinishArgs f) {
     constexpr uint32_t kUnits = 1u << kSumShift;
     static_assert(kUnits <= 64, "one wave scans the units");
-    __shared__ unsigned long long s_red[2][kWG / 64];
+    __shared__ unsigned long long s_red[kWG / 64];
     __shared__ uint32_t s_start[kUnits + 1];
     __shared__ const pfac_match *s_from[kUnits];
     const uint32_t tid = threadIdx.x, b = blockIdx.x;
-    unsigned long long pre = 0, all = 0;
-    for (uint32_t i = tid; i < f.n_sums; i += kWG) {
-        const unsigned long long s = f.blocksum[i];
-        all += s;
-        if (i < b) pre += s;
+    // records of the units before this block's (pre), and of all units (only
+    // the last block needs it: pre + its own)
+    unsigned long long pre = 0;
+    if (f.blocksum) {
+        for (uint32_t i = tid; i < b; i += kWG) pre += f.blocksum[i];
+    } else {
+        const uint4 *c4 = (const uint4 *)f.unit_count;
+        for (uint32_t i = tid; i < b * (kUnits / 4); i += kWG) {
+            const uint4 c = c4[i];
+            pre += (unsigned long long)c.x + c.y + c.z + c.w;
+        }
     }
     pre = wave_reduce_u64(pre);
-    all = wave_reduce_u64(all);
-    if ((tid & 63) == 0) {
-        s_red[0][tid >> 6] = pre;
-        s_red[1][tid >> 6] = all;
-    }
+    if ((tid & 63) == 0) s_red[tid >> 6] = pre;
     if (tid < 64) {
         const uint64_t t = ((uint64_t)b << kSumShift) + tid;
         const uint32_t cnt = (tid < kUnits && t < f.n_tiles) ? f.unit_count[t] : 0u;
@@ -392,12 +394,11 @@ __global__ __launch_bounds__(kWG) void finish_tiles(const FinishArgs f) {
     }
     __syncthreads();
     pre = 0;
-    all = 0;
-    for (uint32_t i = 0; i < kWG / 64; i++) {
-        pre += s_red[0][i];
-        all += s_red[1][i];
+    for (uint32_t i = 0; i < kWG / 64; i++) pre += s_red[i];
+    if (b == f.n_sums - 1 && tid == 0) {
+        *f.n_matches = pre + s_start[kUnits];
+        *f.cursor = 0;  // no scan of this stream uses it any more
     }
-    if (b == 0 && tid == 0) *f.n_matches = all;
     const uint64_t base = pre + (f.base_dev ? *f.base_dev : 0ull);
     const uint32_t total = s_start[kUnits];
     for (uint32_t r = tid; r < total; r += kWG) {

@@ -12,6 +12,12 @@ namespace pfac {
 constexpr uint32_t kWG = 256;            // threads per workgroup (4 waves of 64)
 constexpr uint32_t kMatchCap = 256;      // matched positions a tile sorts in LDS
 constexpr uint32_t kSumShift = 5;        // units per block-sum entry and finisher workgroup = 32
+// Up to this many units the finisher sums the counts of all units before its
+// own (4 bytes each, from L2); past it the scan kernels keep a sum per 32
+// units, which costs an atomic per unit with matches and a kernel that clears
+// them.  On MI355X, 32,000 units: 12 us of a scan's atomics and 5 us of
+// clearing against 4 us more in the finisher.
+constexpr uint64_t kCountUnits = 1u << 16;
 constexpr uint32_t kHaloCap = 1024;      // most halo bytes staged in LDS
 constexpr uint32_t kInlineCap = 8;       // records a wave unit stages without an atomic (at least)
 constexpr uint32_t kInlinePerChunk = 2;  // ... and per 1 KiB chunk of the unit
@@ -49,7 +55,9 @@ struct ImageView {
     uint32_t qa, qb, qalph, q16_mul;  // its symbol map, alphabet bytes and hash multiplier
     uint32_t top_nodes, top_rw;       // bitmapped top nodes: count, words per node
     const uint32_t *gram;     // gram filter: bitmap words (2^gram_lw)
-    const uint4 *gfp;         // gram filter: buckets of 16 x 16-bit slots (2^gfp_lb; 0 = none)
+    const uint4 *gfp;         // gram filter: buckets of 14 slots and a record number (2^gfp_lb; 0 = none)
+    const uint4 *grec;        // gram filter: a record per slot
+    const uint8_t *gpat;      // gram filter: the patterns' bytes
     uint32_t gram_s, gram_lw, gfp_lb, min_len;
 };
 
@@ -85,7 +93,7 @@ struct ScanArgs {
     unsigned long long *stage_cursor;
     uint32_t *unit_count;             // per tile
     unsigned long long *unit_off;     // per tile
-    unsigned long long *blocksum;     // per 1 << kSumShift units
+    unsigned long long *blocksum;     // per 1 << kSumShift units, or NULL: the finisher sums the units' counts
     uint32_t *counts;                 // optional per-position counts
     pfac_match *inline_stage;         // wave kernel: inline_cap records per chunk
     uint64_t inline_cap;
@@ -105,7 +113,7 @@ struct ScanArgs {
 struct FinishArgs {
     const uint32_t *unit_count;
     const unsigned long long *unit_off;
-    const unsigned long long *blocksum;
+    const unsigned long long *blocksum;  // or NULL: sum the counts of the units before
     const pfac_match *stage;
     uint64_t stage_cap;
     uint64_t n_tiles;
@@ -116,11 +124,13 @@ struct FinishArgs {
     const unsigned long long *base_dev;  // optional device value added to every output index
     const pfac_match *inline_stage;   // units with unit_off == ~0 keep their records here
     uint64_t inline_cap;
+    unsigned long long *cursor;       // the staging cursor, cleared for the next scan
 };
 
 // LDS bytes and section offsets for a tile of `bpl` bytes per lane.
 void lds_layout(ScanArgs &a, uint32_t bpl);
 
+// Clears the staging cursor and the block sums (NULL: none).
 hipError_t launch_reset(unsigned long long *stage_cursor, unsigned long long *blocksum,
                         uint32_t n_sums, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);

@@ -17,10 +17,13 @@
 //     gram again later would double the HBM traffic, since the text streams
 //     through L2 faster than the queue fills;
 //   * 64 queued grams at a time are checked against 16-bit slots in global
-//     memory (L2), which also give the offsets of a gram in its patterns, that
-//     is the starts;
-//   * starts are walked from their depth-K node; matches of a unit collect in
-//     LDS, past kGMatch in global memory, and are staged in (pos, id) order.
+//     memory (L2);
+//   * a slot's record gives the offset of the gram in its pattern, that is the
+//     start, and the pattern, which is compared with the text in one go; a
+//     gram of several patterns has its possible starts walked from their
+//     depth-K nodes;
+//   * matches of a unit collect in LDS, past kGMatch in global memory, and are
+//     staged in (pos, id) order.
 // Unit u holds the starts from S - 1 before its first test position to S - 1
 // before its end, so no start is seen by two units.
 #include <hip/hip_runtime.h>
@@ -30,11 +33,13 @@
 
 namespace pfac {
 
-constexpr uint32_t kGQ = 144;     // grams in a wave's queue, 8 bytes each
-constexpr uint32_t kGC = 128;     // grams in its list of starts: 2 + 1 bytes each
+constexpr uint32_t kGQ = 120;     // grams in a wave's queue, 8 bytes each
+constexpr uint32_t kGC = 92;      // grams in its list of starts: 4 + 2 bytes each
 constexpr uint32_t kGMatch = 64;  // matches of a unit in LDS
 
 typedef __attribute__((address_space(3))) const uint32_t lds_word_t;
+typedef __attribute__((address_space(4))) const uint32_t scalar_u32_t;
+typedef __attribute__((address_space(4))) const uint64_t scalar_u64_t;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const u32x2 lds_pair_t;
@@ -46,6 +51,11 @@ __device__ __forceinline__ uint32_t gram_hash(uint32_t x) {
     a.w = x;
     c.w = kGramC0 | kGramC1 << 16;
     return __builtin_amdgcn_udot2(a.h, c.h, 0u, false);
+}
+
+// at + the set bits of m below the lane
+__device__ __forceinline__ uint32_t mbcnt_from(unsigned long long m, uint32_t at) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, at));
 }
 
 // the lesser of each 16-bit half
@@ -73,20 +83,65 @@ __device__ __forceinline__ const ScanArgs &again(const ScanArgs &a) {
 // (the compiler would set the loop's waits for that path).
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
-// The text holding frame position p: its index, start and end.  p lies in the
-// frame's valid range.
+// The texts of one unit's starts: the one text they all lie in (known), or
+// the range [lo, hi) of texts and the lanes' first 64 starts of it.
+struct UnitTexts {
+    bool known = false;
+    uint32_t tid = 0, lo = 0, hi = 0;
+    uint64_t start = 0, end = 0;  // of the one text
+    uint64_t at = 0;              // the lane's: start of text lo + lane (frame position)
+};
+
+// Texts of unit u, whose starts begin at frame position ubase.
+__device__ __forceinline__ UnitTexts unit_texts(const ScanArgs &a, uint32_t u, uint64_t ubase) {
+    UnitTexts t;
+    if (!a.offsets) {
+        t.known = true;
+        t.start = a.shift;
+        t.end = a.shift + a.total;
+        return t;
+    }
+    // (scalar loads: they do not wait for the chunks in flight)
+    const scalar_u32_t *first = (const scalar_u32_t *)(uintptr_t)a.tile_first_text;
+    const scalar_u64_t *off = (const scalar_u64_t *)(uintptr_t)a.offsets;
+    t.lo = first[u];
+    t.hi = (u + 1 < (uint32_t)a.n_tiles ? first[u + 1] : a.n_texts - 1) + 1;
+    if (t.hi - t.lo == 1) {
+        t.tid = t.lo;
+        t.start = off[t.lo] + a.shift;
+        t.end = off[t.lo + 1] + a.shift;
+        // (starts before the first text's are refused by their position)
+        t.known = true;
+    } else {
+        t.at = a.offsets[min(t.lo + lane_id(), a.n_texts)] + a.shift;
+    }
+    return t;
+}
+
+// The text holding frame position p (of the unit's starts, inside the frame's
+// valid range): its index, start and end.  Every lane of the wave calls it at
+// once; a lane without such a position gets any text.
 struct TextSpan {
     uint32_t tid;
     uint64_t start, end;
 };
 
-__device__ __forceinline__ TextSpan text_span(const ScanArgs &a, uint64_t p) {
-    if (!a.offsets) return TextSpan{0u, a.shift, a.shift + a.total};
-    const uint64_t c = p >> a.plan_shift;
-    const uint32_t lo = a.tile_first_text[c];
-    const uint32_t hi = (c + 1 < a.n_plan ? a.tile_first_text[c + 1] : a.n_texts - 1) + 1;
-    const uint32_t tid = text_of(a.offsets, lo, hi, a.shift, p);
-    return TextSpan{tid, a.offsets[tid] + a.shift, a.offsets[tid + 1] + a.shift};
+__device__ __forceinline__ TextSpan text_span(const ScanArgs &a, uint64_t p, const UnitTexts &t) {
+    if (t.known) return TextSpan{t.tid, t.start, t.end};
+    uint32_t i;
+    if (t.hi - t.lo < 64) {
+        // among the starts that the lanes hold (those past hi lie past p):
+        // the largest r with start(lo + r) <= p
+        uint32_t r = 0;
+        for (uint32_t step = 32; step > 0; step >>= 1) {
+            const uint64_t v = __shfl(t.at, (int)(r + step), 64);
+            if (v <= p && r + step < t.hi - t.lo) r += step;
+        }
+        const uint64_t s0 = __shfl(t.at, (int)r, 64), s1 = __shfl(t.at, (int)(r + 1), 64);
+        return TextSpan{t.lo + r, s0, s1};
+    }
+    i = text_of(a.offsets, t.lo, t.hi, a.shift, p);
+    return TextSpan{i, a.offsets[i] + a.shift, a.offsets[i + 1] + a.shift};
 }
 
 // Walk for the start p whose text ends at `end` (end - p >= the shortest
@@ -113,13 +168,63 @@ __device__ __forceinline__ uint2 walk_start(const ImageView &im, const uint8_t *
     return walk_g(im, base, p, (uint32_t)umin64(lim, 0xffffffffull), v, K, hi_valid);
 }
 
-// A start's pattern list (0 ids: no match), for starts in any order.
-__device__ __forceinline__ uint2 scan_start(const ScanArgs &a, uint64_t p, const UnitText &ut, uint64_t ut_end) {
-    const uint64_t lo_valid = a.shift, hi_valid = a.shift + a.total;
-    if (p < lo_valid || p >= hi_valid) return make_uint2(0, 0);
-    const uint64_t end = ut.known ? ut_end : text_span(a, p).end;
-    if (end - p < a.im.min_len) return make_uint2(0, 0);
-    return walk_start(a.im, a.base, p, end, hi_valid);
+// A start's pattern list (0 ids: no match), for starts in any order; `in`:
+// the lane has one.
+__device__ __forceinline__ uint2 scan_start(const ScanArgs &a, bool in, uint64_t p, const UnitTexts &ut) {
+    const TextSpan t = text_span(a, p, ut);
+    // (a start before the text wraps around)
+    if (!in || p - a.shift >= a.total || t.end - p < a.im.min_len) return make_uint2(0, 0);
+    return walk_start(a.im, a.base, p, t.end, a.shift + a.total);
+}
+
+// 1 when the text at frame position p equals the `len` pattern bytes at pat
+// (a multiple of four), 0 when not, -1 when its whole loads could pass the
+// text's last 16-byte block (at blk_hi).  64 bytes a round, all in flight.
+__device__ __forceinline__ int equal_pattern(const uint8_t *base, uint64_t p, const uint8_t *pat, uint32_t len,
+                                             uint64_t blk_hi) {
+    const uint64_t p4 = p & ~3ull;
+    if (p4 + (len + 63u) / 64u * 64u + 4 > blk_hi + 16) return -1;
+    const uint32_t sh = (uint32_t)(p & 3);
+    uint32_t diff = 0;
+    for (uint32_t i = 0; i < len; i += 64) {
+        const uint32_t *t32 = (const uint32_t *)(base + p4 + i);
+        const uint32_t *c32 = (const uint32_t *)(pat + i);
+        uint32_t tw[17], cw[16];
+#pragma unroll
+        for (int k = 0; k < 17; k++) tw[k] = t32[k];
+#pragma unroll
+        for (int k = 0; k < 16; k++) cw[k] = c32[k];
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            const int32_t left = (int32_t)(len - i) - 4 * k;
+            const uint32_t mask = left >= 4 ? 0xffffffffu : (left <= 0 ? 0u : ((1u << (8 * left)) - 1u));
+            diff |= (__builtin_amdgcn_alignbyte(tw[k + 1], tw[k], sh) ^ cw[k]) & mask;
+        }
+        if (diff) return 0;
+    }
+    return 1;
+}
+
+// Matches in the kernel's lists: x = unit position | stored list length << 16,
+// y = the list's offset or kGramId | the id of a list of one.
+__device__ __forceinline__ uint2 list_of(const ImageView &im, uint2 e) {
+    const uint32_t n = e.x >> 16;
+    return (e.y & kGramId) ? make_uint2(e.y, 1u) : hit_list(im, make_uint2(e.y, n));
+}
+
+// Write the records of a match at p (`ids` from list_of; none: no match) to
+// dst[idx ..] below cap.
+__device__ __forceinline__ void put(const ScanArgs &a, uint64_t p, uint2 ids, pfac_match *dst, uint64_t idx,
+                                    uint64_t cap, const UnitTexts &ut) {
+    const TextSpan t = text_span(a, p, ut);
+    for (uint32_t k = 0; k < ids.y && idx < cap; k++, idx++) {
+        pfac_match m;
+        m.pos = p - t.start;
+        m.pattern_id = (ids.x & kGramId) ? ids.x & ~kGramId : a.im.pout_ids[ids.x + k];
+        m.text_id = t.tid + a.text_id0;
+        dst[idx] = m;
+    }
+    if (a.counts && ids.y) a.counts[p - a.shift] = ids.y;
 }
 
 // Reserve `total` records of unit u: its inline slots or the staging area.
@@ -132,17 +237,43 @@ __device__ __forceinline__ void reserve_unit(const ScanArgs &a, uint64_t u, uint
         if (!in) b = atomicAdd(a.stage_cursor, (unsigned long long)total);
         a.unit_count[u] = total;
         a.unit_off[u] = in ? ~0ull : b;
-        if (total) atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
+        if (a.blocksum && total) atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
     }
     base = __shfl(b, 0, 64);
     dst = in ? a.inline_stage + u * a.inline_cap : a.stage;
     cap = in ? a.inline_cap : a.stage_cap;
 }
 
+// Stage a unit of at most 64 matches, one a lane: each is ranked by its
+// position against the others (scalar reads of their lanes).
+__device__ __forceinline__ void emit_small(const ScanArgs &a, uint64_t u, uint64_t ubase, const uint2 *wm,
+                                           uint32_t mn, uint2 *sorted, const UnitTexts &ut) {
+    const uint32_t lane = lane_id();
+    if (mn == 0) {
+        if (lane == 0) a.unit_count[u] = 0;
+        return;
+    }
+    const uint2 e = wm[lane];
+    const uint32_t pos = e.x & 0xffffu;
+    uint32_t rk = 0;
+    for (uint32_t q = 0; q < mn; q++)
+        rk += (uint32_t)__builtin_amdgcn_readlane((int)pos, (int)q) < pos ? 1u : 0u;
+    if (lane < mn) sorted[rk] = e;
+    wave_sync();
+    const uint2 f = sorted[lane];
+    const uint2 ids = lane < mn ? list_of(a.im, f) : make_uint2(0, 0);
+    uint32_t total;
+    const uint32_t before = wave_excl_scan(ids.y, total);
+    pfac_match *dst;
+    uint64_t base, cap;
+    reserve_unit(a, u, total, dst, base, cap);
+    put(a, ubase + (f.x & 0xffffu), ids, dst, base + before, cap, ut);
+}
+
 // Unit u again, 64 starts at a time in position order, when its matches
 // overflow both lists: one pass counts, the next emits.
 __device__ __forceinline__ void redo_unit(const ScanArgs &a, uint64_t u, uint64_t ubase, uint32_t n_starts,
-                                          const UnitText &ut, uint64_t ut_end) {
+                                          const UnitTexts &ut) {
     const uint32_t lane = lane_id();
     pfac_match *dst = nullptr;
     uint64_t base = 0, cap = 0;
@@ -151,16 +282,14 @@ __device__ __forceinline__ void redo_unit(const ScanArgs &a, uint64_t u, uint64_
         for (uint32_t r = 0; r < n_starts; r += 64) {
             const uint64_t p = ubase + r + lane;
             uint2 ids = make_uint2(0, 0);
-            if (r + lane < n_starts) {
-                const uint2 h = scan_start(a, p, ut, ut_end);
-                if (h.y) ids = hit_list(a.im, h);
-            }
+            const uint2 h = scan_start(a, r + lane < n_starts, p, ut);
+            if (h.y) ids = hit_list(a.im, h);
             uint32_t t;
             const uint32_t before = wave_excl_scan(ids.y, t);
             if (pass == 0) {
                 total += t;
             } else {
-                if (ids.y) emit(a, p, ids, dst, base + before, cap, ut);
+                put(a, p, ids, dst, base + before, cap, ut);
                 base += t;
             }
         }
@@ -175,7 +304,7 @@ __device__ __forceinline__ void redo_unit(const ScanArgs &a, uint64_t u, uint64_
 // which a last pass emits.
 __device__ __forceinline__ void emit_spilled(const ScanArgs &a, uint64_t u, uint64_t ubase, const uint2 *wm,
                                              uint32_t mcap, const uint2 *spill, uint2 *sorted, uint32_t mn,
-                                             uint32_t n_starts, uint32_t *map, uint32_t *pre, const UnitText &ut) {
+                                             uint32_t n_starts, uint32_t *map, uint32_t *pre, const UnitTexts &ut) {
     const uint32_t lane = lane_id();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     // (two loads, not one through a pointer to either memory)
@@ -210,7 +339,7 @@ __device__ __forceinline__ void emit_spilled(const ScanArgs &a, uint64_t u, uint
                     uint32_t rk = pre[w >> 2] + (uint32_t)__builtin_popcount(map[w] & ((1u << (q & 31u)) - 1u));
                     for (uint32_t k = w & ~3u; k < w; k++) rk += (uint32_t)__builtin_popcount(map[k]);
                     sorted[done + rk] = e;
-                    n = hit_list(a.im, make_uint2(e.y, e.x >> 16)).y;
+                    n = list_of(a.im, e).y;
                 }
             }
             uint32_t t;
@@ -229,11 +358,11 @@ __device__ __forceinline__ void emit_spilled(const ScanArgs &a, uint64_t u, uint
         uint2 e = make_uint2(0, 0), ids = make_uint2(0, 0);
         if (i < mn) {
             e = sorted[i];
-            ids = hit_list(a.im, make_uint2(e.y, e.x >> 16));
+            ids = list_of(a.im, e);
         }
         uint32_t t;
         const uint32_t before = wave_excl_scan(ids.y, t);
-        if (i < mn) emit(a, ubase + (e.x & 0xffffu), ids, dst, base + before, cap, ut);
+        put(a, ubase + (e.x & 0xffffu), ids, dst, base + before, cap, ut);
         base += t;
     }
 }
@@ -256,14 +385,15 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         if (b + lane < n_tab)
             __builtin_amdgcn_global_load_lds((const void *)((const uint4 *)im.gram + b + lane),
                                              (__attribute__((address_space(3))) void *)(lds + 16 * b), 16, 0, 0);
+    if (tid == 0) *(uint32_t *)(lds + a.off_wave + waves * a.wave_bytes) = waves;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
     uint8_t *wbase = lds + a.off_wave + wave * a.wave_bytes;
     uint2 *wq = (uint2 *)wbase;                              // queue: (gram, unit position)
-    uint16_t *wc = (uint16_t *)(wbase + 8 * kGQ);            // starts: unit position of the gram ...
-    uint8_t *wcm = wbase + 8 * kGQ + 2 * kGC;                // ... and its offsets
-    uint2 *wm = (uint2 *)(wbase + 8 * kGQ + 3 * kGC);        // matches
+    uint32_t *wcr = (uint32_t *)(wbase + 8 * kGQ);           // starts: record of the gram's slot ...
+    uint16_t *wcp = (uint16_t *)(wbase + 8 * kGQ + 4 * kGC); // ... and its unit position
+    uint2 *wm = (uint2 *)(wbase + 8 * kGQ + 6 * kGC);        // matches
 
     const uint64_t hi_valid = a.shift + a.total;
     const uint32_t n_u = (uint32_t)a.n_tiles, n_ch = (uint32_t)a.n_plan, G = a.group;
@@ -284,9 +414,18 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         uint32_t u, g, n;  // unit, first chunk of the group, chunks of the unit
     };
     auto start_at = [&](uint32_t u) -> Cur { return Cur{u, 0u, u < n_u ? min(G, n_ch - u * G) : 0u}; };
+    // the workgroup's units are blockIdx.x * waves + (0 .. waves - 1), plus
+    // multiples of the grid's waves; a wave's first one is its own, each next
+    // one is the workgroup's next, so that a wave held up by a cluster of
+    // matches or of small texts ends with fewer units
+    uint32_t *wnext = (uint32_t *)(lds + a.off_wave + waves * a.wave_bytes);
     auto advance = [&](Cur &c) {
         c.g += GC;
-        if (c.g >= c.n) c = start_at(c.u + ustride);
+        if (c.g < c.n) return;
+        uint32_t i = 0;
+        if (lane == 0) i = atomicAdd(wnext, 1u);
+        i = (uint32_t)__builtin_amdgcn_readfirstlane((int)i);
+        c = start_at(i / waves * ustride + blockIdx.x * waves + i % waves);
     };
     auto load = [&](const Cur &c, uint32_t i) -> Slot {
         uint64_t sb = ((uint64_t)c.u * G + c.g) * kChunk;
@@ -317,7 +456,12 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         if (mk == 0) return;
         const uint32_t at = qn;
         qn += (uint32_t)__popcll(mk);
-        if (qn <= kGQ && hit) wq[at + mbcnt(mk)] = make_uint2(x, pos);
+        if (qn > kGQ) return;
+        if (__builtin_amdgcn_inverse_ballot_w64(mk)) {  // the compare's mask as it is
+            uint32_t *q = (uint32_t *)wq + 2 * mbcnt_from(mk, at);
+            q[0] = x;
+            q[1] = pos;
+        }
     };
     // the TL tests of a lane's 16 positions from unit position pos on
     auto tests = [&](const Slot &s, uint32_t pos) {
@@ -331,22 +475,6 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         }
 #pragma unroll
         for (uint32_t j = 0; j < TL; j++) queue(test(ent[j], h[j], x[j]), x[j], pos + j * S);
-    };
-
-    // the text of a batch unit that lies inside one: its starts need no search
-    auto unit_text = [&](uint32_t u, uint32_t n, uint64_t ulo, uint64_t &end) -> UnitText {
-        UnitText ut;
-        const ScanArgs &r = again(a);
-        if (!r.offsets) return ut;
-        const uint64_t c0 = (uint64_t)u * G, c1 = c0 + n;
-        if (c1 >= n_ch) return ut;
-        const uint32_t t0 = r.tile_first_text[c0];
-        if (t0 != r.tile_first_text[c1]) return ut;
-        ut.tid = t0;
-        ut.start = r.offsets[t0] + r.shift;
-        end = r.offsets[t0 + 1] + r.shift;
-        ut.known = ut.start + (S - 1) <= ulo;
-        return ut;
     };
 
     // ---- the unit being scanned
@@ -363,23 +491,23 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     // the loop that empties the queue.
     auto check = [&](uint32_t at_least) __attribute__((always_inline)) {
         if (nb) {
-            // offsets in the slot with the gram's fingerprint
-            uint32_t om = (1u << S) - 1u;
+            // the slot with the gram's fingerprint
+            uint32_t m = 0, base = 0;
             if (lb) {
                 const uint32_t want = gb >> (20u - lb) << 4 & 0xfff0u, w2 = want << 16 | want;
-                uint32_t m = pk_min(fb0.x ^ w2, fb0.y ^ w2);
+                m = pk_min(fb0.x ^ w2, fb0.y ^ w2);
                 m = pk_min(m, pk_min(fb0.z ^ w2, fb0.w ^ w2));
                 m = pk_min(m, pk_min(fb1.x ^ w2, fb1.y ^ w2));
-                m = pk_min(m, pk_min(fb1.z ^ w2, fb1.w ^ w2));
+                m = pk_min(m, fb1.z ^ w2);
                 m = min(m & 0xffffu, m >> 16);
-                om &= m < 16u ? m : 0u;  // (an empty slot may add offsets, which the walk refuses)
+                base = fb1.w;
             }
-            const bool pass = lane < nb && om != 0;
+            const bool pass = lane < nb && m < 14u;
             const unsigned long long mk = __ballot(pass);
             if (pass) {
                 const uint32_t i = cn + mbcnt(mk);
-                wc[i] = (uint16_t)tb;
-                wcm[i] = (uint8_t)om;
+                wcr[i] = base + m;
+                wcp[i] = (uint16_t)tb;
             }
             cn += (uint32_t)__popcll(mk);
             nb = 0;
@@ -433,13 +561,12 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         wave_sync();
         check(64);
         uint32_t ra = 0;  // next test of chunk r_from
-        UnitText ut;
-        uint64_t ut_end = 0;
 
         if (last || r_from < r_to || qn >= 64 || cn > kGC - 64) {
             // ---- empty the queue as far as the next group needs it, and wholly
             // after the unit's last group
-            if (last) ut = unit_text(cc.u, cc.n, ulo, ut_end);
+            const ScanArgs &r = again(a);
+            UnitTexts ut = unit_texts(r, cc.u, ubase);
             for (;;) {
                 if (r_from < r_to && qn + 64 <= kGQ) {
                     const uint32_t pos = gpos + r_from * kChunk + ra;
@@ -459,23 +586,32 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                 }
                 const bool done = r_from >= r_to && (last ? (nb | qn) == 0 : qn < 64);
                 if (cn > kGC - 64 || (last && done)) {
-                    // ---- walk the starts; matches go to LDS, past kGMatch to
-                    // global memory
+                    // ---- compare or walk the starts; matches go to LDS, past
+                    // kGMatch to global memory
                     wave_sync();
-                    const ScanArgs &r = again(a);
                     for (uint32_t c0 = 0; c0 < cn; c0 += 64) {
-                        const bool in = c0 + lane < cn;
-                        const uint32_t t = wc[min(c0 + lane, kGC - 1)] + (uint32_t)(S - 1);
-                        uint32_t om = in ? wcm[min(c0 + lane, kGC - 1)] : 0u;
-                        do {
-                            uint2 h = make_uint2(0, 0);
-                            uint32_t pr = 0;
-                            if (om) {
-                                const uint32_t b = (uint32_t)__builtin_ctz(om);
-                                om &= om - 1;
-                                pr = t - b;
-                                h = scan_start(r, ubase + pr, ut, ut_end);
+                        const uint32_t ci = min(c0 + lane, kGC - 1);
+                        const uint32_t t = wcp[ci];
+                        // (without slots every offset is walked)
+                        uint4 rec = make_uint4(0xffffffffu, (1u << S) - 1u, 0u, 0u);
+                        if (lb && c0 + lane < cn) rec = r.im.grec[wcr[ci]];
+                        uint32_t om = 0;
+                        uint2 h = make_uint2(0, 0);
+                        const uint32_t len = rec.y & 0xffffu;
+                        uint32_t pr = t + (uint32_t)(S - 1) - (rec.y >> 16 & 3u);
+                        const TextSpan ts = text_span(r, ubase + pr, ut);
+                        if (c0 + lane < cn) {
+                            om = rec.x == 0xffffffffu ? rec.y : 0u;
+                            // (a start before the text wraps around)
+                            if (!om && ubase + pr - r.shift < r.total && ts.end - (ubase + pr) >= len) {
+                                const int eq = equal_pattern(r.base, ubase + pr, r.im.gpat + rec.x, len, blk_hi);
+                                if (eq < 0)  // too near the text's end for whole loads
+                                    om = 1u << (rec.y >> 16 & 3u);
+                                else if (eq)
+                                    h = make_uint2(rec.z, rec.y >> 18);
                             }
+                        }
+                        for (;;) {
                             const bool got = h.y != 0;
                             const unsigned long long mk = __ballot(got);
                             if (got) {
@@ -485,30 +621,36 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                                 else if (s - kGMatch < r.spill_cap) r.spill[2ull * cc.u * r.spill_cap + s - kGMatch] = e;
                             }
                             mn += (uint32_t)__popcll(mk);
-                        } while (__ballot(om != 0));
+                            if (__ballot(om != 0) == 0) break;
+                            const bool in = om != 0;
+                            if (in) pr = t + (uint32_t)(S - 1) - (uint32_t)__builtin_ctz(om);
+                            om &= om - 1;
+                            h = scan_start(r, in, ubase + pr, ut);
+                        }
                     }
                     cn = 0;
                     wave_sync();
                 }
                 if (done) break;
-                check(last && r_from >= r_to ? 1 : 64);
+                // (the loop ends: with tests left, either the queue takes one
+                // above or this takes grams from it; then it only shrinks)
+                check(r_from < r_to ? kGQ - 63 : last ? 1 : 64);
             }
 
             // ---- the unit's last group: its matches in (pos, id) order
+            wait_loads();
             if (last) {
-                const ScanArgs &r = again(a);
                 uint2 *spill = r.spill + 2ull * cc.u * r.spill_cap;
                 if (mn <= kGMatch)
-                    emit_unit(r, cc.u, ubase, wm, mn, (uint2 *)wbase, ut);
+                    emit_small(r, cc.u, ubase, wm, mn, (uint2 *)wbase, ut);
                 else if (mn <= r.spill_cap)
                     emit_spilled(r, cc.u, ubase, wm, kGMatch, spill, spill + r.spill_cap, mn, cc.n * kChunk, (uint32_t *)wbase,
                                  (uint32_t *)(wbase + 1024), ut);
                 else
-                    redo_unit(r, cc.u, ubase, cc.n * kChunk, ut, ut_end);
+                    redo_unit(r, cc.u, ubase, cc.n * kChunk, ut);
                 mn = 0;
                 wave_sync();
             }
-            wait_loads();
         }
         cc = pc;
     }
@@ -524,9 +666,10 @@ void gram_lds_layout(ScanArgs &a, uint32_t waves) {
     a.off_wave = 4u << a.im.gram_lw;
     // the queue's and the starts' place is also where a unit's matches are
     // sorted (kGMatch entries, or 256 + 64 words)
-    static_assert(8 * kGMatch <= 8 * kGQ && 4 * (256 + 64) <= 8 * kGQ + 3 * kGC, "sort area");
-    a.wave_bytes = 8 * kGQ + 3 * kGC + 8 * kGMatch;
-    a.lds_total = a.off_wave + waves * a.wave_bytes;
+    static_assert(8 * kGMatch <= 8 * kGQ && 4 * (256 + 64) <= 8 * kGQ + 6 * kGC, "sort area");
+    a.wave_bytes = 8 * kGQ + 6 * kGC + 8 * kGMatch;
+    a.wave_bytes = (a.wave_bytes + 7u) & ~7u;
+    a.lds_total = a.off_wave + waves * a.wave_bytes + 16;
 }
 
 hipError_t prepare_gram_kernel(int s, uint32_t lds_bytes) {

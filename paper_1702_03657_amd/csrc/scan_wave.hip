@@ -173,7 +173,7 @@ __device__ __forceinline__ void unit_from_root(const ScanArgs &a, uint64_t u, ui
                 b = atomicAdd(a.stage_cursor, (unsigned long long)total);
                 a.unit_count[u] = total;
                 a.unit_off[u] = b;
-                if (total) atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
+                if (a.blocksum && total) atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
             }
             base = __shfl(b, 0, 64);
         }
@@ -218,7 +218,8 @@ __global__ __launch_bounds__(1024) void scan_waves(const ScanArgs a) {
     if (SPLIT) {
         const uint32_t gt = blockIdx.x * nthreads + tid;
         if (gt == 0) *a.stage_cursor = 0;
-        for (uint32_t i = gt; i < a.n_sums; i += gridDim.x * nthreads) a.blocksum[i] = 0;
+        if (a.blocksum)
+            for (uint32_t i = gt; i < a.n_sums; i += gridDim.x * nthreads) a.blocksum[i] = 0;
     }
 
     // ---- shared tables, once per workgroup

@@ -145,14 +145,22 @@ struct DeviceImageHost {
     // low byte of each half, which text needs):
     //  - gram: 2^gram_lw words; word (h >> kGramShift) mod 2^gram_lw has bits
     //    h & 31 and x & 31 set;
-    //  - gfp: 2^gfp_lb buckets of 16 slots (0xffff: empty): for g = x * kPfx4Mul
-    //    bucket g >> (32 - gfp_lb) has one slot with the 12 bits of g below
-    //    those in its upper bits, and in its lower four the offsets o of the
-    //    grams that share them, as bits 1 << o (gfp_lb = 0: no slots).
+    //  - gfp: 2^gfp_lb buckets of 32 bytes: 14 16-bit slots and the number of
+    //    the bucket's first record.  For g = x * kPfx4Mul, bucket g >> (32 -
+    //    gfp_lb) has one slot i with the 12 bits of g below those in its upper
+    //    bits and i in its lower four (0xffff: empty); gfp_lb = 0: no slots;
+    //  - grec: a record (4 words) per slot.  When one string remains below the
+    //    only trie node that its grams end at: the string's offset in gpat,
+    //    its length | offset of the gram in it << 16 | ids of its pattern list
+    //    << 18, and kGramId | id for a list of one id, else the list's offset.
+    //    Otherwise kNone and the offsets of its grams as bits 1 << offset;
+    //  - gpat: every pattern's bytes, each from a multiple of four on.
     uint32_t gram_s = 0;               // S: 4, 2 or 1 (0 = no gram filter)
     uint32_t gram_lw = 0, gfp_lb = 0;
     std::vector<uint32_t> gram;
     std::vector<uint16_t> gfp;
+    std::vector<uint32_t> grec;
+    std::vector<uint8_t> gpat;
 };
 
 // Multiplicative (Fibonacci) hashing, Knuth TAOCP vol. 3, 6.4: odd
@@ -162,6 +170,7 @@ constexpr uint32_t kPfx4Mul = 0x9E3779B1u;  // 32-bit multiplier
 constexpr uint32_t kPfx4M1 = 0x9E3779u;     // 24-bit multipliers of the prefix-4 filter
 constexpr uint32_t kPfx4M2 = 0x7F4A7Du;
 constexpr uint32_t kGramC0 = 0x9E37u, kGramC1 = 0xC2B3u;  // 16-bit multipliers of the gram filter
+constexpr uint32_t kGramId = 1u << 31;                    // a pattern id in place of a list's offset
 constexpr uint32_t kGramShift = 10;                       // ... and the bits below its word index
 
 // Derives the device image from the CRS trie for a level index of at most

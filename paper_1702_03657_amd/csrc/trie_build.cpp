@@ -600,7 +600,7 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
         for (uint32_t o = 0; o < S; o++) n += level(o + 4);  // at most so many distinct grams at offset o
         if (S == 1 || n <= (1u << 18)) break;
     }
-    if (n > (1u << 19)) return;
+    if (n > (1u << 19) || I.pout_ids.size() >= kGramId) return;
     // small alphabets: past a quarter of all grams the filter keeps too much
     const double all = (double)I.alphabet * I.alphabet * I.alphabet * I.alphabet;
     if (4.0 * (double)n > all) return;
@@ -613,43 +613,97 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
         for (uint32_t o = 0; o < S; o++)
             for (uint32_t v = T.level_start[o + 4]; v < T.level_start[o + 5]; v++) {
                 const uint8_t *p = T.pat_data.data() + T.pat_off[T.rep[v]] + o;
-                f((uint32_t)p[0] | (uint32_t)p[1] << 8 | (uint32_t)p[2] << 16 | (uint32_t)p[3] << 24, o);
+                f((uint32_t)p[0] | (uint32_t)p[1] << 8 | (uint32_t)p[2] << 16 | (uint32_t)p[3] << 24, o, v);
             }
     };
-    each_gram([&](uint32_t x, uint32_t) {
+    each_gram([&](uint32_t x, uint32_t, uint32_t) {
         const uint32_t h = (x & 0xffffu) * kGramC0 + (x >> 16) * kGramC1;
         I.gram[(h >> kGramShift) & ((1u << I.gram_lw) - 1u)] |= (1u << (h & 31)) | (1u << (x & 31));
     });
-    // buckets of 16 slots: about three grams each, more buckets while one overflows
+    // buckets of 14 slots: about three grams each, more buckets while one overflows
+    struct Slot {
+        uint32_t node, mask;  // the trie node its only gram ends at (kNone: several), offsets
+    };
+    constexpr uint32_t kSlots = 14;
     uint32_t lb = 1;
     while ((1ull << lb) * 3 < n) lb++;
     bool put_all = false;
+    std::vector<Slot> slots;
     for (const uint32_t top = std::min(lb + 3, 20u); !put_all && lb <= top; lb++) {
+        const uint32_t nb = 1u << lb;
         I.gfp_lb = lb;
-        I.gfp.assign((size_t)16 << lb, 0xffffu);
-        std::vector<uint8_t> used_slots((size_t)1 << lb, 0);
+        I.gfp.assign((size_t)16 * nb, 0xffffu);
+        slots.assign((size_t)kSlots * nb, Slot{0, 0});
         put_all = true;
-        each_gram([&](uint32_t x, uint32_t o) {
-            const uint32_t g = x * kPfx4Mul;
-            uint16_t *bk = I.gfp.data() + ((size_t)(g >> (32 - lb)) << 4);
-            uint8_t &n_used = used_slots[g >> (32 - lb)];
+        each_gram([&](uint32_t x, uint32_t o, uint32_t v) {
+            const uint32_t g = x * kPfx4Mul, b = g >> (32 - lb);
+            uint16_t *bk = I.gfp.data() + ((size_t)b << 4);
+            Slot *sl = slots.data() + (size_t)b * kSlots;
             const uint32_t fp = (g >> (20 - lb)) & 0xfffu;
             uint32_t i = 0;
-            while (i < n_used && (uint32_t)(bk[i] >> 4) != fp) i++;
-            if (i == 16) {
+            while (i < kSlots && sl[i].mask && (uint32_t)(bk[i] >> 4) != fp) i++;
+            if (i == kSlots) {
                 put_all = false;
                 return;
             }
-            if (i == n_used) {
-                bk[i] = (uint16_t)(fp << 4);
-                n_used++;
-            }
-            bk[i] = (uint16_t)(bk[i] | 1u << o);
+            bk[i] = (uint16_t)(fp << 4 | i);
+            sl[i].node = sl[i].mask ? kNone : v;
+            sl[i].mask |= 1u << o;
         });
     }
+    lb = I.gfp_lb;
     if (!put_all) {  // every offset of a gram is walked
         I.gfp_lb = 0;
         I.gfp.clear();
+        return;
+    }
+    // The record of each slot.  A gram that ends at one trie node only, below
+    // which one pattern string remains: that string is compared with the text
+    // in one go.  No pattern ends above the node (its depth is at most
+    // S + 3, no pattern is shorter).
+    std::vector<uint32_t> leaf(T.n_nodes());  // the only leaf below a node without another pattern's end, or kNone
+    for (uint32_t v = T.n_nodes(); v-- > 0;) {
+        const uint32_t nc = T.row_ptr[v + 1] - T.row_ptr[v];
+        const bool term = T.term_ptr[v + 1] > T.term_ptr[v];
+        leaf[v] = nc == 0 ? v : nc == 1 && !term ? leaf[T.row_ptr[v] + 1] : kNone;
+    }
+    std::vector<uint32_t> pat_at(T.k);
+    size_t bytes = 0;
+    for (uint32_t j = 0; j < T.k; j++) {
+        pat_at[j] = (uint32_t)bytes;
+        bytes += (T.pat_off[j + 1] - T.pat_off[j] + 3) & ~3ull;
+    }
+    if (bytes >= 0xffffff00ull) {
+        I.gfp_lb = 0;
+        I.gfp.clear();
+        return;
+    }
+    I.gpat.assign(bytes + 64, 0);
+    for (uint32_t j = 0; j < T.k; j++)
+        std::memcpy(I.gpat.data() + pat_at[j], T.pat_data.data() + T.pat_off[j], T.pat_off[j + 1] - T.pat_off[j]);
+    I.grec.reserve(4 * n);
+    for (size_t b = 0; b < ((size_t)1 << lb); b++) {
+        const uint32_t base = (uint32_t)(I.grec.size() / 4);
+        I.gfp[16 * b + 14] = (uint16_t)base;
+        I.gfp[16 * b + 15] = (uint16_t)(base >> 16);
+        for (uint32_t i = 0; i < kSlots && slots[b * kSlots + i].mask; i++) {
+            const Slot &s = slots[b * kSlots + i];
+            const uint32_t l = s.node != kNone ? leaf[s.node] : kNone;
+            uint32_t rec[4] = {kNone, s.mask, 0, 0};
+            if (l != kNone) {
+                const uint32_t j = T.rep[l];
+                const uint64_t len = T.pat_off[j + 1] - T.pat_off[j];
+                const uint32_t list = I.node[4ull * l + 2] >> kCountShift, at = I.node[4ull * l + 3];
+                const uint32_t o = (uint32_t)__builtin_ctz(s.mask);
+                if (len <= 0xffff && list < kCountEsc) {
+                    rec[0] = pat_at[j];
+                    rec[1] = (uint32_t)len | o << 16 | list << 18;
+                    // a list of one id: the id itself
+                    rec[2] = list == 1 && I.pout_ids[at] < kGramId ? kGramId | I.pout_ids[at] : at;
+                }
+            }
+            I.grec.insert(I.grec.end(), rec, rec + 4);
+        }
     }
 }
 

@@ -158,7 +158,7 @@ __device__ __forceinline__ void emit_unit(const ScanArgs &a, uint64_t u, uint64_
         if (lane == 0) {
             a.unit_count[u] = total;
             a.unit_off[u] = ~0ull;
-            atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
+            if (a.blocksum) atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
         }
     } else {
         unsigned long long b = 0;
@@ -166,7 +166,7 @@ __device__ __forceinline__ void emit_unit(const ScanArgs &a, uint64_t u, uint64_
             b = atomicAdd(a.stage_cursor, (unsigned long long)total);
             a.unit_count[u] = total;
             a.unit_off[u] = b;
-            atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
+            if (a.blocksum) atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
         }
         base = __shfl(b, 0, 64);
         dst = a.stage;
