@@ -811,27 +811,69 @@ static bool use_wave_kernel(const pfac_trie *t, const pfac_tuning &tn, uint32_t 
     return wave;
 }
 
+static bool use_gram_kernel(const pfac_trie *t);
+
+// launches with candidate lists (the gram kernel's past-LDS matches lie there)
 static bool uses_split(const pfac_trie *t, const pfac_tuning &tn) {
-    return tn.kernel == 2 && use_wave_kernel(t, tn, nullptr);
+    return use_gram_kernel(t) || (tn.kernel == 2 && use_wave_kernel(t, tn, nullptr));
 }
 
 // How a scan of `total` bytes at `text` is cut with the trie's tuning:
 // output units (tiles, or units of G chunks), batch-plan units (1 KiB chunks
 // of the wave kernels, else tiles), and which kernels run.
 struct ScanShape {
-    bool wave_kernel, split;
-    uint32_t waves, tile, plan_unit;
+    bool wave_kernel, split, gram;
+    bool gram_lds;                    // gram kernel: its bitmap in LDS
+    uint32_t waves, group, tile, plan_unit;
     uint64_t shift, n_tiles, n_plan;
     uint64_t ws_units() const { return std::max(n_tiles, n_plan); }
 };
 
-static ScanShape scan_shape(const pfac_trie *t, const pfac_tuning &tn, const void *text, uint64_t total) {
+// The gram kernel runs the launches whose kernel the library chooses (kernel
+// 3), where the image has a gram filter.
+static bool use_gram_kernel(const pfac_trie *t) {
+    return t->tuning.kernel == 3 && t->img.gram_s && !t->img.trunc_depth && !t->img.dag;
+}
+
+// Launch shape of the gram kernel, placed by a sweep of 16 KiB to 32 MiB with
+// 1,000 to 10,000 patterns on MI355X (us per scan).  Large launches keep the
+// bitmap (at most 128 KiB) in LDS, one workgroup of 16 waves a CU, and give
+// each wave one unit while they can: 16 MiB in 16.1 with units of 4 chunks,
+// 20.2 with 2, 25.7 with 1.  Loading the bitmap pays from 2.5 MiB on: 2 MiB
+// take 11.1 with tests that read it from L2 and 12.1 from LDS, 3 MiB 12.7 and
+// 12.4.  Small bitmaps (16 KiB) are worth loading at any size: 64 KiB in 9.3
+// against 9.9.
+constexpr uint64_t kGramFewChunks = 2560;
+constexpr uint32_t kGramSmallTable = 12;  // log2 of its words
+
+static ScanShape scan_shape(const pfac_trie *t, const pfac_tuning &tn, const void *text, uint64_t total,
+                            bool allow_gram = true) {
     ScanShape h{};
-    h.waves = tn.waves_per_wg;
-    h.wave_kernel = use_wave_kernel(t, tn, &h.waves);
-    h.split = h.wave_kernel && tn.kernel == 2;
-    h.tile = h.wave_kernel ? kWaveChunk * tn.chunks_per_unit : kWG * tn.bytes_per_lane;
     h.shift = (uintptr_t)text & 15;
+    h.gram = allow_gram && use_gram_kernel(t);
+    if (h.gram) {
+        h.wave_kernel = true;
+        const uint64_t chunks = tiles_for(total, h.shift, kWaveChunk);
+        if (chunks > kGramFewChunks) {
+            h.gram_lds = true;
+            h.waves = 16;
+            h.group = balanced_unit_chunks(chunks, 16ull * std::max(t->n_cu, 1), kAutoUnitChunks);
+        } else if (t->img.gram_lw <= kGramSmallTable) {
+            h.gram_lds = true;
+            h.waves = 8;
+            h.group = 1;
+        } else {
+            h.waves = 4;
+            h.group = chunks > kGramFewChunks / 2 ? 2 : 1;
+        }
+        h.tile = kWaveChunk * h.group;
+    } else {
+        h.waves = tn.waves_per_wg;
+        h.wave_kernel = use_wave_kernel(t, tn, &h.waves);
+        h.split = h.wave_kernel && tn.kernel == 2;
+        h.group = tn.chunks_per_unit;
+        h.tile = h.wave_kernel ? kWaveChunk * tn.chunks_per_unit : kWG * tn.bytes_per_lane;
+    }
     h.n_tiles = tiles_for(total, h.shift, h.tile);
     if (t->crs.k == 0) h.n_tiles = 0;  // nothing can match
     h.plan_unit = h.wave_kernel ? kWaveChunk : h.tile;
@@ -839,17 +881,12 @@ static ScanShape scan_shape(const pfac_trie *t, const pfac_tuning &tn, const voi
     return h;
 }
 
-// The gram kernel runs the launches whose kernel the library chooses (kernel
-// 3), where the image has a gram filter.
-static bool use_gram_kernel(const pfac_trie *t, uint64_t total) {
-    return t->tuning.kernel == 3 && t->img.gram_s && !t->img.trunc_depth && !t->img.dag && total >= kAutoSplitBytes;
-}
-
-static int enqueue_scan(const Launch &L, bool reserve) {
+static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
     const pfac_trie *t = L.t;
     const pfac_tuning tn = launch_tuning(t, L.total);
-    const ScanShape h = scan_shape(t, tn, L.text, L.total);
+    const ScanShape h = scan_shape(t, tn, L.text, L.total, allow_gram);
     uint32_t waves = h.waves;
+    const bool gram = h.gram;
     const bool wave_kernel = h.wave_kernel;
     const bool split = h.split;
     const uint32_t bpl = tn.bytes_per_lane;
@@ -860,18 +897,20 @@ static int enqueue_scan(const Launch &L, bool reserve) {
     const uint32_t plan_unit = h.plan_unit;
     const uint64_t n_plan = h.n_plan;
     if (reserve) {
-        int rc = ws_reserve(L.w, h.ws_units(), L.capacity, split);
+        int rc = ws_reserve(L.w, h.ws_units(), L.capacity, split || gram);
         if (rc != PFAC_OK) return rc;
     }
     pfac_workspace *w = L.w;
     const uint32_t n_sums = (uint32_t)std::max<uint64_t>(1, (n_tiles + (1u << kSumShift) - 1) >> kSumShift);
 
-    ScanArgs a = layout_for(t, tn, &waves);
-    a.im = t->view;
-    const bool gram = wave_kernel && split && use_gram_kernel(t, L.total);
+    ScanArgs a{};
     if (gram) {
-        waves = kGramWaves;
-        gram_lds_layout(a, waves);
+        a.im = t->view;
+        a.group = h.group;
+        gram_lds_layout(a, waves, h.gram_lds);
+    } else {
+        a = layout_for(t, tn, &waves);
+        a.im = t->view;
     }
     a.base = (const uint8_t *)(addr - shift);
     a.shift = shift;
@@ -892,12 +931,12 @@ static int enqueue_scan(const Launch &L, bool reserve) {
     a.blocksum = (unsigned long long *)w->blocksum.p;
     a.counts = L.counts;
     a.inline_stage = (pfac_match *)w->inline_stage.p;
-    a.inline_cap = wave_kernel ? std::max(kInlineCap, kInlinePerChunk * tn.chunks_per_unit) : 0;
+    a.inline_cap = wave_kernel ? std::max(kInlineCap, kInlinePerChunk * h.group) : 0;
     if (gram) {
         // the candidate area (32 x 16 bytes a chunk) holds the matches past
         // the LDS lists, 8 bytes each, in scan order and again in position order
         a.spill = (uint2 *)w->cand.p;
-        a.spill_cap = a.group * kCandPerChunk;
+        a.spill_cap = a.spill ? a.group * kCandPerChunk : 0;
     } else if (split) {
         a.cand = (uint4 *)w->cand.p;
         a.cand_count = (uint32_t *)w->cand_count.p;
@@ -910,7 +949,7 @@ static int enqueue_scan(const Launch &L, bool reserve) {
     a.n_sums = n_sums;
     if (n_tiles <= kCountUnits) a.blocksum = nullptr;
     // (the split filter kernel clears the block sums and the cursor itself)
-    if ((a.blocksum || w->cursor_stale) && !(split && !gram && n_tiles))
+    if ((a.blocksum || w->cursor_stale) && !(split && n_tiles))
         HIP_TRY(launch_reset(a.stage_cursor, a.blocksum, a.blocksum ? n_sums : 0, L.s));
     w->cursor_stale = true;  // until the finisher is queued
     if (L.counts) HIP_TRY(launch_fill_u32(L.counts, L.total, 0, L.s));
@@ -927,8 +966,9 @@ static int enqueue_scan(const Launch &L, bool reserve) {
         uint64_t want;
         if (gram) {
             const int sl = (int)a.im.gram_s;
-            if (a.lds_total > 64 * 1024) HIP_TRY(grant_lds(20 + sl, a.lds_total, prepare_gram_kernel, sl));
-            occ = 1;
+            if (h.gram_lds) HIP_TRY(grant_lds(20 + sl, a.lds_total, prepare_gram_kernel, sl));
+            // (without the bitmap in LDS at least a wave per unit is resident)
+            occ = h.gram_lds ? 1 : 1 << 20;
             want = (n_tiles + waves - 1) / waves;
         } else if (wave_kernel) {
             const int mode = wave_mode(a);
@@ -954,13 +994,13 @@ static int enqueue_scan(const Launch &L, bool reserve) {
         w->main_block = wave_kernel ? 64 * waves : kWG;
         w->main_lds = a.lds_total;
         if (gram)
-            HIP_TRY(launch_scan_grams(a, waves, grid, L.s));
+            HIP_TRY(launch_scan_grams(a, waves, h.gram_lds, grid, L.s));
         else if (wave_kernel)
             HIP_TRY(launch_scan_waves(a, waves, grid, L.s));
         else
             HIP_TRY(launch_scan(a, bpl, grid, L.s));
         if (w->ev_stop) HIP_TRY(hipEventRecordWithFlags(w->ev_stop, L.s, ev_flags));
-        if (split && !gram) HIP_TRY(launch_walk_units(a, L.s));
+        if (split) HIP_TRY(launch_walk_units(a, L.s));
     }
     FinishArgs f{};
     f.unit_count = a.unit_count;
@@ -1039,39 +1079,51 @@ extern "C" int pfac_scan_noalloc(const pfac_trie *t, const uint8_t *text_dev, ui
     if (n > 0 && !text_dev) return PFAC_EINVAL;
     if (capacity > 0 && !out_dev) return PFAC_EINVAL;
     // the workspace pfac_scan would reserve, carved out of the scratch
-    const ScanShape h = scan_shape(t, launch_tuning(t, n), text_dev, n);
-    if (h.ws_units() > (1ull << 40) || capacity > (1ull << 40)) return PFAC_EINVAL;
-    const WsSizes z = ws_sizes(h.ws_units(), capacity, h.split);
     uint8_t *base = nullptr;
     int dev = 0;
-    int rc = noalloc_scratch(&base, dev);
-    if (rc != PFAC_OK) return rc;
+    int rc = PFAC_OK;
     pfac_workspace w{};
-    uint64_t off = 0;
-    auto take = [&](DeviceBuf &b, uint64_t bytes) {
-        b.p = base + off;
-        b.bytes = bytes;
-        off += (bytes + 255) & ~255ull;
-    };
-    take(w.misc, 256);
-    take(w.unit_count, z.unit_count);
-    take(w.unit_off, z.unit_off);
-    take(w.tile_first, z.tile_first);
-    take(w.chunk_info, z.chunk_info);
-    take(w.blocksum, z.blocksum);
-    take(w.stage, z.stage);
-    take(w.inline_stage, z.inline_stage);
-    if (h.split) {
-        take(w.cand, z.cand);
-        take(w.cand_count, z.cand_count);
+    // the kernel the library chooses, or where its scratch does not fit the
+    // one of explicit tunings, which needs less for small texts
+    bool gram = use_gram_kernel(t), fits = false;
+    for (;; gram = false) {
+        w = pfac_workspace{};
+        const ScanShape h = scan_shape(t, launch_tuning(t, n), text_dev, n, gram);
+        if (h.ws_units() > (1ull << 40) || capacity > (1ull << 40)) return PFAC_EINVAL;
+        const WsSizes z = ws_sizes(h.ws_units(), capacity, h.split || h.gram);
+        uint64_t off = 0;
+        auto take = [&](DeviceBuf &b, uint64_t bytes) {
+            b.p = (void *)(uintptr_t)off;  // (offsets; the base is added below)
+            b.bytes = bytes;
+            off += (bytes + 255) & ~255ull;
+        };
+        take(w.misc, 256);
+        take(w.unit_count, z.unit_count);
+        take(w.unit_off, z.unit_off);
+        take(w.tile_first, z.tile_first);
+        take(w.chunk_info, z.chunk_info);
+        take(w.blocksum, z.blocksum);
+        take(w.stage, z.stage);
+        take(w.inline_stage, z.inline_stage);
+        if (h.split || h.gram) {
+            take(w.cand, z.cand);
+            take(w.cand_count, z.cand_count);
+        }
+        fits = off <= kNoAllocScratch;
+        if (fits || !gram) break;
     }
-    if (off > kNoAllocScratch) return PFAC_EINVAL;  // text or capacity beyond the scratch
+    if (!fits) return PFAC_EINVAL;  // text or capacity beyond the scratch
+    rc = noalloc_scratch(&base, dev);
+    if (rc != PFAC_OK) return rc;
+    for (DeviceBuf *b : {&w.misc, &w.unit_count, &w.unit_off, &w.tile_first, &w.chunk_info, &w.blocksum, &w.stage,
+                         &w.inline_stage, &w.cand, &w.cand_count})
+        b->p = base + (uintptr_t)b->p;
     Launch L{t, &w, text_dev, n, nullptr, 1, 0, out_dev, capacity, n_matches_dev, counts_dev,
              nullptr, (hipStream_t)stream};
     // every buffer is in place: the scan allocates nothing (the DeviceBufs
     // are not owned and are dropped without release)
     w.cursor_stale = g_scratch_stale[dev].load();
-    rc = enqueue_scan(L, false);
+    rc = enqueue_scan(L, false, gram);
     g_scratch_stale[dev].store(w.cursor_stale);
     return rc;
 }

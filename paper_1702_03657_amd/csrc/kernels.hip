@@ -424,9 +424,19 @@ __global__ void reset_kernel(unsigned long long *cursor, unsigned long long *blo
         blocksum[i] = 0;
 }
 
+// 16 bytes a store over the aligned middle (20 MB of per-position counts: 7.4
+// us with 4-byte stores from 65,536 workgroups).
 __global__ void fill_u32_kernel(uint32_t *p, uint64_t n, uint32_t v) {
+    const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
+    const uint64_t head = min(n, (uint64_t)((16 - ((uintptr_t)p & 15)) & 15) / 4);
+    const uint64_t n4 = (n - head) / 4;
+    uint4 *q = (uint4 *)(p + head);
+    const uint4 v4 = make_uint4(v, v, v, v);
+    for (uint64_t i = i0; i < n4; i += stride) q[i] = v4;
+    // the words before and after it
+    for (uint64_t i = i0; i < head; i += stride) p[i] = v;
+    for (uint64_t i = head + 4 * n4 + i0; i < n; i += stride) p[i] = v;
 }
 
 // Largest i in [lo, hi) whose text starts at or before frame position G
@@ -650,8 +660,8 @@ hipError_t launch_reset(unsigned long long *cursor, unsigned long long *blocksum
 
 hipError_t launch_fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    uint64_t g = (n + 255) / 256;
-    const uint32_t grid = (uint32_t)(g < 65536 ? g : 65536);
+    uint64_t g = (n + 1023) / 1024;
+    const uint32_t grid = (uint32_t)(g < 4096 ? g : 4096);
     hipLaunchKernelGGL(fill_u32_kernel, dim3(grid), dim3(256), 0, s, p, n, v);
     return hipGetLastError();
 }

@@ -157,10 +157,9 @@ int max_wave_wg_per_cu(const ScanArgs &a, uint32_t waves);
 // Gram kernel (images with a gram filter): filter, walks and emission of
 // every unit in one kernel.  The LDS layout for `waves` waves (the bitmap and
 // one area per wave), and the launch.
-constexpr uint32_t kGramWaves = 16;
-void gram_lds_layout(ScanArgs &a, uint32_t waves);
+void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table);
 hipError_t prepare_gram_kernel(int s, uint32_t lds_bytes);
-hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, uint32_t grid, hipStream_t s);
+hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, bool lds_table, uint32_t grid, hipStream_t s);
 
 // Largest resident workgroups per CU for this layout.
 int max_wg_per_cu(uint32_t bpl, uint32_t lds_bytes, int var);  // var: 0 level index, 1 top nodes, 2 DAG

@@ -367,8 +367,9 @@ __device__ __forceinline__ void emit_spilled(const ScanArgs &a, uint64_t u, uint
     }
 }
 
-// S: the distance of test positions (im.gram_s).
-template <int S>
+// S: the distance of test positions (im.gram_s).  LT: the bitmap is copied to
+// LDS; without it the tests read it from global memory.
+template <int S, bool LT>
 __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     extern __shared__ __align__(16) uint8_t lds[];
     constexpr uint32_t TL = 16 / S;            // tests per lane and chunk
@@ -380,7 +381,7 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     const uint32_t lane = tid & 63;
 
     // the bitmap by direct global-to-LDS loads, at LDS address 0
-    const uint32_t n_tab = (4u << im.gram_lw) / 16;
+    const uint32_t n_tab = LT ? (4u << im.gram_lw) / 16 : 0u;
     for (uint32_t b = wave * 64; b < n_tab; b += waves * 64)
         if (b + lane < n_tab)
             __builtin_amdgcn_global_load_lds((const void *)((const uint4 *)im.gram + b + lane),
@@ -446,7 +447,8 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     // both bits of x are
     auto lookup = [&](uint32_t x, uint32_t &h) -> uint32_t {
         h = gram_hash(x);
-        return *(lds_word_t *)(uintptr_t)((h >> (kGramShift - 2)) & adr_mask);
+        const uint32_t at = (h >> (kGramShift - 2)) & adr_mask;
+        return LT ? *(lds_word_t *)(uintptr_t)at : *(const uint32_t *)((const uint8_t *)im.gram + at);
     };
     auto test = [&](uint32_t ent, uint32_t h, uint32_t x) -> uint32_t { return (ent >> (h & 31u)) & (ent >> (x & 31u)) & 1u; };
     // queue the grams x that hit, at unit positions pos; past the queue's end
@@ -658,33 +660,38 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
 
 // ------------------------------------------------------------------ launchers
 
-static const void *gram_fn(int s) {
-    return s == 4 ? (const void *)scan_grams<4> : s == 2 ? (const void *)scan_grams<2> : (const void *)scan_grams<1>;
+static const void *gram_fn(uint32_t s, bool lds_table) {
+    if (lds_table)
+        return s == 4 ? (const void *)scan_grams<4, true>
+             : s == 2 ? (const void *)scan_grams<2, true> : (const void *)scan_grams<1, true>;
+    return s == 4 ? (const void *)scan_grams<4, false>
+         : s == 2 ? (const void *)scan_grams<2, false> : (const void *)scan_grams<1, false>;
 }
 
-void gram_lds_layout(ScanArgs &a, uint32_t waves) {
-    a.off_wave = 4u << a.im.gram_lw;
+void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table) {
+    a.off_wave = lds_table ? 4u << a.im.gram_lw : 0u;
     // the queue's and the starts' place is also where a unit's matches are
-    // sorted (kGMatch entries, or 256 + 64 words)
+    // sorted (kGramMatch entries, or 256 + 64 words)
     static_assert(8 * kGMatch <= 8 * kGQ && 4 * (256 + 64) <= 8 * kGQ + 6 * kGC, "sort area");
-    a.wave_bytes = 8 * kGQ + 6 * kGC + 8 * kGMatch;
-    a.wave_bytes = (a.wave_bytes + 7u) & ~7u;
+    a.wave_bytes = (8 * kGQ + 6 * kGC + 8 * kGMatch + 7u) & ~7u;
     a.lds_total = a.off_wave + waves * a.wave_bytes + 16;
 }
 
 hipError_t prepare_gram_kernel(int s, uint32_t lds_bytes) {
     // the bitmap is addressed at LDS address 0: no static LDS in front of it
+    const void *fn = gram_fn((uint32_t)s, true);
     hipFuncAttributes attr;
-    hipError_t e = hipFuncGetAttributes(&attr, gram_fn(s));
+    hipError_t e = hipFuncGetAttributes(&attr, fn);
     if (e != hipSuccess) return e;
     if (attr.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
-    return hipFuncSetAttribute(gram_fn(s), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
 }
 
-hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, uint32_t grid, hipStream_t s) {
+hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, bool lds_table, uint32_t grid, hipStream_t s) {
     ScanArgs arg = a;
     void *args[] = {(void *)&arg};
-    const hipError_t e = hipLaunchKernel(gram_fn((int)a.im.gram_s), dim3(grid), dim3(64 * waves), args, a.lds_total, s);
+    const hipError_t e =
+        hipLaunchKernel(gram_fn(a.im.gram_s, lds_table), dim3(grid), dim3(64 * waves), args, a.lds_total, s);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }

@@ -34,8 +34,12 @@ LOWER = np.arange(97, 123)
 
 
 # shortest pattern 4 tests every position, 5 and 6 every second, 7 and more
-# every fourth; 16 KiB units and 64 KiB units
+# every fourth; units of one chunk and of up to 64, with the bitmap in LDS and
+# read from global memory (up to 2,560 chunks when it is past 16 KiB)
 @pytest.mark.parametrize("lo,alphabet,n,pad", [
+    (4, BYTES, 1, 0), (4, BYTES, 64, 3), (5, BYTES, 1023, 1), (7, BYTES, 1025, 15), (8, BYTES, 16 * 1024 + 9, 5),
+    (8, BYTES, 1280 * 1024 - 5, 5), (6, BYTES, 1280 * 1024 + 1, 0), (8, BYTES, 2560 * 1024, 0),
+    (7, BYTES, 2560 * 1024 + 1, 0), (5, BYTES, 2560 * 1024 + 16, 7), (4, LOWER, 300_001, 11), (8, BYTES, 5_000_011, 3),
     (4, BYTES, 8 * MiB + 1, 0), (5, BYTES, 8 * MiB + 1023, 1), (6, BYTES, 9 * MiB + 7, 13),
     (7, BYTES, 8 * MiB, 15), (8, BYTES, 40 * MiB + 4093, 3), (4, LOWER, 8 * MiB + 77, 2), (7, LOWER, 9 * MiB, 9),
 ])
@@ -43,21 +47,19 @@ def test_one_text(lo, alphabet, n, pad):
     rng = np.random.default_rng(lo * 100 + pad)
     pats = _patterns(rng, 1500, lo, lo + 24, alphabet)
     text = rng.choice(alphabet, n).astype(np.uint8)
-    for q in range(n // 3000):  # whole copies and copies cut short
+    for q in range(0 if n < 64 else max(n // 3000, 8)):  # whole copies and copies cut short
         p = np.frombuffer(pats[int(rng.integers(0, len(pats)))], dtype=np.uint8)
-        at = int(rng.integers(0, n - p.size))
+        at = int(rng.integers(0, n - p.size + 1))
         m = p.size if q % 4 else int(rng.integers(1, p.size + 1))
         text[at:at + m] = p[:m]
-    for at in (0, 1, 2, 3, 5, 6):  # both ends of the text
-        p = np.frombuffer(pats[at], dtype=np.uint8)
-        if at == 0:
-            text[:p.size] = p
-        elif at == 1:
-            text[n - p.size:] = p
-    for e in range(16, 4096, 16):  # starts around the edges of units
+    if n >= 64:  # both ends of the text
+        first, last = (np.frombuffer(p, dtype=np.uint8) for p in pats[:2])
+        text[:first.size] = first
+        text[n - last.size:] = last
+    for e in range(16 if n > 8 * MiB else 1, 4096, 16 if n > 8 * MiB else 3):  # starts around the edges of units
         p = np.frombuffer(pats[e % len(pats)], dtype=np.uint8)
-        at = e * 1024 - pad + e // 16 % 8 - 4
-        if at + p.size <= n:
+        at = e * 1024 - pad + e // 3 % 8 - 4
+        if at + p.size <= n - 40:
             text[at:at + p.size] = p
     want = oracle.bucketed(text, pats, threads=8)
     say(f"gram lo={lo} n={n} pad={pad}: {want.n} matches")
@@ -66,19 +68,20 @@ def test_one_text(lo, alphabet, n, pad):
     assert np.array_equal(counts, oracle.counts(n, want))
 
 
+@pytest.mark.parametrize("total", [30_000, 3 * MiB, 8 * MiB + 50])
 @pytest.mark.parametrize("lo,most,graph", [(4, 40, 0), (5, 300, 3), (8, 3000, 0), (9, 70_000, 2)])
-def test_batch(lo, most, graph):
+def test_batch(lo, most, graph, total):
     rng = np.random.default_rng(lo)
     pats = _patterns(rng, 900, lo, lo + 20, np.arange(32, 48))
     lens = []
-    while sum(lens) < 8 * MiB + 100:
+    while sum(lens) < total + 100:
         lens += rng.integers(0, most, 4000).tolist() + [0, 0, 1, 2, 3]
-    lens = lens[:next(i for i, t in enumerate(np.cumsum(lens)) if t > 8 * MiB + 50) + 1]
+    lens = lens[:next(i for i, t in enumerate(np.cumsum(lens)) if t > total) + 1]
     offs = np.zeros(len(lens) + 1, dtype=np.uint64)
     offs[1:] = np.cumsum(lens)
     n = int(offs[-1])
     text = rng.choice(np.arange(32, 48), n).astype(np.uint8)
-    for _ in range(n // 1000):
+    for _ in range(n // 300 if n < MiB else n // 1000):
         p = np.frombuffer(pats[int(rng.integers(0, len(pats)))], dtype=np.uint8)
         at = int(rng.integers(0, n - p.size))
         text[at:at + p.size] = p
@@ -90,21 +93,21 @@ def test_batch(lo, most, graph):
         assert_same(g, want, with_text=True)
 
 
-@pytest.mark.parametrize("lo", [4, 5, 7])
+@pytest.mark.parametrize("lo,n", [(4, 8 * MiB + 333), (5, 8 * MiB + 333), (7, 8 * MiB + 333), (5, MiB + 3),
+                                  (7, 4 * MiB + 1)])
 @pytest.mark.parametrize("density", ["spill", "redo", "nested"])
-def test_dense_matches(lo, density):
+def test_dense_matches(lo, n, density):
     """Stretches of many matches in units that hold few elsewhere."""
     rng = np.random.default_rng(lo)
-    n = 8 * MiB + 333
     text = rng.integers(0, 200, n).astype(np.uint8)
     if density == "nested":
         pats = [b"\xff" * m for m in range(lo, lo + 9)] * 2 + [b"\xfe" * lo + b"\xff"]
-        for at in (5000, 2 * MiB + 1, n - 3000):
+        for at in (5000, n // 2 + 1, n - 3000):
             text[at:at + 2500] = 0xff
     else:
         pats = _patterns(rng, 40, lo, lo + 3, np.arange(200, 256))
         step = 40 if density == "spill" else 11
-        for lo_at in (0, 3 * MiB + 1):  # past 80 matches a unit, past 32 a KiB
+        for lo_at in (0, n // 2 + 1):  # past 64 matches a unit, past 32 a KiB
             for q in range(3000):
                 p = np.frombuffer(pats[q % len(pats)], dtype=np.uint8)
                 at = lo_at + q * step
