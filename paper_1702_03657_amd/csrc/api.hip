@@ -86,6 +86,7 @@ struct pfac_trie {
     CrsTrie crs;
     DeviceImageHost img;
     pfac_tuning tuning{1, 16, 16, 8, 0, 16, 16, 1};
+    pfac_tuning built{};                    // the tuning chosen at the build
     uint32_t lds_limit = 160 * 1024;  // dynamic LDS a workgroup may use (gfx950; queried on the device)
     bool host_only = false;
     int device = -1;
@@ -343,6 +344,7 @@ static int build_common(const uint8_t *data, const uint64_t *offsets, uint32_t k
     if (t->img.identity && t->img.K == 2) t->tuning.kernel = 3;
     if (t->img.pfx4_log2) t->tuning.child_check = 2;
     if (t->img.q16_lw) t->tuning.kernel = 3;  // four-symbol alphabets: the 16-symbol filter
+    t->built = t->tuning;
     t->build_s = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     set_halo(t);
     t->host_only = (flags & PFAC_BUILD_HOST_ONLY) != 0;
@@ -821,6 +823,10 @@ static bool uses_split(const pfac_trie *t, const pfac_tuning &tn) {
 // How a scan of `total` bytes at `text` is cut with the trie's tuning:
 // output units (tiles, or units of G chunks), batch-plan units (1 KiB chunks
 // of the wave kernels, else tiles), and which kernels run.
+// Up to this many units a finisher workgroup takes 16 of them, past it 32 (16
+// MiB of words: 38 us a scan with 16, 40 with 32).
+constexpr uint64_t kFinishWide = 8192;
+
 struct ScanShape {
     bool wave_kernel, split, gram;
     bool gram_lds;                    // gram kernel: its bitmap in LDS
@@ -830,9 +836,10 @@ struct ScanShape {
 };
 
 // The gram kernel runs the launches whose kernel the library chooses (kernel
-// 3), where the image has a gram filter.
+// 3, or the tuning of the build), where the image has a gram filter.
 static bool use_gram_kernel(const pfac_trie *t) {
-    return t->tuning.kernel == 3 && t->img.gram_s && !t->img.trunc_depth && !t->img.dag;
+    return (t->tuning.kernel == 3 || same_tuning(t->tuning, t->built)) && t->img.gram_s && !t->img.trunc_depth &&
+           !t->img.dag;
 }
 
 // Launch shape of the gram kernel, placed by a sweep of 16 KiB to 32 MiB with
@@ -907,7 +914,7 @@ static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
     if (gram) {
         a.im = t->view;
         a.group = h.group;
-        gram_lds_layout(a, waves, h.gram_lds);
+        gram_lds_layout(a, waves, h.gram_lds, t->lds_limit);
     } else {
         a = layout_for(t, tn, &waves);
         a.im = t->view;
@@ -1009,13 +1016,16 @@ static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
     f.stage = a.stage;
     f.stage_cap = a.stage_cap;
     f.n_tiles = n_tiles;
-    f.n_sums = n_sums;
+    f.shift = a.blocksum || n_tiles > kFinishWide ? kSumShift : 4;
+    f.n_sums = (uint32_t)std::max<uint64_t>(1, (n_tiles + (1u << f.shift) - 1) >> f.shift);
     f.out = L.out;
     f.capacity = L.out ? L.capacity : 0;
     f.n_matches = L.n_matches;
     f.base_dev = L.base_dev;
     f.inline_stage = a.inline_stage;
     f.inline_cap = a.inline_cap;
+    f.spill = (const pfac_match *)a.spill;
+    f.spill_cap = a.spill_cap;
     f.cursor = a.stage_cursor;
     HIP_TRY(launch_finish(f, L.s));
     w->cursor_stale = false;
@@ -1478,7 +1488,7 @@ static int autotune_common(pfac_trie *t, pfac_workspace *w, const void *ctx, tun
         return rc;
     }
 
-    std::vector<pfac_tuning> cands;
+    std::vector<pfac_tuning> cands(1, start);
     for (uint32_t bits : {12u, 16u, 18u}) {
         for (uint32_t fold : {8u, 16u, 0u})
             for (uint32_t kernel : {1u, 2u})

@@ -18,6 +18,7 @@ constexpr uint32_t kSumShift = 5;        // units per block-sum entry and finish
 // them.  On MI355X, 32,000 units: 12 us of a scan's atomics and 5 us of
 // clearing against 4 us more in the finisher.
 constexpr uint64_t kCountUnits = 1u << 16;
+constexpr unsigned long long kUnitSpill = ~1ull;  // unit_off: records in the unit's spill area
 constexpr uint32_t kHaloCap = 1024;      // most halo bytes staged in LDS
 constexpr uint32_t kInlineCap = 8;       // records a wave unit stages without an atomic (at least)
 constexpr uint32_t kInlinePerChunk = 2;  // ... and per 1 KiB chunk of the unit
@@ -105,9 +106,11 @@ struct ScanArgs {
     uint32_t cand_cap;
     uint32_t n_sums;                  // split filter kernel: clears blocksum[0 .. n_sums) and the cursor
     // gram kernel: matches of unit u past the LDS list, at spill[2 * u *
-    // spill_cap ..) in scan order, then spill_cap more in position order
+    // spill_cap ..) in scan order, then spill_cap more in position order; or,
+    // when the LDS list holds them, up to spill_cap records past the inline slots
     uint2 *spill;
-    uint32_t spill_cap, pad2;
+    uint32_t spill_cap;
+    uint32_t gq, gc, gm;              // entries of a wave's LDS lists: grams, starts, matches
 };
 
 struct FinishArgs {
@@ -117,13 +120,15 @@ struct FinishArgs {
     const pfac_match *stage;
     uint64_t stage_cap;
     uint64_t n_tiles;
-    uint32_t n_sums;                  // block-sum entries = finisher workgroups: 1 << kSumShift units each
+    uint32_t n_sums, shift;           // finisher workgroups, of 1 << shift units each (kSumShift with block sums)
     pfac_match *out;
     uint64_t capacity;
     uint64_t *n_matches;              // receives this launch's match count
     const unsigned long long *base_dev;  // optional device value added to every output index
     const pfac_match *inline_stage;   // units with unit_off == ~0 keep their records here
     uint64_t inline_cap;
+    const pfac_match *spill;          // units with unit_off == kUnitSpill keep them here
+    uint64_t spill_cap;
     unsigned long long *cursor;       // the staging cursor, cleared for the next scan
 };
 
@@ -157,7 +162,7 @@ int max_wave_wg_per_cu(const ScanArgs &a, uint32_t waves);
 // Gram kernel (images with a gram filter): filter, walks and emission of
 // every unit in one kernel.  The LDS layout for `waves` waves (the bitmap and
 // one area per wave), and the launch.
-void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table);
+void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table, uint32_t lds_limit);
 hipError_t prepare_gram_kernel(int s, uint32_t lds_bytes);
 hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, bool lds_table, uint32_t grid, hipStream_t s);
 

@@ -20,10 +20,11 @@
 //     memory (L2);
 //   * a slot's record gives the offset of the gram in its pattern, that is the
 //     start, and the pattern, which is compared with the text in one go; a
-//     gram of several patterns has its possible starts walked from their
+//     gram that several patterns share at one trie node is walked from that
+//     node, and one of several nodes has its possible starts walked from their
 //     depth-K nodes;
-//   * matches of a unit collect in LDS, past kGMatch in global memory, and are
-//     staged in (pos, id) order.
+//   * matches of a unit collect in LDS, past that in the unit's part of a
+//     global buffer, and are staged in (pos, id) order.
 // Unit u holds the starts from S - 1 before its first test position to S - 1
 // before its end, so no start is seen by two units.
 #include <hip/hip_runtime.h>
@@ -33,9 +34,13 @@
 
 namespace pfac {
 
-constexpr uint32_t kGQ = 120;     // grams in a wave's queue, 8 bytes each
-constexpr uint32_t kGC = 92;      // grams in its list of starts: 4 + 2 bytes each
-constexpr uint32_t kGMatch = 64;  // matches of a unit in LDS
+// A wave's lists in LDS: queued grams (8 bytes each), grams whose starts are
+// to be looked at (6) and matches of the unit (8).  The short ones fit 16 waves
+// beside a bitmap of 128 KiB; texts that hit often (words: 50 grams a KiB)
+// want the long ones, so that a group never overflows the queue.
+constexpr uint32_t kGqShort = 120, kGcShort = 92, kGmShort = 64;
+constexpr uint32_t kGqLong = 448, kGcLong = 192, kGmLong = 160;
+constexpr uint32_t kGqRoom = 57;  // the queue is emptied when a group leaves less room
 
 typedef __attribute__((address_space(3))) const uint32_t lds_word_t;
 typedef __attribute__((address_space(4))) const uint32_t scalar_u32_t;
@@ -144,11 +149,83 @@ __device__ __forceinline__ TextSpan text_span(const ScanArgs &a, uint64_t p, con
     return TextSpan{i, a.offsets[i] + a.shift, a.offsets[i + 1] + a.shift};
 }
 
+// 16 text bytes at frame position p as four words, or false when their whole
+// loads could pass the text's last 16-byte block (at blk_hi).
+__device__ __forceinline__ bool text16(const uint8_t *base, uint64_t p, uint64_t blk_hi, uint4 &t) {
+    const uint64_t p4 = p & ~3ull;
+    if (p4 + 20 > blk_hi + 16) return false;
+    const uint32_t *q = (const uint32_t *)(base + p4);
+    const uint32_t w0 = q[0], w1 = q[1], w2 = q[2], w3 = q[3], w4 = q[4], sh = (uint32_t)(p & 3);
+    t = make_uint4(__builtin_amdgcn_alignbyte(w1, w0, sh), __builtin_amdgcn_alignbyte(w2, w1, sh),
+                   __builtin_amdgcn_alignbyte(w3, w2, sh), __builtin_amdgcn_alignbyte(w4, w3, sh));
+    return true;
+}
+
+// walk_g from node v at depth d with the first 16 text bytes in registers: a
+// step down to there is one dependent load, the node.
+__device__ __forceinline__ uint2 walk_from(const ImageView &im, const uint8_t *base, uint64_t p, uint32_t lim,
+                                           uint32_t v, uint32_t d, uint64_t hi_valid, const uint4 t) {
+    uint2 hit = make_uint2(0, 0);
+    for (;;) {
+        const uint4 r = im.node[v];
+        if (r.z & kTermFlagD) hit = make_uint2(r.w, r.z >> kCountShiftD);
+        const uint32_t nc = r.z & 0xffffu;
+        if (nc == 0 || d >= lim) break;
+        const bool skip = (r.z & kSkipFlagD) != 0;
+        if (skip) {
+            const uint32_t len = r.z >> kSkipShiftD;
+            if (d + len > lim) break;
+            if (p + d + len + 36 <= hi_valid) {
+                const bool leaf = (r.z & kLeafEndD) != 0;
+                if (!chain_equal_g(base, p + d, im.chain, leaf ? r.x & 0xffffffu : r.x, len)) break;
+                if (leaf) {
+                    hit = make_uint2(r.w, r.x >> 24);
+                    break;
+                }
+                v = r.w;
+                d += len;
+                continue;
+            }
+        }
+        uint32_t c;
+        if (d < 16) {
+            const uint32_t lo = d & 4 ? t.y : t.x, hi = d & 4 ? t.w : t.z;
+            c = ((d & 8 ? hi : lo) >> (8 * (d & 3))) & 0xffu;
+        } else {
+            c = base[p + d];
+        }
+        uint32_t j;
+        if (skip) {
+            if (c != im.label[r.y - 1]) break;
+            j = 0;
+        } else if (nc <= 4) {
+            const uint32_t x = r.x ^ (c * 0x01010101u);
+            const uint32_t m = (x - 0x01010101u) & ~x & 0x80808080u;  // lowest flag = first zero byte
+            if (m == 0) break;
+            j = (uint32_t)__builtin_ctz(m) >> 3;
+            if (j >= nc) break;
+        } else {
+            const uint8_t *lab = im.label + (r.y - 1);
+            uint32_t lo = 0, hi = nc;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (lab[mid] < c) lo = mid + 1; else hi = mid;
+            }
+            if (lo == nc || lab[lo] != c) break;
+            j = lo;
+        }
+        v = r.y + j;
+        d++;
+    }
+    return hit;
+}
+
 // Walk for the start p whose text ends at `end` (end - p >= the shortest
-// pattern), from the depth-K node of its first K symbols.
+// pattern), from the depth-K node of its first K (at most 12) symbols.
 __device__ __forceinline__ uint2 walk_start(const ImageView &im, const uint8_t *base, uint64_t p,
                                             uint64_t end, uint64_t hi_valid) {
     const uint32_t K = im.K;
+    const uint32_t lim = (uint32_t)umin64(end - p, 0xffffffffull);
     uint32_t v = 0;
     if (K) {
         uint32_t code = 0, bad = 0;
@@ -164,8 +241,7 @@ __device__ __forceinline__ uint2 walk_start(const ImageView &im, const uint8_t *
         if (!((lv.x >> bit) & 1u)) return make_uint2(0, 0);
         v = im.lvl_start + lv.y + (uint32_t)__builtin_popcount(lv.x & ((1u << bit) - 1u));
     }
-    const uint64_t lim = end - p;
-    return walk_g(im, base, p, (uint32_t)umin64(lim, 0xffffffffull), v, K, hi_valid);
+    return walk_g(im, base, p, lim, v, K, hi_valid);
 }
 
 // A start's pattern list (0 ids: no match), for starts in any order; `in`:
@@ -217,31 +293,52 @@ __device__ __forceinline__ uint2 list_of(const ImageView &im, uint2 e) {
 __device__ __forceinline__ void put(const ScanArgs &a, uint64_t p, uint2 ids, pfac_match *dst, uint64_t idx,
                                     uint64_t cap, const UnitTexts &ut) {
     const TextSpan t = text_span(a, p, ut);
-    for (uint32_t k = 0; k < ids.y && idx < cap; k++, idx++) {
-        pfac_match m;
-        m.pos = p - t.start;
-        m.pattern_id = (ids.x & kGramId) ? ids.x & ~kGramId : a.im.pout_ids[ids.x + k];
-        m.text_id = t.tid + a.text_id0;
-        dst[idx] = m;
+    // four ids at a time, so that their loads do not wait for stores
+    for (uint32_t k = 0; k < ids.y && idx < cap; k += 4, idx += 4) {
+        uint32_t id[4];
+#pragma unroll
+        for (uint32_t q = 0; q < 4; q++)
+            id[q] = (ids.x & kGramId) ? ids.x & ~kGramId : a.im.pout_ids[ids.x + min(k + q, ids.y - 1)];
+#pragma unroll
+        for (uint32_t q = 0; q < 4; q++) {
+            pfac_match m;
+            m.pos = p - t.start;
+            m.pattern_id = id[q];
+            m.text_id = t.tid + a.text_id0;
+            if (k + q < ids.y && idx + q < cap) dst[idx + q] = m;
+        }
     }
     if (a.counts && ids.y) a.counts[p - a.shift] = ids.y;
 }
 
-// Reserve `total` records of unit u: its inline slots or the staging area.
-__device__ __forceinline__ void reserve_unit(const ScanArgs &a, uint64_t u, uint32_t total,
+// Reserve `total` records of unit u: its inline slots, its part of the spill
+// area where the unit's lists have not used that (spare), or the staging area.
+// (One atomic per unit on the staging cursor takes 10 ns each: 33 of 69 us on
+// 16 MiB of words with 10 matches a KiB.)
+__device__ __forceinline__ void reserve_unit(const ScanArgs &a, uint64_t u, uint32_t total, bool spare,
                                              pfac_match *&dst, uint64_t &base, uint64_t &cap) {
     const uint32_t lane = lane_id();
-    const bool in = total <= a.inline_cap;
-    unsigned long long b = 0;
+    unsigned long long b = ~0ull;
+    dst = a.inline_stage + u * a.inline_cap;
+    cap = a.inline_cap;
+    if (total > cap) {
+        if (spare && total <= a.spill_cap) {
+            b = kUnitSpill;
+            dst = (pfac_match *)(a.spill + 2 * u * a.spill_cap);
+            cap = a.spill_cap;
+        } else {
+            if (lane == 0) b = atomicAdd(a.stage_cursor, (unsigned long long)total);
+            b = __shfl(b, 0, 64);
+            dst = a.stage;
+            cap = a.stage_cap;
+        }
+    }
     if (lane == 0) {
-        if (!in) b = atomicAdd(a.stage_cursor, (unsigned long long)total);
         a.unit_count[u] = total;
-        a.unit_off[u] = in ? ~0ull : b;
+        a.unit_off[u] = b;
         if (a.blocksum && total) atomicAdd(&a.blocksum[u >> kSumShift], (unsigned long long)total);
     }
-    base = __shfl(b, 0, 64);
-    dst = in ? a.inline_stage + u * a.inline_cap : a.stage;
-    cap = in ? a.inline_cap : a.stage_cap;
+    base = b >= kUnitSpill ? 0 : b;
 }
 
 // Stage a unit of at most 64 matches, one a lane: each is ranked by its
@@ -266,8 +363,41 @@ __device__ __forceinline__ void emit_small(const ScanArgs &a, uint64_t u, uint64
     const uint32_t before = wave_excl_scan(ids.y, total);
     pfac_match *dst;
     uint64_t base, cap;
-    reserve_unit(a, u, total, dst, base, cap);
+    reserve_unit(a, u, total, true, dst, base, cap);
     put(a, ubase + (f.x & 0xffffu), ids, dst, base + before, cap, ut);
+}
+
+// Stage a unit of more matches that all lie in LDS, ranked likewise against
+// LDS reads that every lane shares.
+__device__ __forceinline__ void emit_lds(const ScanArgs &a, uint64_t u, uint64_t ubase, const uint2 *wm,
+                                         uint32_t mn, uint2 *sorted, const UnitTexts &ut) {
+    const uint32_t lane = lane_id();
+    uint32_t total = 0;
+    for (uint32_t r = 0; r < mn; r += 64) {
+        const uint32_t i = r + lane;
+        const uint2 e = wm[min(i, mn - 1)];
+        const uint32_t pos = e.x & 0xffffu;
+        uint32_t rk = 0;
+#pragma unroll 8
+        for (uint32_t q = 0; q < mn; q++) rk += (wm[q].x & 0xffffu) < pos ? 1u : 0u;
+        if (i < mn) sorted[rk] = e;
+        uint32_t t;
+        wave_excl_scan(i < mn ? list_of(a.im, e).y : 0u, t);
+        total += t;
+    }
+    wave_sync();
+    pfac_match *dst;
+    uint64_t base, cap;
+    reserve_unit(a, u, total, true, dst, base, cap);
+    for (uint32_t r = 0; r < mn; r += 64) {
+        const uint32_t i = r + lane;
+        const uint2 e = sorted[min(i, mn - 1)];
+        const uint2 ids = i < mn ? list_of(a.im, e) : make_uint2(0, 0);
+        uint32_t t;
+        const uint32_t before = wave_excl_scan(ids.y, t);
+        put(a, ubase + (e.x & 0xffffu), ids, dst, base + before, cap, ut);
+        base += t;
+    }
 }
 
 // Unit u again, 64 starts at a time in position order, when its matches
@@ -293,7 +423,7 @@ __device__ __forceinline__ void redo_unit(const ScanArgs &a, uint64_t u, uint64_
                 base += t;
             }
         }
-        if (pass == 0) reserve_unit(a, u, total, dst, base, cap);
+        if (pass == 0) reserve_unit(a, u, total, true, dst, base, cap);
     }
 }
 
@@ -351,7 +481,7 @@ __device__ __forceinline__ void emit_spilled(const ScanArgs &a, uint64_t u, uint
     }
     pfac_match *dst;
     uint64_t base, cap;
-    reserve_unit(a, u, total, dst, base, cap);
+    reserve_unit(a, u, total, false, dst, base, cap);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     for (uint32_t r = 0; r < mn; r += 64) {
         const uint32_t i = r + lane;
@@ -392,9 +522,10 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
 
     uint8_t *wbase = lds + a.off_wave + wave * a.wave_bytes;
     uint2 *wq = (uint2 *)wbase;                              // queue: (gram, unit position)
-    uint32_t *wcr = (uint32_t *)(wbase + 8 * kGQ);           // starts: record of the gram's slot ...
-    uint16_t *wcp = (uint16_t *)(wbase + 8 * kGQ + 4 * kGC); // ... and its unit position
-    uint2 *wm = (uint2 *)(wbase + 8 * kGQ + 6 * kGC);        // matches
+    const uint32_t gq = a.gq;
+    uint32_t *wcr = (uint32_t *)(wbase + 8 * gq);            // starts: record of the gram's slot ...
+    uint16_t *wcp = (uint16_t *)(wbase + 8 * gq + 4 * a.gc); // ... and its unit position
+    uint2 *wm = (uint2 *)(wbase + 8 * gq + 6 * a.gc);        // matches
 
     const uint64_t hi_valid = a.shift + a.total;
     const uint32_t n_u = (uint32_t)a.n_tiles, n_ch = (uint32_t)a.n_plan, G = a.group;
@@ -458,7 +589,7 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         if (mk == 0) return;
         const uint32_t at = qn;
         qn += (uint32_t)__popcll(mk);
-        if (qn > kGQ) return;
+        if (qn > gq) return;
         if (__builtin_amdgcn_inverse_ballot_w64(mk)) {  // the compare's mask as it is
             uint32_t *q = (uint32_t *)wq + 2 * mbcnt_from(mk, at);
             q[0] = x;
@@ -518,7 +649,7 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
             // the last (up to) 64 grams of the queue
             nb = min(qn, 64u);
             qn -= nb;
-            const uint2 q = wq[min(qn + lane, kGQ - 1)];
+            const uint2 q = wq[min(qn + lane, gq - 1)];
             tb = q.y;
             gb = q.x * im.pfx4_mul;
             if (lb) {
@@ -556,7 +687,7 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         // below, one test at a time
         uint32_t r_from = GC;
         const uint32_t r_to = min(GC, rem);
-        if (qn > kGQ) {
+        if (qn > gq) {
             qn = q0;
             r_from = 0;
         }
@@ -564,13 +695,13 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         check(64);
         uint32_t ra = 0;  // next test of chunk r_from
 
-        if (last || r_from < r_to || qn >= 64 || cn > kGC - 64) {
+        if (last || r_from < r_to || qn + kGqRoom > gq || cn > a.gc - 64) {
             // ---- empty the queue as far as the next group needs it, and wholly
             // after the unit's last group
             const ScanArgs &r = again(a);
             UnitTexts ut = unit_texts(r, cc.u, ubase);
             for (;;) {
-                if (r_from < r_to && qn + 64 <= kGQ) {
+                if (r_from < r_to && qn + 64 <= gq) {
                     const uint32_t pos = gpos + r_from * kChunk + ra;
                     const uint8_t *ub = a.base + ulo;
                     const uint32_t last4 = (uint32_t)umin64(blk_hi + 12 - ulo, 0x7fffffffull);
@@ -587,25 +718,35 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                     }
                 }
                 const bool done = r_from >= r_to && (last ? (nb | qn) == 0 : qn < 64);
-                if (cn > kGC - 64 || (last && done)) {
+                if (cn > r.gc - 64 || (last && done)) {
                     // ---- compare or walk the starts; matches go to LDS, past
-                    // kGMatch to global memory
+                    // gm to global memory
                     wave_sync();
                     for (uint32_t c0 = 0; c0 < cn; c0 += 64) {
-                        const uint32_t ci = min(c0 + lane, kGC - 1);
+                        const uint32_t ci = min(c0 + lane, r.gc - 1);
                         const uint32_t t = wcp[ci];
                         // (without slots every offset is walked)
-                        uint4 rec = make_uint4(0xffffffffu, (1u << S) - 1u, 0u, 0u);
+                        uint4 rec = make_uint4(kNone, (1u << S) - 1u, 0u, 0u);
                         if (lb && c0 + lane < cn) rec = r.im.grec[wcr[ci]];
                         uint32_t om = 0;
                         uint2 h = make_uint2(0, 0);
                         const uint32_t len = rec.y & 0xffffu;
-                        uint32_t pr = t + (uint32_t)(S - 1) - (rec.y >> 16 & 3u);
+                        uint32_t pr = t + (uint32_t)(S - 1) - (rec.x == kGramNode ? rec.y & 3u : rec.y >> 16 & 3u);
                         const TextSpan ts = text_span(r, ubase + pr, ut);
                         if (c0 + lane < cn) {
-                            om = rec.x == 0xffffffffu ? rec.y : 0u;
-                            // (a start before the text wraps around)
-                            if (!om && ubase + pr - r.shift < r.total && ts.end - (ubase + pr) >= len) {
+                            om = rec.x == kNone ? rec.y : 0u;
+                            if (rec.x == kGramNode && ubase + pr - r.shift < r.total &&
+                                ts.end - (ubase + pr) >= r.im.min_len) {
+                                const uint32_t o = rec.y & 3u;
+                                uint4 tw = make_uint4(0, 0, 0, 0);
+                                if (!text16(r.base, ubase + pr, blk_hi, tw))
+                                    om = 1u << o;
+                                else if (tw.x == rec.z && ((tw.y ^ (rec.y >> 8)) & ((1u << (8 * o)) - 1u)) == 0)
+                                    h = walk_from(r.im, r.base, ubase + pr,
+                                                  (uint32_t)umin64(ts.end - (ubase + pr), 0xffffffffull), rec.w, o + 4,
+                                                  hi_valid, tw);
+                            } else if (rec.x < kGramNode && ubase + pr - r.shift < r.total &&
+                                       ts.end - (ubase + pr) >= len) {
                                 const int eq = equal_pattern(r.base, ubase + pr, r.im.gpat + rec.x, len, blk_hi);
                                 if (eq < 0)  // too near the text's end for whole loads
                                     om = 1u << (rec.y >> 16 & 3u);
@@ -619,8 +760,8 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                             if (got) {
                                 const uint32_t s = mn + mbcnt(mk);
                                 const uint2 e = make_uint2(pr | (h.y << 16), h.x);
-                                if (s < kGMatch) wm[s] = e;
-                                else if (s - kGMatch < r.spill_cap) r.spill[2ull * cc.u * r.spill_cap + s - kGMatch] = e;
+                                if (s < r.gm) wm[s] = e;
+                                else if (s - r.gm < r.spill_cap) r.spill[2ull * cc.u * r.spill_cap + s - r.gm] = e;
                             }
                             mn += (uint32_t)__popcll(mk);
                             if (__ballot(om != 0) == 0) break;
@@ -636,17 +777,19 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                 if (done) break;
                 // (the loop ends: with tests left, either the queue takes one
                 // above or this takes grams from it; then it only shrinks)
-                check(r_from < r_to ? kGQ - 63 : last ? 1 : 64);
+                check(r_from < r_to ? gq - 63 : last ? 1 : 64);
             }
 
             // ---- the unit's last group: its matches in (pos, id) order
             wait_loads();
             if (last) {
                 uint2 *spill = r.spill + 2ull * cc.u * r.spill_cap;
-                if (mn <= kGMatch)
+                if (mn <= 64)
                     emit_small(r, cc.u, ubase, wm, mn, (uint2 *)wbase, ut);
+                else if (mn <= r.gm)
+                    emit_lds(r, cc.u, ubase, wm, mn, (uint2 *)wbase, ut);
                 else if (mn <= r.spill_cap)
-                    emit_spilled(r, cc.u, ubase, wm, kGMatch, spill, spill + r.spill_cap, mn, cc.n * kChunk, (uint32_t *)wbase,
+                    emit_spilled(r, cc.u, ubase, wm, r.gm, spill, spill + r.spill_cap, mn, cc.n * kChunk, (uint32_t *)wbase,
                                  (uint32_t *)(wbase + 1024), ut);
                 else
                     redo_unit(r, cc.u, ubase, cc.n * kChunk, ut);
@@ -668,13 +811,21 @@ static const void *gram_fn(uint32_t s, bool lds_table) {
          : s == 2 ? (const void *)scan_grams<2, false> : (const void *)scan_grams<1, false>;
 }
 
-void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table) {
+void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table, uint32_t lds_limit) {
     a.off_wave = lds_table ? 4u << a.im.gram_lw : 0u;
+    auto lists = [&](uint32_t gq, uint32_t gc, uint32_t gm) {
+        a.gq = gq;
+        a.gc = gc;
+        a.gm = gm;
+        a.wave_bytes = (8 * gq + 6 * gc + 8 * gm + 7u) & ~7u;
+        a.lds_total = a.off_wave + waves * a.wave_bytes + 16;
+    };
     // the queue's and the starts' place is also where a unit's matches are
-    // sorted (kGramMatch entries, or 256 + 64 words)
-    static_assert(8 * kGMatch <= 8 * kGQ && 4 * (256 + 64) <= 8 * kGQ + 6 * kGC, "sort area");
-    a.wave_bytes = (8 * kGQ + 6 * kGC + 8 * kGMatch + 7u) & ~7u;
-    a.lds_total = a.off_wave + waves * a.wave_bytes + 16;
+    // sorted (64 entries, or 256 + 64 words)
+    static_assert(8 * 64 <= 8 * kGqShort && 4 * (256 + 64) <= 8 * kGqShort + 6 * kGcShort, "sort area");
+    static_assert(kGqShort >= 64 + kGqRoom - 1 && kGcShort >= 64 && kGmShort >= 64, "a round fits");
+    lists(kGqLong, kGcLong, kGmLong);
+    if (!lds_table || a.lds_total > lds_limit) lists(kGqShort, kGcShort, kGmShort);
 }
 
 hipError_t prepare_gram_kernel(int s, uint32_t lds_bytes) {

@@ -153,7 +153,9 @@ struct DeviceImageHost {
     //    only trie node that its grams end at: the string's offset in gpat,
     //    its length | offset of the gram in it << 16 | ids of its pattern list
     //    << 18, and kGramId | id for a list of one id, else the list's offset.
-    //    Otherwise kNone and the offsets of its grams as bits 1 << offset;
+    //    Of another single node: kGramNode, offset | bytes 4 .. 6 of the path
+    //    to it << 8, the path's first four bytes, the node.  Otherwise kNone
+    //    and the offsets of the grams as bits 1 << offset;
     //  - gpat: every pattern's bytes, each from a multiple of four on.
     uint32_t gram_s = 0;               // S: 4, 2 or 1 (0 = no gram filter)
     uint32_t gram_lw = 0, gfp_lb = 0;
@@ -170,6 +172,7 @@ constexpr uint32_t kPfx4Mul = 0x9E3779B1u;  // 32-bit multiplier
 constexpr uint32_t kPfx4M1 = 0x9E3779u;     // 24-bit multipliers of the prefix-4 filter
 constexpr uint32_t kPfx4M2 = 0x7F4A7Du;
 constexpr uint32_t kGramC0 = 0x9E37u, kGramC1 = 0xC2B3u;  // 16-bit multipliers of the gram filter
+constexpr uint32_t kGramNode = kNone - 1;                 // a record that names a trie node
 constexpr uint32_t kGramId = 1u << 31;                    // a pattern id in place of a list's offset
 constexpr uint32_t kGramShift = 10;                       // ... and the bits below its word index
 

@@ -660,7 +660,8 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
     // The record of each slot.  A gram that ends at one trie node only, below
     // which one pattern string remains: that string is compared with the text
     // in one go.  No pattern ends above the node (its depth is at most
-    // S + 3, no pattern is shorter).
+    // S + 3, no pattern is shorter), so a gram of one node with more below it
+    // is walked from there.
     std::vector<uint32_t> leaf(T.n_nodes());  // the only leaf below a node without another pattern's end, or kNone
     for (uint32_t v = T.n_nodes(); v-- > 0;) {
         const uint32_t nc = T.row_ptr[v + 1] - T.row_ptr[v];
@@ -690,16 +691,26 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
             const Slot &s = slots[b * kSlots + i];
             const uint32_t l = s.node != kNone ? leaf[s.node] : kNone;
             uint32_t rec[4] = {kNone, s.mask, 0, 0};
+            const uint32_t o = (uint32_t)__builtin_ctz(s.mask);
+            if (s.node != kNone) {
+                // the path to the node, o + 4 bytes
+                const uint8_t *pb = T.pat_data.data() + T.pat_off[T.rep[s.node]];
+                rec[0] = kGramNode;
+                rec[1] = o;
+                rec[2] = (uint32_t)pb[0] | (uint32_t)pb[1] << 8 | (uint32_t)pb[2] << 16 | (uint32_t)pb[3] << 24;
+                for (uint32_t i = 0; i < o; i++) rec[1] |= (uint32_t)pb[4 + i] << (8 + 8 * i);
+                rec[3] = s.node;
+            }
             if (l != kNone) {
                 const uint32_t j = T.rep[l];
                 const uint64_t len = T.pat_off[j + 1] - T.pat_off[j];
                 const uint32_t list = I.node[4ull * l + 2] >> kCountShift, at = I.node[4ull * l + 3];
-                const uint32_t o = (uint32_t)__builtin_ctz(s.mask);
                 if (len <= 0xffff && list < kCountEsc) {
                     rec[0] = pat_at[j];
                     rec[1] = (uint32_t)len | o << 16 | list << 18;
                     // a list of one id: the id itself
                     rec[2] = list == 1 && I.pout_ids[at] < kGramId ? kGramId | I.pout_ids[at] : at;
+                    rec[3] = 0;
                 }
             }
             I.grec.insert(I.grec.end(), rec, rec + 4);

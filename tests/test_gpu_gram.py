@@ -117,3 +117,28 @@ def test_dense_matches(lo, n, density):
     got, counts = gpu_scan(pf.Trie(pats), text)
     assert_same(got, want)
     assert np.array_equal(counts, oracle.counts(n, want))
+
+
+@pytest.mark.parametrize("n", [100_003, 3 * MiB + 5, 9 * MiB])
+@pytest.mark.parametrize("lo,dup", [(4, False), (5, True), (7, False)])
+def test_nested_words(lo, dup, n):
+    """Words that are prefixes of others or equal, in text made of them: grams
+    of one trie node with more than one string below it (walked from that
+    node), of several nodes, and lists of several ids."""
+    rng = np.random.default_rng(n + lo)
+    stems = _patterns(rng, 120, lo, lo + 2, LOWER)
+    pats = stems + [s + bytes(rng.choice(LOWER, int(rng.integers(1, 6))).astype(np.uint8)) for s in stems for _ in range(2)]
+    # the same tails behind other heads: one gram at several nodes
+    pats += [bytes(rng.choice(LOWER, 2).astype(np.uint8)) + s for s in stems[:40] if lo >= 5]
+    if dup:
+        pats += pats[::3]
+    words = [pats[int(i)] + bytes(rng.choice(LOWER, int(j)).astype(np.uint8))
+             for i, j in zip(rng.integers(0, len(pats), n // 60), rng.integers(0, 60, n // 60))]
+    text = np.frombuffer(b"".join(words), dtype=np.uint8)[:n]
+    text = np.concatenate([text, rng.choice(LOWER, n - text.size).astype(np.uint8)])
+    text[-lo:] = np.frombuffer(stems[0][:lo], dtype=np.uint8)
+    want = oracle.bucketed(text, pats, threads=8)
+    say(f"gram words lo={lo} dup={dup} n={n}: {want.n} matches")
+    got, counts = gpu_scan(pf.Trie(pats), text, pad_front=n % 16)
+    assert_same(got, want)
+    assert np.array_equal(counts, oracle.counts(n, want))
