@@ -292,6 +292,8 @@ static int upload_image(pfac_trie *t) {
     v.gpat = b + o_gpat;
     v.gram_s = I.gram_s;
     v.gram_lw = I.gram_lw;
+    v.gram_q = I.gram_q;
+    v.gram_sh = I.gram_sh;
     v.gfp_lb = I.gfp_lb;
     v.min_len = (uint32_t)std::min<uint64_t>(t->crs.min_len, 0xffffffffu);
     v.fold_syms = I.fold_syms;
@@ -794,7 +796,7 @@ static uint32_t unit_bytes(const pfac_trie *t, const pfac_tuning &tn) {
 // Opt a kernel into more than 64 KiB of dynamic LDS (once per size).
 static hipError_t grant_lds(int slot, uint32_t bytes, hipError_t (*fn)(int, uint32_t), int arg) {
     static std::mutex mu;
-    static uint32_t granted[32] = {};
+    static uint32_t granted[40] = {};
     std::lock_guard<std::mutex> lock(mu);
     if (granted[slot] >= bytes) return hipSuccess;
     hipError_t e = fn(arg, bytes);
@@ -972,7 +974,7 @@ static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
         int occ;
         uint64_t want;
         if (gram) {
-            const int sl = (int)a.im.gram_s;
+            const int sl = (int)a.im.gram_s + (a.im.gram_q ? 8 : 0);
             if (h.gram_lds) HIP_TRY(grant_lds(20 + sl, a.lds_total, prepare_gram_kernel, sl));
             // (without the bitmap in LDS at least a wave per unit is resident)
             occ = h.gram_lds ? 1 : 1 << 20;

@@ -56,10 +56,11 @@ struct ImageView {
     uint32_t qa, qb, qalph, q16_mul;  // its symbol map, alphabet bytes and hash multiplier
     uint32_t top_nodes, top_rw;       // bitmapped top nodes: count, words per node
     const uint32_t *gram;     // gram filter: bitmap words (2^gram_lw)
-    const uint4 *gfp;         // gram filter: buckets of 14 slots and a record number (2^gfp_lb; 0 = none)
+    const uint4 *gfp;         // gram filter: buckets of 14 slots and a record number (2^gfp_lb)
     const uint4 *grec;        // gram filter: a record per slot
     const uint8_t *gpat;      // gram filter: the patterns' bytes
     uint32_t gram_s, gram_lw, gfp_lb, min_len;
+    uint32_t gram_q, gram_sh;  // grams of gram_q two-bit symbols, from bit gram_sh of a byte (0: of four bytes)
 };
 
 struct ScanArgs {
@@ -163,7 +164,7 @@ int max_wave_wg_per_cu(const ScanArgs &a, uint32_t waves);
 // every unit in one kernel.  The LDS layout for `waves` waves (the bitmap and
 // one area per wave), and the launch.
 void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table, uint32_t lds_limit);
-hipError_t prepare_gram_kernel(int s, uint32_t lds_bytes);
+hipError_t prepare_gram_kernel(int fn_id, uint32_t lds_bytes);
 hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, bool lds_table, uint32_t grid, hipStream_t s);
 
 // Largest resident workgroups per CU for this layout.

@@ -10,6 +10,14 @@
 // positions a lane cost four tests of ten VALU instructions instead of
 // sixteen of four and a second stage over many more survivors.
 //
+// Over four symbols (DNA) a gram of four bytes keeps 1 position in 256 or
+// more; there a gram is up to 16 symbols, packed to two bits each by 8-bit dot
+// products, the next 16 symbols taken from the next lane.  (1 GiB against
+// 100,000 patterns of 20 to 32: 830 us with a hash per position and a second
+// stage of walks, 572 so, VALU busy for 330 of it, L2 reads of the slots of 57
+// false positives a KiB for 230; 32 MiB against 500 patterns of 9 to 14, where
+// the generic filter kept every 25th position: 90 us, 30 so.)
+//
 //   * a workgroup loads the bitmap (two hashed bits per gram, at most 128 KiB)
 //     into LDS; each wave owns units of G consecutive 1 KiB chunks of test
 //     positions and keeps a group of GC chunks of loads in flight;
@@ -34,12 +42,13 @@
 
 namespace pfac {
 
-// A wave's lists in LDS: queued grams (8 bytes each), grams whose starts are
+// A wave's lists in LDS: queued grams (6 bytes each), grams whose starts are
 // to be looked at (6) and matches of the unit (8).  The short ones fit 16 waves
 // beside a bitmap of 128 KiB; texts that hit often (words: 50 grams a KiB)
 // want the long ones, so that a group never overflows the queue.
-constexpr uint32_t kGqShort = 120, kGcShort = 92, kGmShort = 64;
-constexpr uint32_t kGqLong = 448, kGcLong = 192, kGmLong = 160;
+constexpr uint32_t kGqShort = 160, kGcShort = 88, kGmShort = 64;
+constexpr uint32_t kGqLong = 444, kGcLong = 192, kGmLong = 160;
+constexpr uint32_t kGqPad = 4;    // entries past the queue's end, the first written by grams that find it full
 constexpr uint32_t kGqRoom = 57;  // the queue is emptied when a group leaves less room
 
 typedef __attribute__((address_space(3))) const uint32_t lds_word_t;
@@ -48,6 +57,8 @@ typedef __attribute__((address_space(4))) const uint64_t scalar_u64_t;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const u32x2 lds_pair_t;
+typedef __attribute__((address_space(3))) uint32_t lds_out32_t;
+typedef __attribute__((address_space(3))) uint16_t lds_out16_t;
 
 // The filter's hash of a gram: its 16-bit halves times two odd constants.
 __device__ __forceinline__ uint32_t gram_hash(uint32_t x) {
@@ -149,16 +160,30 @@ __device__ __forceinline__ TextSpan text_span(const ScanArgs &a, uint64_t p, con
     return TextSpan{i, a.offsets[i] + a.shift, a.offsets[i + 1] + a.shift};
 }
 
-// 16 text bytes at frame position p as four words, or false when their whole
+// 20 text bytes at frame position p as five words, or false when their whole
 // loads could pass the text's last 16-byte block (at blk_hi).
-__device__ __forceinline__ bool text16(const uint8_t *base, uint64_t p, uint64_t blk_hi, uint4 &t) {
+__device__ __forceinline__ bool text20(const uint8_t *base, uint64_t p, uint64_t blk_hi, uint32_t (&t)[5]) {
     const uint64_t p4 = p & ~3ull;
-    if (p4 + 20 > blk_hi + 16) return false;
+    if (p4 + 24 > blk_hi + 16) return false;
     const uint32_t *q = (const uint32_t *)(base + p4);
-    const uint32_t w0 = q[0], w1 = q[1], w2 = q[2], w3 = q[3], w4 = q[4], sh = (uint32_t)(p & 3);
-    t = make_uint4(__builtin_amdgcn_alignbyte(w1, w0, sh), __builtin_amdgcn_alignbyte(w2, w1, sh),
-                   __builtin_amdgcn_alignbyte(w3, w2, sh), __builtin_amdgcn_alignbyte(w4, w3, sh));
+    uint32_t w[6];
+#pragma unroll
+    for (int k = 0; k < 6; k++) w[k] = q[k];
+#pragma unroll
+    for (int k = 0; k < 5; k++) t[k] = __builtin_amdgcn_alignbyte(w[k + 1], w[k], (uint32_t)(p & 3));
     return true;
+}
+
+// whether the first n (at most 20) of the text bytes t are those at pat
+__device__ __forceinline__ bool equal20(const uint32_t (&t)[5], const uint8_t *pat, uint32_t n) {
+    const uint32_t *c = (const uint32_t *)pat;
+    uint32_t diff = 0;
+#pragma unroll
+    for (int k = 0; k < 5; k++) {
+        const int32_t left = (int32_t)n - 4 * k;
+        diff |= (t[k] ^ c[k]) & (left >= 4 ? 0xffffffffu : left <= 0 ? 0u : (1u << (8 * left)) - 1u);
+    }
+    return diff == 0;
 }
 
 // walk_g from node v at depth d with the first 16 text bytes in registers: a
@@ -498,12 +523,13 @@ __device__ __forceinline__ void emit_spilled(const ScanArgs &a, uint64_t u, uint
 }
 
 // S: the distance of test positions (im.gram_s).  LT: the bitmap is copied to
-// LDS; without it the tests read it from global memory.
-template <int S, bool LT>
+// LDS; without it the tests read it from global memory.  SYM: a gram is
+// im.gram_q symbols of two bits each.
+template <int S, bool LT, bool SYM>
 __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     extern __shared__ __align__(16) uint8_t lds[];
     constexpr uint32_t TL = 16 / S;            // tests per lane and chunk
-    constexpr uint32_t GC = S == 4 ? 4 : 2;    // chunks per group and in flight
+    constexpr uint32_t GC = SYM ? 3 : S == 4 ? 4 : 2;  // chunks per group and in flight
     const ImageView &im = a.im;
     const uint32_t tid = threadIdx.x;
     const uint32_t waves = blockDim.x >> 6;
@@ -521,18 +547,19 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     __syncthreads();
 
     uint8_t *wbase = lds + a.off_wave + wave * a.wave_bytes;
-    uint2 *wq = (uint2 *)wbase;                              // queue: (gram, unit position)
     const uint32_t gq = a.gq;
-    uint32_t *wcr = (uint32_t *)(wbase + 8 * gq);            // starts: record of the gram's slot ...
-    uint16_t *wcp = (uint16_t *)(wbase + 8 * gq + 4 * a.gc); // ... and its unit position
-    uint2 *wm = (uint2 *)(wbase + 8 * gq + 6 * a.gc);        // matches
+    uint32_t *wq = (uint32_t *)wbase;                        // queue: gram ...
+    uint16_t *wqp = (uint16_t *)(wbase + 4 * (gq + kGqPad + a.gc));  // ... and unit position
+    uint32_t *wcr = wq + gq + kGqPad;                            // starts: record of the gram's slot ...
+    uint16_t *wcp = wqp + gq + kGqPad;                            // ... and its unit position
+    uint2 *wm = (uint2 *)(wbase + 6 * (gq + kGqPad + a.gc));          // matches
 
     const uint64_t hi_valid = a.shift + a.total;
     const uint32_t n_u = (uint32_t)a.n_tiles, n_ch = (uint32_t)a.n_plan, G = a.group;
     const uint32_t ustride = gridDim.x * waves;
     const uint64_t blk_hi = (hi_valid - 1) & ~15ull;
     const uint32_t lane16 = 16u * lane;
-    const uint32_t adr_mask = (4u << im.gram_lw) - 4u;
+    uint32_t adr_mask = (4u << im.gram_lw) - 4u;
     const uint32_t lb = im.gfp_lb;
 
     // ---- loads: GC chunks of a unit from chunk g on; a slot past the unit's
@@ -540,7 +567,7 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     // that, so every load is issued and every wait counts only later loads
     struct Slot {
         uint4 v;
-        uint32_t h;  // the dword after the lane's 16 bytes (S < 4)
+        uint32_t h;  // the dword after the lane's 16 bytes (S < 4); SYM: dword lane % 4 of the 16 bytes after the chunk
     };
     struct Cur {
         uint32_t u, g, n;  // unit, first chunk of the group, chunks of the unit
@@ -569,7 +596,10 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         // (non-temporal: the text is read once, the tables of the walks stay in L2)
         const u32x4 v = __builtin_nontemporal_load((const u32x4 *)(a.base + sb + min(o, lim)));
         s.v = make_uint4(v.x, v.y, v.z, v.w);
-        s.h = S == 4 ? 0u : *(const uint32_t *)(a.base + sb + min(o + 16u, lim));
+        if (SYM)
+            s.h = *(const uint32_t *)(a.base + sb + min(kChunk * (min(i, last) + 1), lim) + 4 * (lane & 3));
+        else
+            s.h = S == 4 ? 0u : *(const uint32_t *)(a.base + sb + min(o + 16u, lim));
         return s;
     };
     uint32_t qn = 0;  // grams queued (kept in scalar registers, as all counts)
@@ -583,27 +613,50 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     };
     auto test = [&](uint32_t ent, uint32_t h, uint32_t x) -> uint32_t { return (ent >> (h & 31u)) & (ent >> (x & 31u)) & 1u; };
     // queue the grams x that hit, at unit positions pos; past the queue's end
-    // they are only counted
+    // they are counted, and written to the entry there that nothing reads.
+    // (The loop has more uniform values than scalar registers: those of every
+    // test are in vector ones.)
+    uint32_t q_at = a.off_wave + wave * a.wave_bytes, qp_at = q_at + 4 * (gq + kGqPad + a.gc), q_end = gq;
+    asm volatile("" : "+v"(adr_mask), "+v"(q_at), "+v"(qp_at), "+v"(q_end));
     auto queue = [&](uint32_t hit, uint32_t x, uint32_t pos) {
         const unsigned long long mk = __ballot(hit != 0);
         if (mk == 0) return;
         const uint32_t at = qn;
         qn += (uint32_t)__popcll(mk);
-        if (qn > gq) return;
         if (__builtin_amdgcn_inverse_ballot_w64(mk)) {  // the compare's mask as it is
-            uint32_t *q = (uint32_t *)wq + 2 * mbcnt_from(mk, at);
-            q[0] = x;
-            q[1] = pos;
+            const uint32_t i = min(mbcnt_from(mk, at), q_end);
+            *(lds_out32_t *)(uintptr_t)(q_at + 4 * i) = x;
+            *(lds_out16_t *)(uintptr_t)(qp_at + 2 * i) = (uint16_t)pos;
         }
     };
+    // four text bytes' symbols, two bits each from bit gram_sh of each byte, in
+    // 8 bits from there on (first symbol lowest)
+    const uint32_t sym_sh = im.gram_sh;
+    uint32_t sym_bits = 0x03030303u << sym_sh;
+    uint32_t sym_mask = SYM ? 0xffffffffu >> (32 - 2 * im.gram_q) : 0u;
+    if (SYM) asm volatile("" : "+v"(sym_bits), "+v"(sym_mask));
+    auto pack4 = [&](uint32_t w) -> uint32_t { return __builtin_amdgcn_udot4(w & sym_bits, 0x40100401u, 0u, false); };
     // the TL tests of a lane's 16 positions from unit position pos on
     auto tests = [&](const Slot &s, uint32_t pos) {
         const uint32_t w[5] = {s.v.x, s.v.y, s.v.z, s.v.w, s.h};
         uint32_t x[TL], h[TL], ent[TL];
+        uint32_t p0 = 0, p1 = 0;
+        if (SYM) {
+            // the lane's 16 symbols and, from the next lane, those after them;
+            // lane 63 takes them from the 16 bytes after the chunk
+            p0 = (pack4(w[0]) + (pack4(w[1]) << 8)) >> sym_sh | (pack4(w[2]) + (pack4(w[3]) << 8)) << (16 - sym_sh);
+            uint32_t e = pack4(w[4]) >> sym_sh << (8 * (lane & 3));
+            e |= (uint32_t)__builtin_amdgcn_mov_dpp((int)e, 0xB1, 0xf, 0xf, true);  // of lane ^ 1
+            e |= (uint32_t)__builtin_amdgcn_mov_dpp((int)e, 0x4E, 0xf, 0xf, true);  // of lane ^ 2
+            p1 = (uint32_t)__builtin_amdgcn_update_dpp((int)e, (int)p0, 0x130, 0xf, 0xf, false);  // of lane + 1
+        }
 #pragma unroll
         for (uint32_t j = 0; j < TL; j++) {
             const uint32_t b = j * S;
-            x[j] = (b & 3) == 0 ? w[b >> 2] : __builtin_amdgcn_alignbyte(w[(b >> 2) + 1], w[b >> 2], b & 3);
+            if (SYM)
+                x[j] = (b == 0 ? p0 : __builtin_amdgcn_alignbit(p1, p0, 2 * b)) & sym_mask;
+            else
+                x[j] = (b & 3) == 0 ? w[b >> 2] : __builtin_amdgcn_alignbyte(w[(b >> 2) + 1], w[b >> 2], b & 3);
             ent[j] = lookup(x[j], h[j]);
         }
 #pragma unroll
@@ -625,21 +678,17 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     auto check = [&](uint32_t at_least) __attribute__((always_inline)) {
         if (nb) {
             // the slot with the gram's fingerprint
-            uint32_t m = 0, base = 0;
-            if (lb) {
-                const uint32_t want = gb >> (20u - lb) << 4 & 0xfff0u, w2 = want << 16 | want;
-                m = pk_min(fb0.x ^ w2, fb0.y ^ w2);
-                m = pk_min(m, pk_min(fb0.z ^ w2, fb0.w ^ w2));
-                m = pk_min(m, pk_min(fb1.x ^ w2, fb1.y ^ w2));
-                m = pk_min(m, fb1.z ^ w2);
-                m = min(m & 0xffffu, m >> 16);
-                base = fb1.w;
-            }
+            const uint32_t want = gb >> (20u - lb) << 4 & 0xfff0u, w2 = want << 16 | want;
+            uint32_t m = pk_min(fb0.x ^ w2, fb0.y ^ w2);
+            m = pk_min(m, pk_min(fb0.z ^ w2, fb0.w ^ w2));
+            m = pk_min(m, pk_min(fb1.x ^ w2, fb1.y ^ w2));
+            m = pk_min(m, fb1.z ^ w2);
+            m = min(m & 0xffffu, m >> 16);
             const bool pass = lane < nb && m < 14u;
             const unsigned long long mk = __ballot(pass);
             if (pass) {
                 const uint32_t i = cn + mbcnt(mk);
-                wcr[i] = base + m;
+                wcr[i] = fb1.w + m;
                 wcp[i] = (uint16_t)tb;
             }
             cn += (uint32_t)__popcll(mk);
@@ -649,14 +698,12 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
             // the last (up to) 64 grams of the queue
             nb = min(qn, 64u);
             qn -= nb;
-            const uint2 q = wq[min(qn + lane, gq - 1)];
-            tb = q.y;
-            gb = q.x * im.pfx4_mul;
-            if (lb) {
-                const uint4 *bk = im.gfp + (gb >> (32u - lb) << 1);
-                fb0 = bk[0];
-                fb1 = bk[1];
-            }
+            const uint32_t i = min(qn + lane, gq - 1);
+            tb = wqp[i];
+            gb = wq[i] * im.pfx4_mul;
+            const uint4 *bk = im.gfp + (gb >> (32u - lb) << 1);
+            fb0 = bk[0];
+            fb1 = bk[1];
         }
     };
 
@@ -677,47 +724,60 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         const uint32_t rem = cc.n - cc.g;
         const bool last = rem <= GC;
         const uint32_t gpos = cc.g * kChunk + lane16;
-        const uint32_t q0 = qn;
+        // a chunk that overflows the queue is tested again below, one test at a
+        // time
+        uint32_t redo = 0;
 #pragma unroll
         for (uint32_t i = 0; i < GC; i++) {
+            const uint32_t q0 = qn;
             if (i == 0 || i < rem) tests(slot[i], gpos + i * kChunk);
+            if (qn > gq) {
+                qn = q0;
+                redo |= 1u << i;
+            }
+            // (SYM images may queue 60 grams a chunk)
+            if (SYM) {
+                wave_sync();
+                if (qn >= 64 && cn <= a.gc - 64) check(64);
+            }
             slot[i] = load(pc, i);
         }
-        // the chunks of a group that overflows the queue are tested again
-        // below, one test at a time
-        uint32_t r_from = GC;
-        const uint32_t r_to = min(GC, rem);
-        if (qn > gq) {
-            qn = q0;
-            r_from = 0;
+        if (!SYM) {
+            wave_sync();
+            check(64);
         }
-        wave_sync();
-        check(64);
-        uint32_t ra = 0;  // next test of chunk r_from
+        uint32_t ra = 0;  // next test of the chunk that is tested again
 
-        if (last || r_from < r_to || qn + kGqRoom > gq || cn > a.gc - 64) {
+        if (last || redo || qn + kGqRoom > gq || cn > a.gc - 64) {
             // ---- empty the queue as far as the next group needs it, and wholly
             // after the unit's last group
             const ScanArgs &r = again(a);
             UnitTexts ut = unit_texts(r, cc.u, ubase);
             for (;;) {
-                if (r_from < r_to && qn + 64 <= gq) {
-                    const uint32_t pos = gpos + r_from * kChunk + ra;
+                if (redo && qn + 64 <= gq) {
+                    const uint32_t pos = gpos + (uint32_t)__builtin_ctz(redo) * kChunk + ra;
                     const uint8_t *ub = a.base + ulo;
                     const uint32_t last4 = (uint32_t)umin64(blk_hi + 12 - ulo, 0x7fffffffull);
                     const uint32_t t4 = min(pos & ~3u, last4);
                     uint32_t x = *(const uint32_t *)(ub + t4), h;
-                    if (S < 4) x = __builtin_amdgcn_alignbyte(*(const uint32_t *)(ub + min(t4 + 4u, last4)), x, pos & 3u);
+                    if (SYM) {
+                        uint64_t k = pack4(x);
+                        for (uint32_t i = 1; i < 5; i++)
+                            k += (uint64_t)pack4(*(const uint32_t *)(ub + min(t4 + 4 * i, last4))) << (8 * i);
+                        x = (uint32_t)(k >> sym_sh >> (2 * (pos & 3u))) & sym_mask;
+                    } else if (S < 4) {
+                        x = __builtin_amdgcn_alignbyte(*(const uint32_t *)(ub + min(t4 + 4u, last4)), x, pos & 3u);
+                    }
                     const uint32_t ent = lookup(x, h);
                     queue(test(ent, h, x), x, pos);
                     wave_sync();
                     ra += S;
                     if (ra == 16) {
                         ra = 0;
-                        r_from++;
+                        redo &= redo - 1;
                     }
                 }
-                const bool done = r_from >= r_to && (last ? (nb | qn) == 0 : qn < 64);
+                const bool done = redo == 0 && (last ? (nb | qn) == 0 : qn < 64);
                 if (cn > r.gc - 64 || (last && done)) {
                     // ---- compare or walk the starts; matches go to LDS, past
                     // gm to global memory
@@ -725,9 +785,8 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                     for (uint32_t c0 = 0; c0 < cn; c0 += 64) {
                         const uint32_t ci = min(c0 + lane, r.gc - 1);
                         const uint32_t t = wcp[ci];
-                        // (without slots every offset is walked)
-                        uint4 rec = make_uint4(kNone, (1u << S) - 1u, 0u, 0u);
-                        if (lb && c0 + lane < cn) rec = r.im.grec[wcr[ci]];
+                        uint4 rec = make_uint4(kNone, 0u, 0u, 0u);
+                        if (c0 + lane < cn) rec = r.im.grec[wcr[ci]];
                         uint32_t om = 0;
                         uint2 h = make_uint2(0, 0);
                         const uint32_t len = rec.y & 0xffffu;
@@ -737,14 +796,14 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                             om = rec.x == kNone ? rec.y : 0u;
                             if (rec.x == kGramNode && ubase + pr - r.shift < r.total &&
                                 ts.end - (ubase + pr) >= r.im.min_len) {
-                                const uint32_t o = rec.y & 3u;
-                                uint4 tw = make_uint4(0, 0, 0, 0);
-                                if (!text16(r.base, ubase + pr, blk_hi, tw))
+                                const uint32_t o = rec.y & 3u, d = rec.y >> 8;
+                                uint32_t tw[5];
+                                if (!text20(r.base, ubase + pr, blk_hi, tw))
                                     om = 1u << o;
-                                else if (tw.x == rec.z && ((tw.y ^ (rec.y >> 8)) & ((1u << (8 * o)) - 1u)) == 0)
+                                else if (equal20(tw, r.im.gpat + rec.z, d))
                                     h = walk_from(r.im, r.base, ubase + pr,
-                                                  (uint32_t)umin64(ts.end - (ubase + pr), 0xffffffffull), rec.w, o + 4,
-                                                  hi_valid, tw);
+                                                  (uint32_t)umin64(ts.end - (ubase + pr), 0xffffffffull), rec.w, d,
+                                                  hi_valid, make_uint4(tw[0], tw[1], tw[2], tw[3]));
                             } else if (rec.x < kGramNode && ubase + pr - r.shift < r.total &&
                                        ts.end - (ubase + pr) >= len) {
                                 const int eq = equal_pattern(r.base, ubase + pr, r.im.gpat + rec.x, len, blk_hi);
@@ -777,7 +836,7 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                 if (done) break;
                 // (the loop ends: with tests left, either the queue takes one
                 // above or this takes grams from it; then it only shrinks)
-                check(r_from < r_to ? gq - 63 : last ? 1 : 64);
+                check(redo ? gq - 63 : last ? 1 : 64);
             }
 
             // ---- the unit's last group: its matches in (pos, id) order
@@ -803,12 +862,15 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
 
 // ------------------------------------------------------------------ launchers
 
-static const void *gram_fn(uint32_t s, bool lds_table) {
-    if (lds_table)
-        return s == 4 ? (const void *)scan_grams<4, true>
-             : s == 2 ? (const void *)scan_grams<2, true> : (const void *)scan_grams<1, true>;
-    return s == 4 ? (const void *)scan_grams<4, false>
-         : s == 2 ? (const void *)scan_grams<2, false> : (const void *)scan_grams<1, false>;
+template <bool LT, bool SYM>
+static const void *gram_fn_s(uint32_t s) {
+    return s == 4 ? (const void *)scan_grams<4, LT, SYM>
+         : s == 2 ? (const void *)scan_grams<2, LT, SYM> : (const void *)scan_grams<1, LT, SYM>;
+}
+
+static const void *gram_fn(uint32_t s, bool lds_table, bool sym) {
+    if (sym) return lds_table ? gram_fn_s<true, true>(s) : gram_fn_s<false, true>(s);
+    return lds_table ? gram_fn_s<true, false>(s) : gram_fn_s<false, false>(s);
 }
 
 void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table, uint32_t lds_limit) {
@@ -817,20 +879,21 @@ void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table, uint32_t lds_l
         a.gq = gq;
         a.gc = gc;
         a.gm = gm;
-        a.wave_bytes = (8 * gq + 6 * gc + 8 * gm + 7u) & ~7u;
+        a.wave_bytes = 6 * (gq + kGqPad + gc) + 8 * gm;
         a.lds_total = a.off_wave + waves * a.wave_bytes + 16;
     };
     // the queue's and the starts' place is also where a unit's matches are
-    // sorted (64 entries, or 256 + 64 words)
-    static_assert(8 * 64 <= 8 * kGqShort && 4 * (256 + 64) <= 8 * kGqShort + 6 * kGcShort, "sort area");
+    // sorted (at most gm entries, or 256 + 64 words)
+    static_assert(4 * (256 + 64) <= 6 * (kGqShort + kGqPad + kGcShort) && 8 * kGmLong <= 6 * (kGqLong + kGqPad + kGcLong), "sort area");
+    static_assert((kGqShort + kGqPad + kGcShort) % 4 == 0 && (kGqLong + kGqPad + kGcLong) % 4 == 0, "matches at multiples of 8");
     static_assert(kGqShort >= 64 + kGqRoom - 1 && kGcShort >= 64 && kGmShort >= 64, "a round fits");
     lists(kGqLong, kGcLong, kGmLong);
     if (!lds_table || a.lds_total > lds_limit) lists(kGqShort, kGcShort, kGmShort);
 }
 
-hipError_t prepare_gram_kernel(int s, uint32_t lds_bytes) {
+hipError_t prepare_gram_kernel(int fn_id, uint32_t lds_bytes) {
     // the bitmap is addressed at LDS address 0: no static LDS in front of it
-    const void *fn = gram_fn((uint32_t)s, true);
+    const void *fn = gram_fn((uint32_t)fn_id & 7u, true, fn_id >= 8);
     hipFuncAttributes attr;
     hipError_t e = hipFuncGetAttributes(&attr, fn);
     if (e != hipSuccess) return e;
@@ -842,7 +905,7 @@ hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, bool lds_table, 
     ScanArgs arg = a;
     void *args[] = {(void *)&arg};
     const hipError_t e =
-        hipLaunchKernel(gram_fn(a.im.gram_s, lds_table), dim3(grid), dim3(64 * waves), args, a.lds_total, s);
+        hipLaunchKernel(gram_fn(a.im.gram_s, lds_table, a.im.gram_q != 0), dim3(grid), dim3(64 * waves), args, a.lds_total, s);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }

@@ -139,8 +139,10 @@ struct DeviceImageHost {
     // starts at position p spells, at the next multiple t of S (0 <= t - p <
     // S), a four-byte gram that lies inside it when it has S + 3 bytes or
     // more; so only every S-th position of a text is tested, against the
-    // grams at offsets 0 .. S-1 of every pattern.  For a gram x (first byte
-    // lowest) h = (x mod 2^16) * kGramC0 + (x >> 16) * kGramC1 mod 2^32 (the
+    // grams at offsets 0 .. S-1 of every pattern.  Over at most four symbols
+    // that differ in bits gram_sh and gram_sh + 1, a gram is gram_q (at most 16)
+    // symbols of two bits each, gram_q + S - 1 <= the shortest pattern.  For a
+    // gram x (first byte or symbol lowest) h = (x mod 2^16) * kGramC0 + (x >> 16) * kGramC1 mod 2^32 (the
     // middle bits of the products name the word: the top ones hardly see the
     // low byte of each half, which text needs):
     //  - gram: 2^gram_lw words; word (h >> kGramShift) mod 2^gram_lw has bits
@@ -148,17 +150,18 @@ struct DeviceImageHost {
     //  - gfp: 2^gfp_lb buckets of 32 bytes: 14 16-bit slots and the number of
     //    the bucket's first record.  For g = x * kPfx4Mul, bucket g >> (32 -
     //    gfp_lb) has one slot i with the 12 bits of g below those in its upper
-    //    bits and i in its lower four (0xffff: empty); gfp_lb = 0: no slots;
+    //    bits and i in its lower four (0xffff: empty);
     //  - grec: a record (4 words) per slot.  When one string remains below the
     //    only trie node that its grams end at: the string's offset in gpat,
     //    its length | offset of the gram in it << 16 | ids of its pattern list
     //    << 18, and kGramId | id for a list of one id, else the list's offset.
-    //    Of another single node: kGramNode, offset | bytes 4 .. 6 of the path
-    //    to it << 8, the path's first four bytes, the node.  Otherwise kNone
-    //    and the offsets of the grams as bits 1 << offset;
+    //    Of another single node: kGramNode, offset of the gram | depth of the
+    //    node << 8, the offset in gpat of a pattern below it, the node.
+    //    Otherwise kNone and the offsets of the grams as bits 1 << offset;
     //  - gpat: every pattern's bytes, each from a multiple of four on.
     uint32_t gram_s = 0;               // S: 4, 2 or 1 (0 = no gram filter)
     uint32_t gram_lw = 0, gfp_lb = 0;
+    uint32_t gram_q = 0, gram_sh = 0;  // gram_q 0: grams of four bytes
     std::vector<uint32_t> gram;
     std::vector<uint16_t> gfp;
     std::vector<uint32_t> grec;

@@ -11,6 +11,7 @@
 // identities as ranks carried on its edges (build_dag).  The default image is
 // the whole CRS trie, since every (position, pattern id) match is reported.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <numeric>
 #include <string>
@@ -585,88 +586,124 @@ static void build_dag(const CrsTrie &T, DeviceImageHost &I) {
     I.chain.assign(40, 0);
 }
 
-// Gram filter: the four-byte grams at offsets 0 .. S-1 of every pattern.  A
-// larger S tests fewer positions but puts S grams per pattern into a bitmap
-// that LDS bounds at 2^20 bits; past 2^18 grams a smaller S leaves fewer
-// false positives per byte (two bits a gram: 28% of the positions tested at
-// 400,000 grams, 10% at 200,000), and past 2^19 first grams none is built.
+// Gram filter.  A larger S tests fewer positions but puts S grams per pattern
+// into a bitmap that LDS bounds at 2^20 bits; S is the one with the least cost
+// per text byte, of a test 1, of a false positive (16-bit slots read from L2) 9
+// and of a gram of a pattern (its record and a compare or walk) 130.  (1 GiB
+// with 100,000 patterns of 20 symbols: every second position, 11% false
+// positives, 572 us; every fourth, 29%, 657; 32 MiB with 500 of 9: every
+// position 30, every second, where 1.5% of all grams are a pattern's, 40.)
 static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
     if (!T.k || T.min_len < 4) return;
     auto level = [&](uint32_t d) { return T.level_start[d + 1] - T.level_start[d]; };
-    uint32_t S = T.min_len >= 7 ? 4 : T.min_len >= 5 ? 2 : 1;
-    uint64_t n = 0;
-    for (;; S /= 2) {
-        n = 0;
-        for (uint32_t o = 0; o < S; o++) n += level(o + 4);  // at most so many distinct grams at offset o
-        if (S == 1 || n <= (1u << 18)) break;
+    // at most four symbols that differ in two neighbouring bits: grams of up to
+    // 16 symbols
+    bool sym = false;
+    if (I.alphabet <= 4) {
+        bool used[256] = {};
+        for (const uint8_t c : T.labels) used[c] = true;
+        for (uint32_t sh = 0; sh <= 6 && !sym; sh++) {
+            uint32_t seen = 0;
+            for (uint32_t c = 0; c < 256; c++)
+                if (used[c]) seen |= 1u << ((c >> sh) & 3u);
+            sym = I.alphabet == (uint32_t)__builtin_popcount(seen);
+            if (sym) I.gram_sh = sh;
+        }
     }
-    if (n > (1u << 19) || I.pout_ids.size() >= kGramId) return;
+    auto q_of = [&](uint32_t S) { return sym ? (uint32_t)std::min<uint64_t>(16, T.min_len - S + 1) : 4u; };
+    uint32_t S = 0;
+    uint64_t n = 0;
+    double best = 0;
+    for (uint32_t s = 1; s <= 4 && s + 3 <= T.min_len; s *= 2) {
+        uint64_t m = 0;  // at most so many distinct grams
+        for (uint32_t o = 0; o < s; o++) m += level(o + q_of(s));
+        double f = 1.0 - std::exp(-(double)m / (1u << 19));  // bits set of a full bitmap
+        const double density = (double)m / std::pow((double)I.alphabet, (double)q_of(s));
+        const double c = (1.0 + 9.0 * f * f + 130.0 * density) / s;
+        if (m > (1u << 19) || (S && (c >= best || (sym && 1024 / s * f * f > 60)))) continue;
+        S = s;
+        n = m;
+        best = c;
+    }
+    if (!S || I.pout_ids.size() >= kGramId) return;
+    const uint32_t Q = q_of(S);
+    // where more than 60 false positives a KiB are left the 16-symbol filter is
+    // faster while it holds its keys (96 MiB, 200,000 patterns of 20 to 32
+    // symbols: 171 us, this 312; 500,000: 5,440, this 607)
+    const double fill = 1.0 - std::exp(-(double)n / (1u << 19));
+    if (sym && I.q16_lw && n <= (1u << 18) && 1024 / S * fill * fill > 60) return;
     // small alphabets: past a quarter of all grams the filter keeps too much
-    const double all = (double)I.alphabet * I.alphabet * I.alphabet * I.alphabet;
-    if (4.0 * (double)n > all) return;
+    if (4.0 * (double)n > std::pow((double)I.alphabet, (double)Q)) return;
     uint32_t lg = 12;  // bits of the bitmap: 24 a gram, at most 2^20
     while (lg < 20 && (1ull << lg) < 24 * n) lg++;
+    // without slots of its grams there is no filter
+    auto drop = [&]() {
+        I.gram_s = 0;
+        I.gram.clear();
+        I.gfp.clear();
+        I.grec.clear();
+        I.gpat.clear();
+    };
+    I.gram_q = sym ? Q : 0;
     I.gram_s = S;
     I.gram_lw = lg - 5;
     I.gram.assign(1u << I.gram_lw, 0);
-    auto each_gram = [&](auto &&f) {
-        for (uint32_t o = 0; o < S; o++)
-            for (uint32_t v = T.level_start[o + 4]; v < T.level_start[o + 5]; v++) {
-                const uint8_t *p = T.pat_data.data() + T.pat_off[T.rep[v]] + o;
-                f((uint32_t)p[0] | (uint32_t)p[1] << 8 | (uint32_t)p[2] << 16 | (uint32_t)p[3] << 24, o, v);
-            }
+    struct Gram {
+        uint32_t x, v, o;  // gram, trie node it ends at, offset
     };
-    each_gram([&](uint32_t x, uint32_t, uint32_t) {
-        const uint32_t h = (x & 0xffffu) * kGramC0 + (x >> 16) * kGramC1;
-        I.gram[(h >> kGramShift) & ((1u << I.gram_lw) - 1u)] |= (1u << (h & 31)) | (1u << (x & 31));
-    });
-    // buckets of 14 slots: about three grams each, more buckets while one overflows
+    std::vector<Gram> grams;
+    grams.reserve(n);
+    for (uint32_t o = 0; o < S; o++)
+        for (uint32_t v = T.level_start[o + Q]; v < T.level_start[o + Q + 1]; v++) {
+            const uint8_t *p = T.pat_data.data() + T.pat_off[T.rep[v]] + o;
+            uint32_t x = 0;
+            if (sym)
+                for (uint32_t i = 0; i < Q; i++) x |= (uint32_t)((p[i] >> I.gram_sh) & 3) << (2 * i);
+            else
+                std::memcpy(&x, p, 4);
+            const uint32_t h = (x & 0xffffu) * kGramC0 + (x >> 16) * kGramC1;
+            I.gram[(h >> kGramShift) & ((1u << I.gram_lw) - 1u)] |= (1u << (h & 31)) | (1u << (x & 31));
+            grams.push_back(Gram{x, v, o});
+        }
+    // buckets of 14 slots: about three grams each, more buckets while one
+    // overflows.  The grams in the order of their buckets:
     struct Slot {
-        uint32_t node, mask;  // the trie node its only gram ends at (kNone: several), offsets
+        uint32_t fp, node, mask;  // 12 bits, the trie node its only gram ends at (kNone: several), offsets
     };
     constexpr uint32_t kSlots = 14;
     uint32_t lb = 1;
     while ((1ull << lb) * 3 < n) lb++;
-    bool put_all = false;
-    std::vector<Slot> slots;
-    for (const uint32_t top = std::min(lb + 3, 20u); !put_all && lb <= top; lb++) {
-        const uint32_t nb = 1u << lb;
-        I.gfp_lb = lb;
-        I.gfp.assign((size_t)16 * nb, 0xffffu);
-        slots.assign((size_t)kSlots * nb, Slot{0, 0});
-        put_all = true;
-        each_gram([&](uint32_t x, uint32_t o, uint32_t v) {
-            const uint32_t g = x * kPfx4Mul, b = g >> (32 - lb);
-            uint16_t *bk = I.gfp.data() + ((size_t)b << 4);
-            Slot *sl = slots.data() + (size_t)b * kSlots;
-            const uint32_t fp = (g >> (20 - lb)) & 0xfffu;
+    std::vector<uint32_t> at;
+    std::vector<Gram> order(n);
+    // slots of bucket b (kSlots + 1: too many)
+    auto slots_of = [&](uint32_t b, Slot *sl) -> uint32_t {
+        uint32_t m = 0;
+        for (uint32_t e = at[b]; e < at[b + 1]; e++) {
+            const Gram &q = order[e];
+            const uint32_t fp = (q.x * kPfx4Mul >> (20 - lb)) & 0xfffu;
             uint32_t i = 0;
-            while (i < kSlots && sl[i].mask && (uint32_t)(bk[i] >> 4) != fp) i++;
-            if (i == kSlots) {
-                put_all = false;
-                return;
+            while (i < m && sl[i].fp != fp) i++;
+            if (i == m) {
+                if (m == kSlots) return kSlots + 1;
+                sl[m++] = Slot{fp, q.v, 1u << q.o};
+            } else {
+                sl[i].node = kNone;
+                sl[i].mask |= 1u << q.o;
             }
-            bk[i] = (uint16_t)(fp << 4 | i);
-            sl[i].node = sl[i].mask ? kNone : v;
-            sl[i].mask |= 1u << o;
-        });
-    }
-    lb = I.gfp_lb;
-    if (!put_all) {  // every offset of a gram is walked
-        I.gfp_lb = 0;
-        I.gfp.clear();
-        return;
-    }
-    // The record of each slot.  A gram that ends at one trie node only, below
-    // which one pattern string remains: that string is compared with the text
-    // in one go.  No pattern ends above the node (its depth is at most
-    // S + 3, no pattern is shorter), so a gram of one node with more below it
-    // is walked from there.
-    std::vector<uint32_t> leaf(T.n_nodes());  // the only leaf below a node without another pattern's end, or kNone
-    for (uint32_t v = T.n_nodes(); v-- > 0;) {
-        const uint32_t nc = T.row_ptr[v + 1] - T.row_ptr[v];
-        const bool term = T.term_ptr[v + 1] > T.term_ptr[v];
-        leaf[v] = nc == 0 ? v : nc == 1 && !term ? leaf[T.row_ptr[v] + 1] : kNone;
+        }
+        return m;
+    };
+    Slot sl[kSlots];
+    for (const uint32_t top = std::min(lb + 3, 20u);; lb++) {
+        if (lb > top) return drop();
+        at.assign((1u << lb) + 2, 0);
+        for (const Gram &q : grams) at[(q.x * kPfx4Mul >> (32 - lb)) + 2]++;
+        for (size_t b = 2; b < at.size(); b++) at[b] += at[b - 1];
+        for (const Gram &q : grams) order[at[(q.x * kPfx4Mul >> (32 - lb)) + 1]++] = q;
+        bool fits = true;
+        for (uint32_t b = 0; fits && b < 1u << lb; b++)
+            if (at[b + 1] - at[b] > kSlots) fits = slots_of(b, sl) <= kSlots;
+        if (fits) break;
     }
     std::vector<uint32_t> pat_at(T.k);
     size_t bytes = 0;
@@ -674,42 +711,60 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
         pat_at[j] = (uint32_t)bytes;
         bytes += (T.pat_off[j + 1] - T.pat_off[j] + 3) & ~3ull;
     }
-    if (bytes >= 0xffffff00ull) {
-        I.gfp_lb = 0;
-        I.gfp.clear();
-        return;
-    }
+    if (bytes >= 0xffffff00ull) return drop();
     I.gpat.assign(bytes + 64, 0);
     for (uint32_t j = 0; j < T.k; j++)
         std::memcpy(I.gpat.data() + pat_at[j], T.pat_data.data() + T.pat_off[j], T.pat_off[j + 1] - T.pat_off[j]);
+    // The record of each slot.  A gram that ends at one trie node only, below
+    // which one pattern string remains: that string is compared with the text
+    // in one go.  No pattern ends above the node (its depth is at most
+    // the shortest pattern's length), so a gram of one node with more below it
+    // is walked from there.
+    I.gfp_lb = lb;
+    I.gfp.assign((size_t)16 << lb, 0xffffu);
     I.grec.reserve(4 * n);
-    for (size_t b = 0; b < ((size_t)1 << lb); b++) {
+    for (uint32_t b = 0; b < 1u << lb; b++) {
         const uint32_t base = (uint32_t)(I.grec.size() / 4);
-        I.gfp[16 * b + 14] = (uint16_t)base;
-        I.gfp[16 * b + 15] = (uint16_t)(base >> 16);
-        for (uint32_t i = 0; i < kSlots && slots[b * kSlots + i].mask; i++) {
-            const Slot &s = slots[b * kSlots + i];
-            const uint32_t l = s.node != kNone ? leaf[s.node] : kNone;
+        uint16_t *bk = I.gfp.data() + 16 * (size_t)b;
+        bk[14] = (uint16_t)base;
+        bk[15] = (uint16_t)(base >> 16);
+        const uint32_t m = slots_of(b, sl);
+        for (uint32_t i = 0; i < m; i++) {
+            const Slot &s = sl[i];
+            bk[i] = (uint16_t)(s.fp << 4 | i);
             uint32_t rec[4] = {kNone, s.mask, 0, 0};
-            const uint32_t o = (uint32_t)__builtin_ctz(s.mask);
             if (s.node != kNone) {
-                // the path to the node, o + 4 bytes
-                const uint8_t *pb = T.pat_data.data() + T.pat_off[T.rep[s.node]];
+                const uint32_t o = (uint32_t)__builtin_ctz(s.mask);
                 rec[0] = kGramNode;
-                rec[1] = o;
-                rec[2] = (uint32_t)pb[0] | (uint32_t)pb[1] << 8 | (uint32_t)pb[2] << 16 | (uint32_t)pb[3] << 24;
-                for (uint32_t i = 0; i < o; i++) rec[1] |= (uint32_t)pb[4 + i] << (8 + 8 * i);
+                rec[1] = o | (o + Q) << 8;
+                rec[2] = pat_at[T.rep[s.node]];
                 rec[3] = s.node;
-            }
-            if (l != kNone) {
-                const uint32_t j = T.rep[l];
+                // the list of the only leaf below, if no pattern ends before it
+                uint32_t list = kCountEsc, list_at = 0;
+                for (uint32_t l = s.node;;) {
+                    const uint32_t *r = &I.node[4ull * l];
+                    if (r[2] & kLeafEnd) {
+                        list = r[0] >> 24;
+                        list_at = r[3];
+                    } else if (r[2] & kSkipFlag) {
+                        l = r[3];
+                        continue;
+                    } else if ((r[2] & kNcMask) == 1 && !(r[2] & kTermFlag)) {
+                        l = T.row_ptr[l] + 1;
+                        continue;
+                    } else if ((r[2] & kNcMask) == 0) {
+                        list = r[2] >> kCountShift;
+                        list_at = r[3];
+                    }
+                    break;
+                }
+                const uint32_t j = T.rep[s.node];
                 const uint64_t len = T.pat_off[j + 1] - T.pat_off[j];
-                const uint32_t list = I.node[4ull * l + 2] >> kCountShift, at = I.node[4ull * l + 3];
                 if (len <= 0xffff && list < kCountEsc) {
                     rec[0] = pat_at[j];
                     rec[1] = (uint32_t)len | o << 16 | list << 18;
                     // a list of one id: the id itself
-                    rec[2] = list == 1 && I.pout_ids[at] < kGramId ? kGramId | I.pout_ids[at] : at;
+                    rec[2] = list == 1 && I.pout_ids[list_at] < kGramId ? kGramId | I.pout_ids[list_at] : list_at;
                     rec[3] = 0;
                 }
             }

@@ -1,8 +1,9 @@
 """The gram kernel (launches whose kernel the library chooses, patterns of
-four bytes or more) against the oracle, record by record: each distance of
-test positions, texts at odd addresses whose ends fall inside a chunk, starts
-at every offset around a unit's edge, batches of tiny and empty texts, matches
-past the LDS list of a unit and past its list in global memory."""
+four bytes or more; grams of up to 16 symbols over four) against the oracle,
+record by record: each distance of test positions, texts at odd addresses whose
+ends fall inside a chunk, starts at every offset around a unit's edge, batches
+of tiny and empty texts, matches past the LDS list of a unit and past its list
+in global memory."""
 
 import numpy as np
 import pytest
@@ -142,3 +143,69 @@ def test_nested_words(lo, dup, n):
     got, counts = gpu_scan(pf.Trie(pats), text, pad_front=n % 16)
     assert_same(got, want)
     assert np.array_equal(counts, oracle.counts(n, want))
+
+
+# four symbols: grams of up to 16 of them.  Short patterns (grams of 4 to 13
+# symbols, every position, every second or every fourth), long ones (16), sets
+# that fill the bitmap; alphabets of two and three symbols, bytes that share the
+# symbols' bits (upper case, N) in runs and alone, both ends of the text, starts
+# around the edges of units, runs of one symbol
+@pytest.mark.parametrize("alphabet", [b"acgt", b"ACT", b"01"])
+@pytest.mark.parametrize("lo,k,n,pad", [
+    (9, 500, 70, 3), (9, 60, 1023, 1), (9, 500, 1025, 15), (10, 300, 300_001, 11), (12, 500, 2560 * 1024, 7),
+    (20, 1000, 2560 * 1024 + 1, 0), (6, 20, 3 * MiB, 5), (9, 500, 8 * MiB + 1, 2), (13, 400, 9 * MiB, 13),
+    (20, 40_000, 9 * MiB + 1023, 9), (24, 100_000, 20 * MiB + 5, 1),
+])
+def test_symbols(lo, k, n, pad, alphabet):
+    rng = np.random.default_rng(lo + k + len(alphabet))
+    a = np.frombuffer(alphabet, dtype=np.uint8)
+    if len(alphabet) == 2:
+        lo *= 2
+    pats = _patterns(rng, k, lo, lo + 12, a)
+    text = rng.choice(a, n).astype(np.uint8)
+    if n > MiB:
+        text[n // 3:n // 3 + 9000] = ord("N")
+        text[n // 5:n // 5 + 40_000] ^= 0x20
+        other = rng.integers(0, n, n // 500)
+        text[other] = rng.integers(0, 256, other.size)
+        pats += [alphabet[:1] * lo, alphabet[1:2] * (lo + 3), alphabet[-1:] * 40]
+        text[n // 2:n // 2 + 700] = a[0]
+    for q in range(max(n // 3000, 4)):
+        p = np.frombuffer(pats[int(rng.integers(0, len(pats)))], dtype=np.uint8)
+        at = int(rng.integers(0, n - p.size + 1))
+        m = p.size if q % 4 else int(rng.integers(1, p.size + 1))
+        text[at:at + m] = p[:m]
+    for e in range(1, n // 1024, 16 if n > 8 * MiB else 3):
+        p = np.frombuffer(pats[e % len(pats)], dtype=np.uint8)
+        at = e * 1024 - pad + e // 3 % 24 - 20
+        if at >= 0 and at + p.size <= n - 40:
+            text[at:at + p.size] = p
+    first, last = (np.frombuffer(p, dtype=np.uint8) for p in pats[:2])
+    text[:first.size] = first
+    text[n - last.size:] = last
+    want = oracle.bucketed(text, pats, threads=8)
+    say(f"gram symbols {alphabet} lo={lo} k={k} n={n}: {want.n} matches")
+    got, counts = gpu_scan(pf.Trie(pats), text, pad_front=pad)
+    assert_same(got, want)
+    assert np.array_equal(counts, oracle.counts(n, want))
+
+
+@pytest.mark.parametrize("lo,k,most", [(9, 300, 60), (12, 500, 2000), (20, 5000, 40_000)])
+def test_symbols_batch(lo, k, most):
+    rng = np.random.default_rng(lo)
+    a = np.frombuffer(b"acgt", dtype=np.uint8)
+    pats = _patterns(rng, k, lo, lo + 10, a)
+    lens = rng.integers(0, most, 6 * MiB // most).tolist() + [0, 0, 1, lo]
+    offs = np.zeros(len(lens) + 1, dtype=np.uint64)
+    offs[1:] = np.cumsum(lens)
+    n = int(offs[-1])
+    text = rng.choice(a, n).astype(np.uint8)
+    for _ in range(n // 800):
+        p = np.frombuffer(pats[int(rng.integers(0, len(pats)))], dtype=np.uint8)
+        at = int(rng.integers(0, n - p.size))
+        text[at:at + p.size] = p
+    want = oracle.bucketed(text, pats, offsets=offs, threads=8)
+    say(f"gram symbols batch lo={lo}: {len(lens)} texts, {n} bytes, {want.n} matches")
+    got, cnt = gpu_scan_batch(pf.Trie(pats), text, offs, pad_front=lo)
+    assert cnt == want.n
+    assert_same(got, want, with_text=True)
