@@ -292,6 +292,7 @@ static int upload_image(pfac_trie *t) {
     v.gpat = b + o_gpat;
     v.gram_s = I.gram_s;
     v.gram_lw = I.gram_lw;
+    v.gram_run = I.gram_run;
     v.gram_q = I.gram_q;
     v.gram_sh = I.gram_sh;
     v.gfp_lb = I.gfp_lb;
@@ -974,7 +975,7 @@ static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
         int occ;
         uint64_t want;
         if (gram) {
-            const int sl = (int)a.im.gram_s + (a.im.gram_q ? 8 : 0);
+            const int sl = gram_fn_id(a.im);
             if (h.gram_lds) HIP_TRY(grant_lds(20 + sl, a.lds_total, prepare_gram_kernel, sl));
             // (without the bitmap in LDS at least a wave per unit is resident)
             occ = h.gram_lds ? 1 : 1 << 20;

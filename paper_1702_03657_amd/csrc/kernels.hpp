@@ -60,6 +60,7 @@ struct ImageView {
     const uint4 *grec;        // gram filter: a record per slot
     const uint8_t *gpat;      // gram filter: the patterns' bytes
     uint32_t gram_s, gram_lw, gfp_lb, min_len;
+    uint32_t gram_run;        // a position counts when the three after it hit too
     uint32_t gram_q, gram_sh;  // grams of gram_q two-bit symbols, from bit gram_sh of a byte (0: of four bytes)
 };
 
@@ -164,6 +165,7 @@ int max_wave_wg_per_cu(const ScanArgs &a, uint32_t waves);
 // every unit in one kernel.  The LDS layout for `waves` waves (the bitmap and
 // one area per wave), and the launch.
 void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table, uint32_t lds_limit);
+int gram_fn_id(const ImageView &im);  // at most 17
 hipError_t prepare_gram_kernel(int fn_id, uint32_t lds_bytes);
 hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, bool lds_table, uint32_t grid, hipStream_t s);
 

@@ -12,11 +12,16 @@
 //
 // Over four symbols (DNA) a gram of four bytes keeps 1 position in 256 or
 // more; there a gram is up to 16 symbols, packed to two bits each by 8-bit dot
-// products, the next 16 symbols taken from the next lane.  (1 GiB against
-// 100,000 patterns of 20 to 32: 830 us with a hash per position and a second
-// stage of walks, 572 so, VALU busy for 330 of it, L2 reads of the slots of 57
-// false positives a KiB for 230; 32 MiB against 500 patterns of 9 to 14, where
-// the generic filter kept every 25th position: 90 us, 30 so.)
+// products, the next 16 symbols taken from the next lane.  What bounds it are
+// false positives: each reads its slots from L2 and takes 8 us of 1 GiB's time
+// per KiB.  Patterns of 19 symbols or more hold four 16-symbol grams that start
+// one after another, so there every position is tested against the grams at
+// offsets 0 .. 3, one bit each, and four hits in a row are wanted: 1% for
+// 100,000 patterns, where two bits a gram leave 11% of every second position or
+// 29% of every fourth.  1 GiB, 100,000 patterns of 20 to 32: 329 us, VALU busy
+// for 278 of it (a hash per position and a second stage of walks 830, every
+// second position 571, pairs of two-bit hits 343); 32 MiB, 500 patterns of 9 to
+// 14, where the generic filter kept every 25th position: 30 us (90).
 //
 //   * a workgroup loads the bitmap (two hashed bits per gram, at most 128 KiB)
 //     into LDS; each wave owns units of G consecutive 1 KiB chunks of test
@@ -524,8 +529,9 @@ __device__ __forceinline__ void emit_spilled(const ScanArgs &a, uint64_t u, uint
 
 // S: the distance of test positions (im.gram_s).  LT: the bitmap is copied to
 // LDS; without it the tests read it from global memory.  SYM: a gram is
-// im.gram_q symbols of two bits each.
-template <int S, bool LT, bool SYM>
+// im.gram_q symbols of two bits each; 2 (S = 1): 16 of them, and a position
+// counts when the three after it hit too.
+template <int S, bool LT, int SYM>
 __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     extern __shared__ __align__(16) uint8_t lds[];
     constexpr uint32_t TL = 16 / S;            // tests per lane and chunk
@@ -608,10 +614,12 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     // both bits of x are
     auto lookup = [&](uint32_t x, uint32_t &h) -> uint32_t {
         h = gram_hash(x);
-        const uint32_t at = (h >> (kGramShift - 2)) & adr_mask;
+        const uint32_t at = (SYM == 2 ? h : h >> (kGramShift - 2)) & adr_mask;
         return LT ? *(lds_word_t *)(uintptr_t)at : *(const uint32_t *)((const uint8_t *)im.gram + at);
     };
-    auto test = [&](uint32_t ent, uint32_t h, uint32_t x) -> uint32_t { return (ent >> (h & 31u)) & (ent >> (x & 31u)) & 1u; };
+    auto test = [&](uint32_t ent, uint32_t h, uint32_t x) -> uint32_t {
+        return (SYM == 2 ? 1u : ent >> (h & 31u)) & (ent >> (x & 31u)) & 1u;
+    };
     // queue the grams x that hit, at unit positions pos; past the queue's end
     // they are counted, and written to the entry there that nothing reads.
     // (The loop has more uniform values than scalar registers: those of every
@@ -636,6 +644,21 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     uint32_t sym_mask = SYM ? 0xffffffffu >> (32 - 2 * im.gram_q) : 0u;
     if (SYM) asm volatile("" : "+v"(sym_bits), "+v"(sym_mask));
     auto pack4 = [&](uint32_t w) -> uint32_t { return __builtin_amdgcn_udot4(w & sym_bits, 0x40100401u, 0u, false); };
+    // hits of a lane as bits, one of every lane at a time
+    auto queue_bits = [&](uint32_t m, uint32_t p0, uint32_t p1, uint32_t pos) {
+        for (;;) {
+            const unsigned long long mk = __ballot(m != 0);
+            if (mk == 0) return;
+            const uint32_t at = qn;
+            qn += (uint32_t)__popcll(mk);
+            if (__builtin_amdgcn_inverse_ballot_w64(mk)) {
+                const uint32_t i = min(mbcnt_from(mk, at), q_end), j = (uint32_t)__builtin_ctz(m);
+                *(lds_out32_t *)(uintptr_t)(q_at + 4 * i) = __builtin_amdgcn_alignbit(p1, p0, 2 * j);
+                *(lds_out16_t *)(uintptr_t)(qp_at + 2 * i) = (uint16_t)(pos + j);
+                m &= m - 1;
+            }
+        }
+    };
     // the TL tests of a lane's 16 positions from unit position pos on
     auto tests = [&](const Slot &s, uint32_t pos) {
         const uint32_t w[5] = {s.v.x, s.v.y, s.v.z, s.v.w, s.h};
@@ -654,10 +677,20 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         for (uint32_t j = 0; j < TL; j++) {
             const uint32_t b = j * S;
             if (SYM)
-                x[j] = (b == 0 ? p0 : __builtin_amdgcn_alignbit(p1, p0, 2 * b)) & sym_mask;
+                x[j] = (b == 0 ? p0 : __builtin_amdgcn_alignbit(p1, p0, 2 * b)) & (SYM == 2 ? ~0u : sym_mask);
             else
                 x[j] = (b & 3) == 0 ? w[b >> 2] : __builtin_amdgcn_alignbyte(w[(b >> 2) + 1], w[b >> 2], b & 3);
             ent[j] = lookup(x[j], h[j]);
+        }
+        if (SYM == 2) {
+            uint32_t m = 0;  // the tests that hit, in the upper half
+#pragma unroll
+            for (uint32_t j = 0; j < TL; j++) m = __builtin_amdgcn_alignbit(ent[j] >> (x[j] & 31u), m, 1);
+            // those of the next lane behind them (after lane 63 taken as hits)
+            m = __builtin_amdgcn_alignbit((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)m, 0x130, 0xf, 0xf, false) >> 16, m, 16);
+            m &= m >> 1;
+            queue_bits(m & (m >> 2) & 0xffffu, p0, p1, pos);
+            return;
         }
 #pragma unroll
         for (uint32_t j = 0; j < TL; j++) queue(test(ent[j], h[j], x[j]), x[j], pos + j * S);
@@ -862,16 +895,19 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
 
 // ------------------------------------------------------------------ launchers
 
-template <bool LT, bool SYM>
-static const void *gram_fn_s(uint32_t s) {
-    return s == 4 ? (const void *)scan_grams<4, LT, SYM>
-         : s == 2 ? (const void *)scan_grams<2, LT, SYM> : (const void *)scan_grams<1, LT, SYM>;
+template <bool LT>
+static const void *gram_fn(uint32_t s, uint32_t sym) {
+    if (sym == 2) return (const void *)scan_grams<1, LT, 2>;
+    if (sym == 1)
+        return s == 4 ? (const void *)scan_grams<4, LT, 1>
+             : s == 2 ? (const void *)scan_grams<2, LT, 1> : (const void *)scan_grams<1, LT, 1>;
+    return s == 4 ? (const void *)scan_grams<4, LT, 0>
+         : s == 2 ? (const void *)scan_grams<2, LT, 0> : (const void *)scan_grams<1, LT, 0>;
 }
 
-static const void *gram_fn(uint32_t s, bool lds_table, bool sym) {
-    if (sym) return lds_table ? gram_fn_s<true, true>(s) : gram_fn_s<false, true>(s);
-    return lds_table ? gram_fn_s<true, false>(s) : gram_fn_s<false, false>(s);
-}
+static uint32_t gram_sym(const ImageView &im) { return !im.gram_q ? 0u : im.gram_run ? 2u : 1u; }
+
+int gram_fn_id(const ImageView &im) { return (int)(im.gram_s + 8 * gram_sym(im)); }
 
 void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table, uint32_t lds_limit) {
     a.off_wave = lds_table ? 4u << a.im.gram_lw : 0u;
@@ -893,7 +929,7 @@ void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table, uint32_t lds_l
 
 hipError_t prepare_gram_kernel(int fn_id, uint32_t lds_bytes) {
     // the bitmap is addressed at LDS address 0: no static LDS in front of it
-    const void *fn = gram_fn((uint32_t)fn_id & 7u, true, fn_id >= 8);
+    const void *fn = gram_fn<true>((uint32_t)fn_id & 7u, (uint32_t)fn_id >> 3);
     hipFuncAttributes attr;
     hipError_t e = hipFuncGetAttributes(&attr, fn);
     if (e != hipSuccess) return e;
@@ -904,8 +940,9 @@ hipError_t prepare_gram_kernel(int fn_id, uint32_t lds_bytes) {
 hipError_t launch_scan_grams(const ScanArgs &a, uint32_t waves, bool lds_table, uint32_t grid, hipStream_t s) {
     ScanArgs arg = a;
     void *args[] = {(void *)&arg};
-    const hipError_t e =
-        hipLaunchKernel(gram_fn(a.im.gram_s, lds_table, a.im.gram_q != 0), dim3(grid), dim3(64 * waves), args, a.lds_total, s);
+    const uint32_t sym = gram_sym(a.im);
+    const void *fn = lds_table ? gram_fn<true>(a.im.gram_s, sym) : gram_fn<false>(a.im.gram_s, sym);
+    const hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(64 * waves), args, a.lds_total, s);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }

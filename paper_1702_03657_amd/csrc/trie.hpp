@@ -146,7 +146,10 @@ struct DeviceImageHost {
     // middle bits of the products name the word: the top ones hardly see the
     // low byte of each half, which text needs):
     //  - gram: 2^gram_lw words; word (h >> kGramShift) mod 2^gram_lw has bits
-    //    h & 31 and x & 31 set;
+    //    h & 31 and x & 31 set.  With gram_run (gram_s 1, gram_q 16, patterns
+    //    of 19 symbols or more) the grams at offsets 0 .. 3 have one bit each,
+    //    x & 31 of word (h >> 2) mod 2^gram_lw, and a position counts when the
+    //    three after it hit too;
     //  - gfp: 2^gfp_lb buckets of 32 bytes: 14 16-bit slots and the number of
     //    the bucket's first record.  For g = x * kPfx4Mul, bucket g >> (32 -
     //    gfp_lb) has one slot i with the 12 bits of g below those in its upper
@@ -161,7 +164,7 @@ struct DeviceImageHost {
     //  - gpat: every pattern's bytes, each from a multiple of four on.
     uint32_t gram_s = 0;               // S: 4, 2 or 1 (0 = no gram filter)
     uint32_t gram_lw = 0, gfp_lb = 0;
-    uint32_t gram_q = 0, gram_sh = 0;  // gram_q 0: grams of four bytes
+    uint32_t gram_q = 0, gram_sh = 0, gram_run = 0;  // gram_q 0: grams of four bytes
     std::vector<uint32_t> gram;
     std::vector<uint16_t> gfp;
     std::vector<uint32_t> grec;

@@ -587,12 +587,14 @@ static void build_dag(const CrsTrie &T, DeviceImageHost &I) {
 }
 
 // Gram filter.  A larger S tests fewer positions but puts S grams per pattern
-// into a bitmap that LDS bounds at 2^20 bits; S is the one with the least cost
-// per text byte, of a test 1, of a false positive (16-bit slots read from L2) 9
-// and of a gram of a pattern (its record and a compare or walk) 130.  (1 GiB
-// with 100,000 patterns of 20 symbols: every second position, 11% false
-// positives, 572 us; every fourth, 29%, 657; 32 MiB with 500 of 9: every
-// position 30, every second, where 1.5% of all grams are a pattern's, 40.)
+// into a bitmap that LDS bounds at 2^20 bits.  S, and whether runs of four are
+// wanted, is the choice with the least cost: in units of 210 us per GiB a
+// position tested costs 1.2 / S (0.75 in a run: one bit, no branch per test), a
+// false positive (its slots read from L2) 40 and a gram of a pattern (its record
+// and a compare or walk) 600.  (1 GiB, 100,000 patterns of 20 symbols: runs 329
+// us, every second position with 11% false positives 571, every fourth with 29%
+// 657; 32 MiB, 500 of 9: every position 30, every second, where 1.5% of all
+// grams are a pattern's, 40.)
 static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
     if (!T.k || T.min_len < 4) return;
     auto level = [&](uint32_t d) { return T.level_start[d + 1] - T.level_start[d]; };
@@ -613,29 +615,39 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
     auto q_of = [&](uint32_t S) { return sym ? (uint32_t)std::min<uint64_t>(16, T.min_len - S + 1) : 4u; };
     uint32_t S = 0;
     uint64_t n = 0;
-    double best = 0;
-    for (uint32_t s = 1; s <= 4 && s + 3 <= T.min_len; s *= 2) {
-        uint64_t m = 0;  // at most so many distinct grams
-        for (uint32_t o = 0; o < s; o++) m += level(o + q_of(s));
-        double f = 1.0 - std::exp(-(double)m / (1u << 19));  // bits set of a full bitmap
+    bool run = false;
+    double best = 0, fp = 0;
+    auto consider = [&](uint32_t s, uint32_t span, double test) {
+        uint64_t m = 0, all = 0;  // at most so many distinct grams with records, in the bitmap
+        for (uint32_t o = 0; o < span; o++) {
+            all += level(o + q_of(s));
+            if (o < s) m = all;
+        }
+        // bits set of a full bitmap: two a gram, one in a run of four
+        const double f = 1.0 - std::exp((span > s ? -0.5 : -1.0) * (double)all / (1u << 19));
+        const double pass = span > s ? f * f * f * f : f * f;
         const double density = (double)m / std::pow((double)I.alphabet, (double)q_of(s));
-        const double c = (1.0 + 9.0 * f * f + 130.0 * density) / s;
-        if (m > (1u << 19) || (S && (c >= best || (sym && 1024 / s * f * f > 60)))) continue;
+        const double c = (test + 40.0 * pass + 600.0 * density) / s;
+        if (m > (1u << 19) || (S && c >= best)) return;
         S = s;
         n = m;
+        run = span > s;
         best = c;
-    }
+        fp = pass;
+    };
+    for (uint32_t s = 1; s <= 4 && s + 3 <= T.min_len; s *= 2) consider(s, s, 1.2);
+    if (sym && T.min_len >= 19) consider(1, 4, 0.75);
     if (!S || I.pout_ids.size() >= kGramId) return;
     const uint32_t Q = q_of(S);
-    // where more than 60 false positives a KiB are left the 16-symbol filter is
-    // faster while it holds its keys (96 MiB, 200,000 patterns of 20 to 32
-    // symbols: 171 us, this 312; 500,000: 5,440, this 607)
-    const double fill = 1.0 - std::exp(-(double)n / (1u << 19));
-    if (sym && I.q16_lw && n <= (1u << 18) && 1024 / S * fill * fill > 60) return;
+    // where more than 60 false positives a KiB are left (a wave checks 64 a
+    // chunk) the 16-symbol filter is faster while it has fingerprints (96 MiB,
+    // patterns of 20 to 32 symbols: 150,000 take 161 us there and 66 here,
+    // 300,000 269 and 515, 500,000, without fingerprints, 5,440 and 607)
+    if (sym && I.qfp_lb && 1024 / S * fp > 60) return;
     // small alphabets: past a quarter of all grams the filter keeps too much
     if (4.0 * (double)n > std::pow((double)I.alphabet, (double)Q)) return;
     uint32_t lg = 12;  // bits of the bitmap: 24 a gram, at most 2^20
-    while (lg < 20 && (1ull << lg) < 24 * n) lg++;
+    while (lg < 20 && (1ull << lg) < (run ? 48 : 24) * n) lg++;
     // without slots of its grams there is no filter
     auto drop = [&]() {
         I.gram_s = 0;
@@ -645,6 +657,7 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
         I.gpat.clear();
     };
     I.gram_q = sym ? Q : 0;
+    I.gram_run = run;
     I.gram_s = S;
     I.gram_lw = lg - 5;
     I.gram.assign(1u << I.gram_lw, 0);
@@ -653,7 +666,7 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
     };
     std::vector<Gram> grams;
     grams.reserve(n);
-    for (uint32_t o = 0; o < S; o++)
+    for (uint32_t o = 0; o < (run ? 4 : S); o++)
         for (uint32_t v = T.level_start[o + Q]; v < T.level_start[o + Q + 1]; v++) {
             const uint8_t *p = T.pat_data.data() + T.pat_off[T.rep[v]] + o;
             uint32_t x = 0;
@@ -662,8 +675,9 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
             else
                 std::memcpy(&x, p, 4);
             const uint32_t h = (x & 0xffffu) * kGramC0 + (x >> 16) * kGramC1;
-            I.gram[(h >> kGramShift) & ((1u << I.gram_lw) - 1u)] |= (1u << (h & 31)) | (1u << (x & 31));
-            grams.push_back(Gram{x, v, o});
+            const uint32_t w = (h >> (run ? 2 : kGramShift)) & ((1u << I.gram_lw) - 1u);
+            I.gram[w] |= (run ? 0u : 1u << (h & 31)) | (1u << (x & 31));
+            if (o < S) grams.push_back(Gram{x, v, o});
         }
     // buckets of 14 slots: about three grams each, more buckets while one
     // overflows.  The grams in the order of their buckets:

@@ -146,15 +146,16 @@ def test_nested_words(lo, dup, n):
 
 
 # four symbols: grams of up to 16 of them.  Short patterns (grams of 4 to 13
-# symbols, every position, every second or every fourth), long ones (16), sets
-# that fill the bitmap; alphabets of two and three symbols, bytes that share the
+# symbols, every position, every second or every fourth), long ones (16, and from
+# 19 on runs of four in large sets), sets that fill the bitmap; alphabets of two and three symbols, bytes that share the
 # symbols' bits (upper case, N) in runs and alone, both ends of the text, starts
 # around the edges of units, runs of one symbol
 @pytest.mark.parametrize("alphabet", [b"acgt", b"ACT", b"01"])
 @pytest.mark.parametrize("lo,k,n,pad", [
     (9, 500, 70, 3), (9, 60, 1023, 1), (9, 500, 1025, 15), (10, 300, 300_001, 11), (12, 500, 2560 * 1024, 7),
     (20, 1000, 2560 * 1024 + 1, 0), (6, 20, 3 * MiB, 5), (9, 500, 8 * MiB + 1, 2), (13, 400, 9 * MiB, 13),
-    (20, 40_000, 9 * MiB + 1023, 9), (24, 100_000, 20 * MiB + 5, 1),
+    (19, 40_000, 5 * MiB + 3, 4), (18, 40_000, 5 * MiB, 8), (20, 40_000, 9 * MiB + 1023, 9),
+    (24, 100_000, 20 * MiB + 5, 1),
 ])
 def test_symbols(lo, k, n, pad, alphabet):
     rng = np.random.default_rng(lo + k + len(alphabet))
@@ -190,7 +191,7 @@ def test_symbols(lo, k, n, pad, alphabet):
     assert np.array_equal(counts, oracle.counts(n, want))
 
 
-@pytest.mark.parametrize("lo,k,most", [(9, 300, 60), (12, 500, 2000), (20, 5000, 40_000)])
+@pytest.mark.parametrize("lo,k,most", [(9, 300, 60), (12, 500, 2000), (20, 5000, 40_000), (20, 60_000, 900)])
 def test_symbols_batch(lo, k, most):
     rng = np.random.default_rng(lo)
     a = np.frombuffer(b"acgt", dtype=np.uint8)
