@@ -117,6 +117,7 @@ struct pfac_workspace {
     // A launch failed after the scan's kernels were (partly) queued: the
     // staging cursor, which every finisher leaves at zero, may not be.
     bool cursor_stale = false;
+    uint64_t *host_count = nullptr;  // count of synchronous scans, in pinned memory
     // misc: [0] stage cursor, [1] running total, [2] per-launch count
     unsigned long long *cursor() { return (unsigned long long *)misc.p; }
     unsigned long long *running() { return (unsigned long long *)misc.p + 1; }
@@ -696,6 +697,7 @@ extern "C" int pfac_workspace_create(pfac_workspace **out) {
 
 extern "C" void pfac_workspace_free(pfac_workspace *w) {
     if (!w) return;
+    if (w->host_count) (void)hipHostFree(w->host_count);
     w->stage.release();
     w->unit_count.release();
     w->unit_off.release();
@@ -1145,11 +1147,13 @@ extern "C" int pfac_scan_sync(const pfac_trie *t, pfac_workspace *w, const uint8
                               uint64_t n, pfac_match *out_dev, uint64_t capacity,
                               uint64_t *n_matches_host, uint32_t *counts_dev, void *stream) {
     if (!n_matches_host || !w) return PFAC_EINVAL;
-    uint64_t *dcount = w->tmp_count();
-    int rc = pfac_scan(t, w, text_dev, n, out_dev, capacity, dcount, counts_dev, stream);
+    // The finisher writes the count to pinned host memory: a copy of eight bytes
+    // behind it took 8 of 28 us for a packet.
+    if (!w->host_count) HIP_TRY(hipHostMalloc((void **)&w->host_count, 64, hipHostMallocPortable));
+    int rc = pfac_scan(t, w, text_dev, n, out_dev, capacity, w->host_count, counts_dev, stream);
     if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(n_matches_host, dcount, 8, hipMemcpyDeviceToHost, (hipStream_t)stream));
     HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
+    *n_matches_host = *(const volatile uint64_t *)w->host_count;
     return *n_matches_host > capacity ? PFAC_ETRUNC : PFAC_OK;
 }
 
