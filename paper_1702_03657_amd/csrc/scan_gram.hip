@@ -21,7 +21,7 @@
 // 29% of every fourth.  1 GiB, 100,000 patterns of 20 to 32: 329 us, VALU busy
 // for 278 of it (a hash per position and a second stage of walks 830, every
 // second position 571, pairs of two-bit hits 343); 32 MiB, 500 patterns of 9 to
-// 14, where the generic filter kept every 25th position: 30 us (90).
+// 14, where the generic filter kept every 25th position: 26 us (90).
 //
 //   * a workgroup loads the bitmap (two hashed bits per gram, at most 128 KiB)
 //     into LDS; each wave owns units of G consecutive 1 KiB chunks of test
@@ -644,7 +644,11 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     uint32_t sym_mask = SYM ? 0xffffffffu >> (32 - 2 * im.gram_q) : 0u;
     if (SYM) asm volatile("" : "+v"(sym_bits), "+v"(sym_mask));
     auto pack4 = [&](uint32_t w) -> uint32_t { return __builtin_amdgcn_udot4(w & sym_bits, 0x40100401u, 0u, false); };
-    // hits of a lane as bits, one of every lane at a time
+    // Queue a lane's grams that hit (bit j of m: at unit position pos + j * S),
+    // one of every lane at a time: symbols, whose grams are one shift away.  (32
+    // MiB against 500 motifs: 26 us, 30 with a ballot per test.  Bytes, whose
+    // gram is chosen among five registers: 64 MiB and packets 718, 515 with a
+    // ballot per test.)
     auto queue_bits = [&](uint32_t m, uint32_t p0, uint32_t p1, uint32_t pos) {
         for (;;) {
             const unsigned long long mk = __ballot(m != 0);
@@ -652,9 +656,10 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
             const uint32_t at = qn;
             qn += (uint32_t)__popcll(mk);
             if (__builtin_amdgcn_inverse_ballot_w64(mk)) {
-                const uint32_t i = min(mbcnt_from(mk, at), q_end), j = (uint32_t)__builtin_ctz(m);
-                *(lds_out32_t *)(uintptr_t)(q_at + 4 * i) = __builtin_amdgcn_alignbit(p1, p0, 2 * j);
-                *(lds_out16_t *)(uintptr_t)(qp_at + 2 * i) = (uint16_t)(pos + j);
+                const uint32_t i = min(mbcnt_from(mk, at), q_end), b = S * (uint32_t)__builtin_ctz(m);
+                *(lds_out32_t *)(uintptr_t)(q_at + 4 * i) =
+                    __builtin_amdgcn_alignbit(p1, p0, 2 * b) & (SYM == 2 ? ~0u : sym_mask);
+                *(lds_out16_t *)(uintptr_t)(qp_at + 2 * i) = (uint16_t)(pos + b);
                 m &= m - 1;
             }
         }
@@ -682,14 +687,20 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                 x[j] = (b & 3) == 0 ? w[b >> 2] : __builtin_amdgcn_alignbyte(w[(b >> 2) + 1], w[b >> 2], b & 3);
             ent[j] = lookup(x[j], h[j]);
         }
-        if (SYM == 2) {
-            uint32_t m = 0;  // the tests that hit, in the upper half
+        if (SYM) {
+            uint32_t m = 0;  // the tests that hit, shifted in from the upper end
 #pragma unroll
-            for (uint32_t j = 0; j < TL; j++) m = __builtin_amdgcn_alignbit(ent[j] >> (x[j] & 31u), m, 1);
-            // those of the next lane behind them (after lane 63 taken as hits)
-            m = __builtin_amdgcn_alignbit((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)m, 0x130, 0xf, 0xf, false) >> 16, m, 16);
-            m &= m >> 1;
-            queue_bits(m & (m >> 2) & 0xffffu, p0, p1, pos);
+            for (uint32_t j = 0; j < TL; j++)
+                m = __builtin_amdgcn_alignbit((SYM == 2 ? ~0u : ent[j] >> (h[j] & 31u)) & (ent[j] >> (x[j] & 31u)), m, 1);
+            if (SYM == 2) {
+                // those of the next lane behind them (after lane 63 taken as hits)
+                m = __builtin_amdgcn_alignbit((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)m, 0x130, 0xf, 0xf, false) >> 16, m, 16);
+                m &= m >> 1;
+                m &= (m >> 2) & 0xffffu;
+            } else {
+                m >>= 32 - TL;
+            }
+            queue_bits(m, p0, p1, pos);
             return;
         }
 #pragma unroll

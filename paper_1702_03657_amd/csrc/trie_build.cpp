@@ -593,7 +593,7 @@ static void build_dag(const CrsTrie &T, DeviceImageHost &I) {
 // false positive (its slots read from L2) 40 and a gram of a pattern (its record
 // and a compare or walk) 600.  (1 GiB, 100,000 patterns of 20 symbols: runs 329
 // us, every second position with 11% false positives 571, every fourth with 29%
-// 657; 32 MiB, 500 of 9: every position 30, every second, where 1.5% of all
+// 657; 32 MiB, 500 of 9: every position 26, every second, where 1.5% of all
 // grams are a pattern's, 40.)
 static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
     if (!T.k || T.min_len < 4) return;
