@@ -124,7 +124,8 @@ TIMING_EVENTS = None
 CSRC = os.path.join(ROOT, "paper_1702_03657_amd", "csrc")
 # sources each scan kernel is compiled from (the traffic counts are tied to them)
 KERNEL_SOURCES = {
-    "scan_waves": ("scan_wave.hip", "kernels.hpp", "device_common.hpp"),
+    "scan_grams": ("scan_gram.hip", "wave_common.hpp", "kernels.hpp", "device_common.hpp"),
+    "scan_waves": ("scan_wave.hip", "wave_common.hpp", "kernels.hpp", "device_common.hpp"),
     "scan_tiles": ("kernels.hip", "kernels.hpp", "device_common.hpp"),
 }
 
@@ -750,25 +751,28 @@ def valu_issue(counts, n_cu, kernel_ms):
             "issue_bound_ms": round(issue_ms, 5), "frac": round(issue_ms / kernel_ms, 4)}
 
 
-def kernel_of(stats):
+def kernel_of(stats, tuning):
     """(name, split) of the main scan kernel of a launch; `stats` carries
-    "launch_kernel", the kernel a launch of the measured size runs."""
+    "launch_kernel", the kernel a launch of the measured size runs where the
+    gram kernel does not: that takes the launches whose kernel the library
+    chooses (kernel 3) for patterns of four bytes or more."""
+    if tuning["kernel"] == 3 and int(stats["min_len"]) >= 4 and not (tuning["trunc_depth"] or tuning["dag"]):
+        return "scan_grams", False
     k = int(stats["launch_kernel"])
     return ("scan_waves" if k in (1, 2) else "scan_tiles"), k == 2
 
 
-def alg_bytes_of(stats, text_bytes, n_matches):
+def alg_bytes_of(stats, tuning, text_bytes, n_matches):
     """Algorithmic bytes of one launch of the main scan kernel: every text
-    byte read once and the CRS trie read once; the tile and fused wave
-    kernels also write the 16-byte match records (on the split path the walk
-    kernel writes them)."""
-    _, split = kernel_of(stats)
+    byte read once and the CRS trie read once; all but the filter kernel of
+    the split path also write the 16-byte match records."""
+    _, split = kernel_of(stats, tuning)
     return text_bytes + int(stats["bytes_crs"]) + (0 if split else 16 * n_matches)
 
 
 def roofline_entry(stats, workload, tuning, text_bytes, n_matches, kernel_ms, step_ms, probe, n_cu):
-    kernel_name, split = kernel_of(stats)
-    alg = alg_bytes_of(stats, text_bytes, n_matches)
+    kernel_name, split = kernel_of(stats, tuning)
+    alg = alg_bytes_of(stats, tuning, text_bytes, n_matches)
     achieved = alg / (kernel_ms / 1e3) / 1e9
     step_bytes = text_bytes + int(stats["bytes_crs"]) + 16 * n_matches
     counts = profile_counts(kernel_name, workload, tuning)

@@ -120,12 +120,16 @@ typedef struct {
                                   kernels (filter kernel writes walk candidates, a walk kernel
                                   runs them; for alphabets of at most four bytes it uses the
                                   16-symbol filter when every pattern has 16 bytes or more),
-                                  3 = by launch size: 2 with units of up to 64 chunks
-                                  for launches (a text, or a whole batch) of 8 MiB or more,
-                                  else 0 with 4 bytes per lane below 1 MiB and 8 from
-                                  there (the default for byte
-                                  alphabets with K = 2 and for alphabets of at most four
-                                  bytes).  Statistics report the kernel of large launches */
+                                  3 = by the library (the default for byte alphabets with
+                                  K = 2 and for alphabets of at most four bytes): the gram
+                                  kernel where the trie has a gram filter (patterns of four
+                                  bytes or more, the whole trie on the device, and a filter
+                                  that keeps few positions), else by launch size 2 with
+                                  units of up to 64 chunks for launches (a text, or a whole
+                                  batch) of 8 MiB or more, else 0 with 4 bytes per lane
+                                  below 1 MiB and 8 from there.  A trie whose tuning is as
+                                  it was built takes the gram kernel likewise.  Statistics
+                                  report the kernel of large launches without it */
     uint32_t bytes_per_lane;   /* tile kernel: start positions per lane per tile: 4, 8 or 16 */
     uint32_t index_bits;       /* level-index width in bits (1..18); depth K = bits / symbol_bits */
     uint32_t fold_bits;        /* wave kernel prefix filter: 0 (level bitmap), 8 or 16 bits per node */
@@ -228,7 +232,8 @@ int pfac_trie_set_tuning(pfac_trie *t, const pfac_tuning *tuning);
 /* The kernels a launch over `total_bytes` bytes (one text, or a whole
  * batch) runs with the current tuning, with kernel 3 resolved by that size:
  * *kernel = 0 (tile kernel), 1 (fused wave kernel) or 2 (split filter +
- * walk kernels); *tuning (may be NULL) = the tuning that launch uses.
+ * walk kernels); *tuning (may be NULL) = the tuning that launch uses.  A
+ * launch that takes the gram kernel is reported as what it would run without.
  * Host only.  Errors: PFAC_EINVAL (NULL trie or kernel). */
 int pfac_trie_launch_kernel(const pfac_trie *t, uint64_t total_bytes, uint32_t *kernel,
                             pfac_tuning *tuning);
@@ -252,8 +257,8 @@ int pfac_workspace_reserve(pfac_workspace *w, uint64_t max_bytes, uint32_t max_t
 /*
  * Instrumentation: when both events are set (hipEvent_t, NULL to clear),
  * every later scan on this workspace records `start_event` on its stream
- * right before the main scan kernel (the tile kernel, the fused wave kernel,
- * or the filter kernel of the split pair) and `stop_event` right after it,
+ * right before the main scan kernel (the gram kernel, the tile kernel, the
+ * fused wave kernel, or the filter kernel of the split pair) and `stop_event` right after it,
  * so the caller can time that kernel alone.  The events are only recorded,
  * never created or destroyed, by the library.
  */
@@ -283,7 +288,8 @@ int pfac_scan(const pfac_trie *t, pfac_workspace *w, const uint8_t *text_dev, ui
  * from its load until the process ends, so no call allocates or frees
  * anything.  The scratch a scan needs grows with n and capacity: about
  * 700 bytes per KiB of text plus 16 bytes per unit of capacity (a 32 MiB
- * text with capacity 2^20 fits); a call whose needs exceed 64 MiB returns
+ * text with capacity 2^20 fits; a call whose needs fit only without the gram
+ * kernel's list area runs without that kernel); a call whose needs exceed 64 MiB returns
  * PFAC_EINVAL before touching the device.  Every call on a device uses the
  * same array: calls that may overlap on one device (different streams or
  * threads) race and must be ordered by the caller; a call on one stream
