@@ -50,8 +50,10 @@ namespace pfac {
 // A wave's lists in LDS: queued grams (6 bytes each), grams whose starts are
 // to be looked at (6) and matches of the unit (8).  The short ones fit 16 waves
 // beside a bitmap of 128 KiB; texts that hit often (words: 50 grams a KiB)
-// want the long ones, so that a group never overflows the queue.
-constexpr uint32_t kGqShort = 160, kGcShort = 88, kGmShort = 64;
+// want the long ones, so that a group never overflows the queue.  Either way a
+// wave's area is a multiple of 16 bytes: emit_spilled reads 16 at a time from
+// its start.
+constexpr uint32_t kGqShort = 160, kGcShort = 84, kGmShort = 64;
 constexpr uint32_t kGqLong = 444, kGcLong = 192, kGmLong = 160;
 constexpr uint32_t kGqPad = 4;    // entries past the queue's end, the first written by grams that find it full
 constexpr uint32_t kGqRoom = 57;  // the queue is emptied when a group leaves less room
@@ -932,7 +934,9 @@ void gram_lds_layout(ScanArgs &a, uint32_t waves, bool lds_table, uint32_t lds_l
     // the queue's and the starts' place is also where a unit's matches are
     // sorted (at most gm entries, or 256 + 64 words)
     static_assert(4 * (256 + 64) <= 6 * (kGqShort + kGqPad + kGcShort) && 8 * kGmLong <= 6 * (kGqLong + kGqPad + kGcLong), "sort area");
-    static_assert((kGqShort + kGqPad + kGcShort) % 4 == 0 && (kGqLong + kGqPad + kGcLong) % 4 == 0, "matches at multiples of 8");
+    static_assert(6 * (kGqShort + kGqPad + kGcShort) % 16 == 0 && 8 * kGmShort % 16 == 0 &&
+                      6 * (kGqLong + kGqPad + kGcLong) % 16 == 0 && 8 * kGmLong % 16 == 0,
+                  "lists and matches at multiples of 16");
     static_assert(kGqShort >= 64 + kGqRoom - 1 && kGcShort >= 64 && kGmShort >= 64, "a round fits");
     lists(kGqLong, kGcLong, kGmLong);
     if (!lds_table || a.lds_total > lds_limit) lists(kGqShort, kGcShort, kGmShort);
