@@ -114,8 +114,9 @@ struct pfac_workspace {
     // launch shape of the last main scan kernel (grid, block, dynamic LDS):
     // graphs find its node by it
     uint32_t main_grid = 0, main_block = 0, main_lds = 0;
-    // A launch failed after the scan's kernels were (partly) queued: the
-    // staging cursor, which every finisher leaves at zero, may not be.
+    // The staging cursor, which every finisher leaves at zero, may not be: no
+    // scan has run yet, or a launch failed after the scan's kernels were
+    // (partly) queued.  The next scan clears it on its own stream.
     bool cursor_stale = false;
     uint64_t *host_count = nullptr;  // count of synchronous scans, in pinned memory
     // misc: [0] stage cursor, [1] running total, [2] per-launch count
@@ -685,12 +686,12 @@ extern "C" int pfac_workspace_create(pfac_workspace **out) {
     pfac_workspace *w = new (std::nothrow) pfac_workspace();
     if (!w) return PFAC_ENOMEM;
     hipError_t e = w->misc.reserve(256);
-    if (e == hipSuccess) e = hipMemset(w->misc.p, 0, 256);
     if (e != hipSuccess) {
         delete w;
         *out = nullptr;
         return hip_fail(e);
     }
+    w->cursor_stale = true;
     *out = w;
     return PFAC_OK;
 }
@@ -960,6 +961,11 @@ static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
 
     a.n_sums = n_sums;
     if (n_tiles <= kCountUnits) a.blocksum = nullptr;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (w->cursor_stale && hipStreamIsCapturing(L.s, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        capture = hipStreamCaptureStatusActive;
+    }
     // (the split filter kernel clears the block sums and the cursor itself)
     if ((a.blocksum || w->cursor_stale) && !(split && n_tiles))
         HIP_TRY(launch_reset(a.stage_cursor, a.blocksum, a.blocksum ? n_sums : 0, L.s));
@@ -1033,7 +1039,7 @@ static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
     f.spill_cap = a.spill_cap;
     f.cursor = a.stage_cursor;
     HIP_TRY(launch_finish(f, L.s));
-    w->cursor_stale = false;
+    w->cursor_stale = capture != hipStreamCaptureStatusNone;  // captured: nothing ran
     return PFAC_OK;
 }
 
@@ -1317,6 +1323,15 @@ extern "C" int pfac_graph_create_batch(const pfac_trie *t, pfac_workspace *w,
         pfac_graph_free(g);
         return hip_fail_at(ec, "hipStreamCreateWithFlags", __LINE__);
     }
+    // the scratch is the graph's alone: its cursor is cleared here, once, so
+    // that no replay does
+    ec = launch_reset(g->ws->cursor(), nullptr, 0, s);
+    if (ec == hipSuccess) ec = hipStreamSynchronize(s);
+    if (ec != hipSuccess) {
+        (void)hipStreamDestroy(s);
+        pfac_graph_free(g);
+        return hip_fail_at(ec, "hipStreamSynchronize", __LINE__);
+    }
     // With the caller's timing events set, event-record nodes around the
     // main kernel record two events of the graph's own (plain hipEventCreate
     // events), pointed at the caller's events once the graph is
@@ -1327,7 +1342,7 @@ extern "C" int pfac_graph_create_batch(const pfac_trie *t, pfac_workspace *w,
     const bool timed = w && w->ev_start && w->ev_stop;
     for (int method = timed ? 0 : 2; method <= 2; method++) {
         g->ws->ev_start = g->ws->ev_stop = nullptr;
-        g->ws->cursor_stale = false;  // (a failed attempt ran nothing)
+        g->ws->cursor_stale = false;  // (nor does a failed attempt run anything)
         g->n_start = g->n_stop = nullptr;
         rc = PFAC_OK;
         if (method < 2) {

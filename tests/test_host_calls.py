@@ -74,7 +74,73 @@ def lists_aligned():
             assert (lds - 16 - table) % (16 * waves) == 0, (k, n, lds, waves)
 
 
-TESTS = [lists_aligned]
+def _kernels(lines=None):
+    return [name for name, *_ in _launches(lines)]
+
+
+def cursor_cleared():
+    """The staging cursor of a new workspace is cleared by its first scan, on
+    the scan's own stream (streams need not wait for the one that a clearing at
+    creation would take), a captured scan leaves that to the next one too, and
+    later scans have nothing to clear unless a launch failed."""
+    trie = pf.Trie(_bytes_set(500))
+    stream = 0x770
+
+    def scan(ws):
+        pf.pfac_scan(trie, ws, TEXT, 5000, OUT, 100, COUNT, stream=stream)
+
+    ws = pf.Workspace()
+    assert not [ln for ln in _lines() if ln.startswith("memset")]
+    scan(ws)
+    lines = _lines()
+    assert _kernels(lines) == ["reset_kernel", "scan_grams", "finish_tiles"]
+    assert all(f"stream {stream} " in ln for ln in lines if ln.startswith("launch"))
+    scan(ws)
+    assert _kernels() == ["scan_grams", "finish_tiles"]
+
+    ws = pf.Workspace()
+    ws.reserve(5000, 1, 100)
+    _lines()
+    hip.host_hip_capture(1)
+    scan(ws)
+    hip.host_hip_capture(0)
+    assert _kernels() == ["reset_kernel", "scan_grams", "finish_tiles"]
+    scan(ws)
+    assert _kernels() == ["reset_kernel", "scan_grams", "finish_tiles"]
+    scan(ws)
+    assert _kernels() == ["scan_grams", "finish_tiles"]
+
+    def noalloc():
+        pf.pfac_scan_noalloc(trie, TEXT, 5000, OUT, 100, COUNT, stream=stream)
+
+    for call in (lambda: scan(ws), noalloc):
+        call()
+        hip.host_hip_refuse(b"finish_tiles")
+        with pytest.raises(pf.PfacError) as e:
+            call()
+        assert e.value.code == pf.PFAC_EDEVICE
+        hip.host_hip_refuse(b"")
+        _lines()
+        call()
+        assert _kernels() == ["reset_kernel", "scan_grams", "finish_tiles"]
+        call()
+        assert _kernels() == ["scan_grams", "finish_tiles"]
+
+
+def graph_cursor_cleared():
+    """A graph's own workspace is cleared, and the clearing waited for, before
+    its scan is captured: replays have nothing to clear."""
+    trie = pf.Trie(_bytes_set(500))
+    _lines()
+    pf.Graph(trie, None, TEXT, OFFSETS, 10, 5000, OUT, 100, COUNT)
+    lines = [ln for ln in _lines() if ln.startswith(("launch", "capture", "sync", "memset"))]
+    at = lines.index("capture begins")
+    assert _kernels(lines[:at]) == ["reset_kernel"] and lines[at - 1].startswith("sync stream ")
+    assert lines[at - 1].split()[2] == re.search(r"stream (\d+)", lines[at - 2])[1]
+    assert _kernels(lines[at:]) == ["plan_kernel", "scan_grams", "finish_tiles"]
+
+
+TESTS = [lists_aligned, cursor_cleared, graph_cursor_cleared]
 
 
 @pytest.mark.parametrize("name", [t.__name__ for t in TESTS])
