@@ -681,19 +681,26 @@ extern "C" int pfac_trie_set_tuning(pfac_trie *t, const pfac_tuning *tn) {
 
 // ---------------------------------------------------------------- workspace
 
-extern "C" int pfac_workspace_create(pfac_workspace **out) {
-    if (!out) return PFAC_EINVAL;
+// sync: the workspace is for synchronous scans as well
+static int ws_create(pfac_workspace **out, bool sync) {
+    *out = nullptr;
     pfac_workspace *w = new (std::nothrow) pfac_workspace();
     if (!w) return PFAC_ENOMEM;
     hipError_t e = w->misc.reserve(256);
+    if (e == hipSuccess && sync) e = hipHostMalloc((void **)&w->host_count, 64, hipHostMallocPortable);
     if (e != hipSuccess) {
+        w->misc.release();
         delete w;
-        *out = nullptr;
         return hip_fail(e);
     }
     w->cursor_stale = true;
     *out = w;
     return PFAC_OK;
+}
+
+extern "C" int pfac_workspace_create(pfac_workspace **out) {
+    if (!out) return PFAC_EINVAL;
+    return ws_create(out, true);
 }
 
 extern "C" void pfac_workspace_free(pfac_workspace *w) {
@@ -1155,7 +1162,6 @@ extern "C" int pfac_scan_sync(const pfac_trie *t, pfac_workspace *w, const uint8
     if (!n_matches_host || !w) return PFAC_EINVAL;
     // The finisher writes the count to pinned host memory: a copy of eight bytes
     // behind it took 8 of 28 us for a packet.
-    if (!w->host_count) HIP_TRY(hipHostMalloc((void **)&w->host_count, 64, hipHostMallocPortable));
     int rc = pfac_scan(t, w, text_dev, n, out_dev, capacity, w->host_count, counts_dev, stream);
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
@@ -1299,7 +1305,7 @@ extern "C" int pfac_graph_create_batch(const pfac_trie *t, pfac_workspace *w,
     // lends the graph only its timing events
     pfac_graph *g = new (std::nothrow) pfac_graph();
     if (!g) return PFAC_ENOMEM;
-    int rc = pfac_workspace_create(&g->ws);
+    int rc = ws_create(&g->ws, false);
     if (rc == PFAC_OK)
         rc = check_scan_args(t, g->ws, texts_dev, total_bytes, out_dev, capacity, n_matches_dev);
     if (rc == PFAC_OK && !offsets_dev) rc = PFAC_EINVAL;

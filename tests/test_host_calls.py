@@ -140,7 +140,38 @@ def graph_cursor_cleared():
     assert _kernels(lines[at:]) == ["plan_kernel", "scan_grams", "finish_tiles"]
 
 
-TESTS = [lists_aligned, cursor_cleared, graph_cursor_cleared]
+def reserved_scans_allocate_nothing():
+    """After pfac_workspace_reserve no scan allocates, device memory or pinned
+    memory; a synchronous scan waits once and copies nothing.  A call that is
+    refused touches nothing either, and graphs (which have no synchronous scans)
+    take no pinned memory."""
+    for pats in (_bytes_set(500), [b"ab", b"abc", b"xyz"]):
+        trie = pf.Trie(pats)
+        ws = pf.Workspace()
+        ws.reserve(20 * MiB, 10, 1000)
+        _lines()
+        for n in (1460, 64 * KiB, 20 * MiB):
+            for _ in range(2):
+                pf.pfac_scan_sync(trie, ws, TEXT, n, OUT, 1000)
+                lines = _lines()
+                assert not [ln for ln in lines if "malloc" in ln or ln.startswith("copy")], (n, lines)
+                assert [ln for ln in lines if ln.startswith("sync")] == ["sync stream 0"]
+            pf.pfac_scan(trie, ws, TEXT, n, OUT, 1000, COUNT)
+            pf.pfac_scan_batch(trie, ws, TEXT, OFFSETS, 3, n, OUT, 1000, COUNT)
+            assert not [ln for ln in _lines() if "malloc" in ln]
+    host_only = pf.Trie(_bytes_set(500), host_only=True)
+    for t in (host_only, trie):
+        fresh = pf.Workspace()
+        _lines()
+        with pytest.raises(pf.PfacError) as e:
+            pf.pfac_scan_sync(t, fresh, None, 100, OUT, 1000)
+        assert e.value.code == (pf.PFAC_EINVAL if t is trie else pf.PFAC_ENODEV)
+        assert not _lines()
+    pf.Graph(trie, None, TEXT, OFFSETS, 10, 5000, OUT, 100, COUNT)
+    assert not [ln for ln in _lines() if ln.startswith("host malloc")]
+
+
+TESTS = [lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
 
 
 @pytest.mark.parametrize("name", [t.__name__ for t in TESTS])
