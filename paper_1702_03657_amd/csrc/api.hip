@@ -721,31 +721,33 @@ extern "C" void pfac_workspace_free(pfac_workspace *w) {
 
 // Scratch sizes of a scan over n_tiles units (or 1 KiB chunks of the wave
 // kernels, at least as many) with room for `capacity` staged matches; split:
-// also the candidate lists of the split wave kernels.
+// also the candidate lists of the split wave kernels; gram: only what the gram
+// kernel reads, block sums included where there may be more units than the
+// finisher counts.
 struct WsSizes {
     uint64_t unit_count, unit_off, tile_first, chunk_info, blocksum, stage, inline_stage, cand,
         cand_count;
 };
 
-static WsSizes ws_sizes(uint64_t n_tiles, uint64_t capacity, bool split) {
+static WsSizes ws_sizes(uint64_t n_tiles, uint64_t capacity, bool split, bool gram) {
     const uint64_t n_sums = std::max<uint64_t>(1, (n_tiles + (1u << kSumShift) - 1) >> kSumShift);
     WsSizes z{};
     z.unit_count = std::max<uint64_t>(n_tiles, 1) * 4;
     z.unit_off = std::max<uint64_t>(n_tiles, 1) * 8;
     z.tile_first = std::max<uint64_t>(n_tiles, 1) * 4;
-    z.chunk_info = std::max<uint64_t>(n_tiles, 1) * 8;
-    z.blocksum = n_sums * 8;
+    z.chunk_info = gram ? 0 : std::max<uint64_t>(n_tiles, 1) * 8;
+    z.blocksum = gram && n_tiles <= kCountUnits ? 0 : n_sums * 8;
     z.stage = std::max<uint64_t>(capacity, 1) * sizeof(pfac_match);
     // wave kernels: max(kInlineCap, kInlinePerChunk * G) slots per unit of G
     // chunks, at most kInlineCap per chunk
     z.inline_stage = (n_tiles + 64) * kInlineCap * sizeof(pfac_match);
-    z.cand = split ? (n_tiles + 64) * kCandPerChunk * 16 : 0;
+    z.cand = split || gram ? (n_tiles + 64) * kCandPerChunk * 16 : 0;
     z.cand_count = split ? std::max<uint64_t>(n_tiles, 1) * 4 : 0;
     return z;
 }
 
-static int ws_reserve(pfac_workspace *w, uint64_t n_tiles, uint64_t capacity, bool split) {
-    const WsSizes z = ws_sizes(n_tiles, capacity, split);
+static int ws_reserve(pfac_workspace *w, uint64_t n_tiles, uint64_t capacity, bool split, bool gram) {
+    const WsSizes z = ws_sizes(n_tiles, capacity, split, gram);
     HIP_TRY(w->unit_count.reserve(z.unit_count));
     HIP_TRY(w->unit_off.reserve(z.unit_off));
     HIP_TRY(w->tile_first.reserve(z.tile_first));
@@ -753,10 +755,8 @@ static int ws_reserve(pfac_workspace *w, uint64_t n_tiles, uint64_t capacity, bo
     HIP_TRY(w->blocksum.reserve(z.blocksum));
     HIP_TRY(w->stage.reserve(z.stage));
     HIP_TRY(w->inline_stage.reserve(z.inline_stage));
-    if (split) {
-        HIP_TRY(w->cand.reserve(z.cand));
-        HIP_TRY(w->cand_count.reserve(z.cand_count));
-    }
+    HIP_TRY(w->cand.reserve(z.cand));
+    HIP_TRY(w->cand_count.reserve(z.cand_count));
     return PFAC_OK;
 }
 
@@ -774,7 +774,7 @@ extern "C" int pfac_workspace_reserve(pfac_workspace *w, uint64_t max_bytes, uin
     // sizes whose byte counts would not even fit in 64 bits cannot be allocated
     if (max_bytes > (1ull << 56) || max_matches > (1ull << 56)) return PFAC_ENOMEM;
     uint64_t n_tiles = (max_bytes + 16 + kWG * 4 - 1) / (kWG * 4);  // smallest tile
-    return ws_reserve(w, n_tiles, max_matches, true);
+    return ws_reserve(w, n_tiles, max_matches, true, false);
 }
 
 // ---------------------------------------------------------------------- scan
@@ -828,9 +828,8 @@ static bool use_wave_kernel(const pfac_trie *t, const pfac_tuning &tn, uint32_t 
 
 static bool use_gram_kernel(const pfac_trie *t);
 
-// launches with candidate lists (the gram kernel's past-LDS matches lie there)
 static bool uses_split(const pfac_trie *t, const pfac_tuning &tn) {
-    return use_gram_kernel(t) || (tn.kernel == 2 && use_wave_kernel(t, tn, nullptr));
+    return tn.kernel == 2 && use_wave_kernel(t, tn, nullptr);
 }
 
 // How a scan of `total` bytes at `text` is cut with the trie's tuning:
@@ -917,7 +916,7 @@ static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
     const uint32_t plan_unit = h.plan_unit;
     const uint64_t n_plan = h.n_plan;
     if (reserve) {
-        int rc = ws_reserve(L.w, h.ws_units(), L.capacity, split || gram);
+        int rc = ws_reserve(L.w, h.ws_units(), L.capacity, split, gram);
         if (rc != PFAC_OK) return rc;
     }
     pfac_workspace *w = L.w;
@@ -1118,7 +1117,7 @@ extern "C" int pfac_scan_noalloc(const pfac_trie *t, const uint8_t *text_dev, ui
         w = pfac_workspace{};
         const ScanShape h = scan_shape(t, launch_tuning(t, n), text_dev, n, gram);
         if (h.ws_units() > (1ull << 40) || capacity > (1ull << 40)) return PFAC_EINVAL;
-        const WsSizes z = ws_sizes(h.ws_units(), capacity, h.split || h.gram);
+        const WsSizes z = ws_sizes(h.ws_units(), capacity, h.split, h.gram);
         uint64_t off = 0;
         auto take = [&](DeviceBuf &b, uint64_t bytes) {
             b.p = (void *)(uintptr_t)off;  // (offsets; the base is added below)
@@ -1133,10 +1132,8 @@ extern "C" int pfac_scan_noalloc(const pfac_trie *t, const uint8_t *text_dev, ui
         take(w.blocksum, z.blocksum);
         take(w.stage, z.stage);
         take(w.inline_stage, z.inline_stage);
-        if (h.split || h.gram) {
-            take(w.cand, z.cand);
-            take(w.cand_count, z.cand_count);
-        }
+        take(w.cand, z.cand);
+        take(w.cand_count, z.cand_count);
         fits = off <= kNoAllocScratch;
         if (fits || !gram) break;
     }
@@ -1199,7 +1196,8 @@ extern "C" int pfac_scan_batch_plain(const pfac_trie *t, pfac_workspace *w,
         max_tiles = std::max(max_tiles, tiles_for(n, 15, std::min(unit_bytes(t, tn), kWaveChunk)));
         split = split || uses_split(t, tn);
     }
-    rc = ws_reserve(w, max_tiles, capacity, split);
+    const bool gram = use_gram_kernel(t);
+    rc = ws_reserve(w, max_tiles, capacity, split && !gram, gram);
     if (rc) return rc;
     HIP_TRY(launch_fill_u32((uint32_t *)w->running(), 2, 0, s));
     for (uint32_t i = 0; i < n_texts; i++) {
@@ -1314,7 +1312,7 @@ extern "C" int pfac_graph_create_batch(const pfac_trie *t, pfac_workspace *w,
         const pfac_tuning tn = launch_tuning(t, total_bytes);
         if (rc == PFAC_OK)
             rc = ws_reserve(g->ws, tiles_for(total_bytes, 15, std::min(unit_bytes(t, tn), kWaveChunk)),
-                            capacity, uses_split(t, tn));
+                            capacity, uses_split(t, tn) && !use_gram_kernel(t), use_gram_kernel(t));
     }
     if (rc != PFAC_OK) {
         pfac_graph_free(g);

@@ -171,7 +171,34 @@ def reserved_scans_allocate_nothing():
     assert not [ln for ln in _lines() if ln.startswith("host malloc")]
 
 
-TESTS = [lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
+def _areas(lines):
+    return [int(ln.split()[1]) for ln in lines if ln.startswith("malloc ")]
+
+
+def first_scan_allocates_what_it_reads():
+    """The first scan of a workspace allocates no more areas than the tile
+    kernel does, whose launches the gram kernel took over: counts, offsets and
+    first texts per unit, the staging area, the inline slots and the list area
+    (in place of the chunks' boundaries and the block sums)."""
+    trie = pf.Trie(_bytes_set(500))
+    for n in (1460, 5_000_011):
+        calls = [lambda ws: pf.pfac_scan(trie, ws, TEXT, n, OUT, 100, COUNT),
+                 lambda ws: pf.pfac_scan_batch(trie, ws, TEXT, OFFSETS, 3, n, OUT, 100, COUNT),
+                 lambda ws: pf.pfac_scan_batch_plain(trie, ws, TEXT, np.array([0, n], dtype=np.uint64), 1, OUT, 100,
+                                                     COUNT)]
+        for call in calls:
+            ws = pf.Workspace()
+            _lines()
+            call(ws)
+            lines = _lines()
+            assert "scan_grams" in _kernels(lines)
+            assert len(_areas(lines)) == 6, lines
+        _lines()
+        pf.Graph(trie, None, TEXT, OFFSETS, 3, n, OUT, 100, COUNT)
+        assert len(_areas(_lines())) == 1 + 6  # and the cursor's
+
+
+TESTS = [first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
 
 
 @pytest.mark.parametrize("name", [t.__name__ for t in TESTS])
