@@ -241,7 +241,9 @@ int pfac_trie_launch_kernel(const pfac_trie *t, uint64_t total_bytes, uint32_t *
 /* -------------------------------------------------------------- workspace */
 
 /* Device scratch for scans: match staging, per-tile counts, plan tables.
- * It grows on demand (hipMalloc) and is reused across calls. */
+ * It grows on demand (hipMalloc) and is reused across calls.  Where the device
+ * cannot hold the gram kernel's list area, scans on the workspace run the
+ * kernels that need none, until pfac_workspace_reserve is called again. */
 int pfac_workspace_create(pfac_workspace **out);
 void pfac_workspace_free(pfac_workspace *w);
 /* Pre-size the scratch for texts of up to `max_bytes` bytes, `max_texts`

@@ -119,6 +119,10 @@ struct pfac_workspace {
     // (partly) queued.  The next scan clears it on its own stream.
     bool cursor_stale = false;
     uint64_t *host_count = nullptr;  // count of synchronous scans, in pinned memory
+    // Bytes of the gram kernel's list area from which on the device could not
+    // hold it: scans that need as much run the other kernels and do not ask
+    // again (an allocation that fails would cost every scan, and end a capture).
+    uint64_t no_lists = kNoSize;
     // misc: [0] stage cursor, [1] running total, [2] per-launch count
     unsigned long long *cursor() { return (unsigned long long *)misc.p; }
     unsigned long long *running() { return (unsigned long long *)misc.p + 1; }
@@ -746,8 +750,8 @@ static WsSizes ws_sizes(uint64_t n_tiles, uint64_t capacity, bool split, bool gr
     return z;
 }
 
-static int ws_reserve(pfac_workspace *w, uint64_t n_tiles, uint64_t capacity, bool split, bool gram) {
-    const WsSizes z = ws_sizes(n_tiles, capacity, split, gram);
+// all areas but the candidate lists
+static int ws_reserve_areas(pfac_workspace *w, const WsSizes &z) {
     HIP_TRY(w->unit_count.reserve(z.unit_count));
     HIP_TRY(w->unit_off.reserve(z.unit_off));
     HIP_TRY(w->tile_first.reserve(z.tile_first));
@@ -755,8 +759,31 @@ static int ws_reserve(pfac_workspace *w, uint64_t n_tiles, uint64_t capacity, bo
     HIP_TRY(w->blocksum.reserve(z.blocksum));
     HIP_TRY(w->stage.reserve(z.stage));
     HIP_TRY(w->inline_stage.reserve(z.inline_stage));
+    return PFAC_OK;
+}
+
+static int ws_reserve(pfac_workspace *w, uint64_t n_tiles, uint64_t capacity, bool split) {
+    const WsSizes z = ws_sizes(n_tiles, capacity, split, false);
+    const int rc = ws_reserve_areas(w, z);
+    if (rc != PFAC_OK) return rc;
     HIP_TRY(w->cand.reserve(z.cand));
     HIP_TRY(w->cand_count.reserve(z.cand_count));
+    return PFAC_OK;
+}
+
+// Room for a scan by the gram kernel; `gram` is cleared where its list area
+// cannot be had.
+static int ws_reserve_gram(pfac_workspace *w, uint64_t n_tiles, uint64_t capacity, bool &gram) {
+    const WsSizes z = ws_sizes(n_tiles, capacity, false, true);
+    gram = gram && z.cand < w->no_lists;
+    if (!gram) return PFAC_OK;
+    const int rc = ws_reserve_areas(w, z);
+    if (rc != PFAC_OK) return rc;
+    const hipError_t e = w->cand.reserve(z.cand);
+    if (e == hipSuccess) return PFAC_OK;
+    if (hip_fail(e) != PFAC_ENOMEM) return PFAC_EDEVICE;
+    w->no_lists = z.cand;
+    gram = false;
     return PFAC_OK;
 }
 
@@ -774,7 +801,8 @@ extern "C" int pfac_workspace_reserve(pfac_workspace *w, uint64_t max_bytes, uin
     // sizes whose byte counts would not even fit in 64 bits cannot be allocated
     if (max_bytes > (1ull << 56) || max_matches > (1ull << 56)) return PFAC_ENOMEM;
     uint64_t n_tiles = (max_bytes + 16 + kWG * 4 - 1) / (kWG * 4);  // smallest tile
-    return ws_reserve(w, n_tiles, max_matches, true, false);
+    w->no_lists = kNoSize;
+    return ws_reserve(w, n_tiles, max_matches, true);
 }
 
 // ---------------------------------------------------------------------- scan
@@ -903,7 +931,16 @@ static ScanShape scan_shape(const pfac_trie *t, const pfac_tuning &tn, const voi
 static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
     const pfac_trie *t = L.t;
     const pfac_tuning tn = launch_tuning(t, L.total);
-    const ScanShape h = scan_shape(t, tn, L.text, L.total, allow_gram);
+    ScanShape h = scan_shape(t, tn, L.text, L.total, allow_gram);
+    if (reserve) {
+        bool with_lists = h.gram;
+        int rc = ws_reserve_gram(L.w, h.ws_units(), L.capacity, with_lists);
+        if (rc == PFAC_OK && !with_lists) {
+            if (h.gram) h = scan_shape(t, tn, L.text, L.total, false);
+            rc = ws_reserve(L.w, h.ws_units(), L.capacity, h.split);
+        }
+        if (rc != PFAC_OK) return rc;
+    }
     uint32_t waves = h.waves;
     const bool gram = h.gram;
     const bool wave_kernel = h.wave_kernel;
@@ -915,10 +952,6 @@ static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
     // the batch plan is per 1 KiB chunk for the wave kernel, per tile otherwise
     const uint32_t plan_unit = h.plan_unit;
     const uint64_t n_plan = h.n_plan;
-    if (reserve) {
-        int rc = ws_reserve(L.w, h.ws_units(), L.capacity, split, gram);
-        if (rc != PFAC_OK) return rc;
-    }
     pfac_workspace *w = L.w;
     const uint32_t n_sums = (uint32_t)std::max<uint64_t>(1, (n_tiles + (1u << kSumShift) - 1) >> kSumShift);
 
@@ -1196,8 +1229,9 @@ extern "C" int pfac_scan_batch_plain(const pfac_trie *t, pfac_workspace *w,
         max_tiles = std::max(max_tiles, tiles_for(n, 15, std::min(unit_bytes(t, tn), kWaveChunk)));
         split = split || uses_split(t, tn);
     }
-    const bool gram = use_gram_kernel(t);
-    rc = ws_reserve(w, max_tiles, capacity, split && !gram, gram);
+    bool gram = use_gram_kernel(t);
+    rc = ws_reserve_gram(w, max_tiles, capacity, gram);
+    if (rc == PFAC_OK && !gram) rc = ws_reserve(w, max_tiles, capacity, split);
     if (rc) return rc;
     HIP_TRY(launch_fill_u32((uint32_t *)w->running(), 2, 0, s));
     for (uint32_t i = 0; i < n_texts; i++) {
@@ -1205,7 +1239,7 @@ extern "C" int pfac_scan_batch_plain(const pfac_trie *t, pfac_workspace *w,
         if (n == 0) continue;
         Launch L{t, w, texts_dev + offsets_host[i], n, nullptr, 1, i, out_dev, capacity,
                  w->tmp_count(), nullptr, w->running(), s};
-        rc = enqueue_scan(L, false);
+        rc = enqueue_scan(L, false, gram);
         if (rc) return rc;
         HIP_TRY(launch_add_running(w->running(), w->tmp_count(), s));
     }
@@ -1307,12 +1341,13 @@ extern "C" int pfac_graph_create_batch(const pfac_trie *t, pfac_workspace *w,
     if (rc == PFAC_OK)
         rc = check_scan_args(t, g->ws, texts_dev, total_bytes, out_dev, capacity, n_matches_dev);
     if (rc == PFAC_OK && !offsets_dev) rc = PFAC_EINVAL;
-    if (rc == PFAC_OK)
-    {
+    bool gram = false;
+    if (rc == PFAC_OK) {
         const pfac_tuning tn = launch_tuning(t, total_bytes);
-        if (rc == PFAC_OK)
-            rc = ws_reserve(g->ws, tiles_for(total_bytes, 15, std::min(unit_bytes(t, tn), kWaveChunk)),
-                            capacity, uses_split(t, tn) && !use_gram_kernel(t), use_gram_kernel(t));
+        const uint64_t units = tiles_for(total_bytes, 15, std::min(unit_bytes(t, tn), kWaveChunk));
+        gram = use_gram_kernel(t);
+        rc = ws_reserve_gram(g->ws, units, capacity, gram);
+        if (rc == PFAC_OK && !gram) rc = ws_reserve(g->ws, units, capacity, uses_split(t, tn));
     }
     if (rc != PFAC_OK) {
         pfac_graph_free(g);
@@ -1365,7 +1400,7 @@ extern "C" int pfac_graph_create_batch(const pfac_trie *t, pfac_workspace *w,
         if (e == hipSuccess) {
             Launch L{t, g->ws, texts_dev, total_bytes, offsets_dev, n_texts, 0, out_dev, capacity,
                      n_matches_dev, nullptr, nullptr, s};
-            rc = enqueue_scan(L, false);
+            rc = enqueue_scan(L, false, gram);
             hipGraph_t graph = nullptr;
             hipError_t e2 = hipStreamEndCapture(s, &graph);
             g->graph = graph;

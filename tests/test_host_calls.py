@@ -198,7 +198,56 @@ def first_scan_allocates_what_it_reads():
         assert len(_areas(_lines())) == 1 + 6  # and the cursor's
 
 
-TESTS = [first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
+def list_area_refused():
+    """Where the device cannot hold the gram kernel's list area (512 bytes a
+    KiB), the kernels that ran these scans without one still do; the workspace
+    asks again only when it is reserved anew, so captured scans after a first
+    one find it ready."""
+    n = 5_000_011
+    words = [bytes(np.random.default_rng(i).choice(np.arange(97, 107), 9).astype(np.uint8)) for i in range(300)]
+    offsets = np.array([0, n // 3, n], dtype=np.uint64)
+    for pats, kernel in ((_bytes_set(500), "scan_tiles"), (words, "scan_waves")):
+        trie = pf.Trie(pats)
+        for call in (lambda: pf.pfac_scan(trie, ws, TEXT, n, OUT, 100, COUNT),
+                     lambda: pf.pfac_scan_sync(trie, ws, TEXT, n, OUT, 100),
+                     lambda: pf.pfac_scan_batch(trie, ws, TEXT, OFFSETS, 2, n, OUT, 100, COUNT),
+                     lambda: pf.pfac_scan_batch_plain(trie, ws, TEXT, offsets, 2, OUT, 100, COUNT),
+                     lambda: pf.Graph(trie, None, TEXT, OFFSETS, 2, n, OUT, 100, COUNT)):
+            ws = pf.Workspace()
+            hip.host_hip_limit(1 * MiB)
+            _lines()
+            call()
+            lines = _lines()
+            assert kernel in _kernels(lines) and "scan_grams" not in _kernels(lines), lines
+            hip.host_hip_limit(1 << 40)
+        call = lambda: pf.pfac_scan(trie, ws, TEXT, n, OUT, 100, COUNT)  # noqa: E731
+        ws = pf.Workspace()
+        hip.host_hip_limit(1 * MiB)
+        call()
+        _lines()
+        call()
+        lines = _lines()
+        assert not [ln for ln in lines if "malloc" in ln or ln.startswith("sync")]
+        assert kernel in _kernels(lines)
+        with pytest.raises(pf.PfacError) as e:
+            ws.reserve(n, 1, 100)
+        assert e.value.code == pf.PFAC_ENOMEM
+        hip.host_hip_limit(1 << 40)
+        ws.reserve(n, 1, 100)
+        _lines()
+        call()
+        assert "scan_grams" in _kernels()
+        # the split kernels always needed theirs
+        ws = pf.Workspace()
+        hip.host_hip_limit(6 * MiB)
+        if kernel == "scan_tiles":
+            with pytest.raises(pf.PfacError) as e:
+                pf.pfac_scan(trie, ws, TEXT, 16 * MiB, OUT, 100, COUNT)
+            assert e.value.code == pf.PFAC_ENOMEM
+        hip.host_hip_limit(1 << 40)
+
+
+TESTS = [list_area_refused, first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
 
 
 @pytest.mark.parametrize("name", [t.__name__ for t in TESTS])
