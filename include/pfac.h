@@ -127,9 +127,11 @@ typedef struct {
                                   that keeps few positions), else by launch size 2 with
                                   units of up to 64 chunks for launches (a text, or a whole
                                   batch) of 8 MiB or more, else 0 with 4 bytes per lane
-                                  below 1 MiB and 8 from there.  A trie whose tuning is as
-                                  it was built takes the gram kernel likewise.  Statistics
-                                  report the kernel of large launches without it */
+                                  below 1 MiB and 8 from there.  A trie whose tuning was
+                                  never set takes the gram kernel likewise (kernel 3 brings
+                                  that back); kernels 0, 1 and 2, once set, always run.
+                                  Statistics report the kernel of large launches without
+                                  the gram kernel */
     uint32_t bytes_per_lane;   /* tile kernel: start positions per lane per tile: 4, 8 or 16 */
     uint32_t index_bits;       /* level-index width in bits (1..18); depth K = bits / symbol_bits */
     uint32_t fold_bits;        /* wave kernel prefix filter: 0 (level bitmap), 8 or 16 bits per node */

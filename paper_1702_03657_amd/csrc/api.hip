@@ -86,7 +86,8 @@ struct pfac_trie {
     CrsTrie crs;
     DeviceImageHost img;
     pfac_tuning tuning{1, 16, 16, 8, 0, 16, 16, 1};
-    pfac_tuning built{};                    // the tuning chosen at the build
+    // no tuning was set: the library chooses the kernel as with kernel 3
+    std::atomic<bool> by_library{true};
     uint32_t lds_limit = 160 * 1024;  // dynamic LDS a workgroup may use (gfx950; queried on the device)
     bool host_only = false;
     int device = -1;
@@ -353,7 +354,6 @@ static int build_common(const uint8_t *data, const uint64_t *offsets, uint32_t k
     if (t->img.identity && t->img.K == 2) t->tuning.kernel = 3;
     if (t->img.pfx4_log2) t->tuning.child_check = 2;
     if (t->img.q16_lw) t->tuning.kernel = 3;  // four-symbol alphabets: the 16-symbol filter
-    t->built = t->tuning;
     t->build_s = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     set_halo(t);
     t->host_only = (flags & PFAC_BUILD_HOST_ONLY) != 0;
@@ -677,9 +677,10 @@ extern "C" int pfac_trie_set_tuning(pfac_trie *t, const pfac_tuning *tn) {
         if (rc != PFAC_OK) {  // the previous device image is still in place
             t->tuning = old;
             std::swap(t->img, fresh);
+            return rc;
         }
-        return rc;
     }
+    t->by_library = false;
     return PFAC_OK;
 }
 
@@ -875,11 +876,11 @@ struct ScanShape {
     uint64_t ws_units() const { return std::max(n_tiles, n_plan); }
 };
 
-// The gram kernel runs the launches whose kernel the library chooses (kernel
-// 3, or the tuning of the build), where the image has a gram filter.
+// The gram kernel runs the launches whose kernel the library chooses, where the
+// image has a gram filter.  Asked once per scan: a set_tuning may come between
+// (of the same values, which a server's trie accepts).
 static bool use_gram_kernel(const pfac_trie *t) {
-    return (t->tuning.kernel == 3 || same_tuning(t->tuning, t->built)) && t->img.gram_s && !t->img.trunc_depth &&
-           !t->img.dag;
+    return (t->tuning.kernel == 3 || t->by_library.load()) && t->img.gram_s && !t->img.trunc_depth && !t->img.dag;
 }
 
 // Launch shape of the gram kernel, placed by a sweep of 16 KiB to 32 MiB with
@@ -893,11 +894,10 @@ static bool use_gram_kernel(const pfac_trie *t) {
 constexpr uint64_t kGramFewChunks = 2560;
 constexpr uint32_t kGramSmallTable = 12;  // log2 of its words
 
-static ScanShape scan_shape(const pfac_trie *t, const pfac_tuning &tn, const void *text, uint64_t total,
-                            bool allow_gram = true) {
+static ScanShape scan_shape(const pfac_trie *t, const pfac_tuning &tn, const void *text, uint64_t total, bool gram) {
     ScanShape h{};
     h.shift = (uintptr_t)text & 15;
-    h.gram = allow_gram && use_gram_kernel(t);
+    h.gram = gram;
     if (h.gram) {
         h.wave_kernel = true;
         const uint64_t chunks = tiles_for(total, h.shift, kWaveChunk);
@@ -928,21 +928,20 @@ static ScanShape scan_shape(const pfac_trie *t, const pfac_tuning &tn, const voi
     return h;
 }
 
-static int enqueue_scan(const Launch &L, bool reserve, bool allow_gram = true) {
+// gram: by the gram kernel (use_gram_kernel)
+static int enqueue_scan(const Launch &L, bool reserve, bool gram) {
     const pfac_trie *t = L.t;
     const pfac_tuning tn = launch_tuning(t, L.total);
-    ScanShape h = scan_shape(t, tn, L.text, L.total, allow_gram);
+    ScanShape h = scan_shape(t, tn, L.text, L.total, gram);
     if (reserve) {
-        bool with_lists = h.gram;
-        int rc = ws_reserve_gram(L.w, h.ws_units(), L.capacity, with_lists);
-        if (rc == PFAC_OK && !with_lists) {
-            if (h.gram) h = scan_shape(t, tn, L.text, L.total, false);
+        int rc = ws_reserve_gram(L.w, h.ws_units(), L.capacity, gram);
+        if (rc == PFAC_OK && !gram) {
+            h = scan_shape(t, tn, L.text, L.total, false);
             rc = ws_reserve(L.w, h.ws_units(), L.capacity, h.split);
         }
         if (rc != PFAC_OK) return rc;
     }
     uint32_t waves = h.waves;
-    const bool gram = h.gram;
     const bool wave_kernel = h.wave_kernel;
     const bool split = h.split;
     const uint32_t bpl = tn.bytes_per_lane;
@@ -1098,7 +1097,7 @@ extern "C" int pfac_scan(const pfac_trie *t, pfac_workspace *w, const uint8_t *t
     if (rc) return rc;
     Launch L{t, w, text_dev, n, nullptr, 1, 0, out_dev, capacity, n_matches_dev, counts_dev,
              nullptr, (hipStream_t)stream};
-    return enqueue_scan(L, true);
+    return enqueue_scan(L, true, use_gram_kernel(t));
 }
 
 // ------------------------------------------------- scan without allocation
@@ -1208,7 +1207,7 @@ extern "C" int pfac_scan_batch(const pfac_trie *t, pfac_workspace *w, const uint
     if (!offsets_dev || (n_texts == 0 && total_bytes != 0)) return PFAC_EINVAL;
     Launch L{t, w, texts_dev, total_bytes, offsets_dev, n_texts, 0, out_dev, capacity,
              n_matches_dev, nullptr, nullptr, (hipStream_t)stream};
-    return enqueue_scan(L, true);
+    return enqueue_scan(L, true, use_gram_kernel(t));
 }
 
 extern "C" int pfac_scan_batch_plain(const pfac_trie *t, pfac_workspace *w,
@@ -1549,7 +1548,10 @@ static int autotune_common(pfac_trie *t, pfac_workspace *w, const void *ctx, tun
         return rc;
     }
 
+    // the launches as they are, under a name that asks for them (kernel 3 where
+    // the library chose the gram kernel), and the grid
     std::vector<pfac_tuning> cands(1, start);
+    if (use_gram_kernel(t)) cands[0].kernel = 3;
     for (uint32_t bits : {12u, 16u, 18u}) {
         for (uint32_t fold : {8u, 16u, 0u})
             for (uint32_t kernel : {1u, 2u})
@@ -1568,7 +1570,7 @@ static int autotune_common(pfac_trie *t, pfac_workspace *w, const void *ctx, tun
         for (auto &c : cands) c.trunc_depth = start.trunc_depth;
     }
     float best_ms = 1e30f;
-    pfac_tuning best_t = start;
+    pfac_tuning best_t = cands[0];
     std::vector<uint64_t> seen;  // (bytes per lane, index depth, wg per CU) already timed
     for (const pfac_tuning &c : cands) {
         if (pfac_trie_set_tuning(t, &c) != PFAC_OK) continue;

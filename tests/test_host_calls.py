@@ -247,7 +247,46 @@ def list_area_refused():
         hip.host_hip_limit(1 << 40)
 
 
-TESTS = [list_area_refused, first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
+def explicit_kernels_run():
+    """Kernels 0, 1 and 2 mean what they say, also where a call sets the very
+    values that the build chose; kernel 3, and a trie whose tuning was never
+    set, leave the choice to the library."""
+    rng = np.random.default_rng(3)
+    words = [bytes(rng.choice(np.arange(97, 107), 9).astype(np.uint8)) for _ in range(300)]
+    main = {0: "scan_tiles", 1: "scan_waves", 2: "scan_waves", 3: "scan_grams"}
+
+    def ran(trie, n=9 * MiB):
+        _lines()
+        pf.pfac_scan(trie, pf.Workspace(), TEXT, n, OUT, 100, COUNT)
+        lines = _lines()
+        name, = [k for k in _kernels(lines) if k in main.values()]
+        return name, "walk_units" in _kernels(lines)
+
+    for pats, chosen in ((words, 1), (_bytes_set(500), 3), ([b"ACGTACGTAC" + bytes([c]) for c in b"ACGT"], 1)):
+        trie = pf.Trie(pats)
+        built = trie.tuning()
+        assert built["kernel"] == chosen
+        assert ran(trie) == ("scan_grams", False)
+        for kernel in (chosen, 0, 1, 2, 3, 1):
+            trie.set_tuning(kernel=kernel)
+            assert trie.tuning() == dict(built, kernel=kernel)
+            assert ran(trie) == (main[kernel], kernel == 2)
+        # other fields of a tuning are a choice as well
+        trie = pf.Trie(pats)
+        trie.set_tuning(waves_per_wg=8)
+        assert ran(trie)[0] == main[chosen]
+
+    # the autotuner times the library's choice and each kernel under its own name
+    trie = pf.Trie(words)
+    best = pf.pfac_autotune(trie, pf.Workspace(), TEXT, 9 * MiB)
+    assert best["kernel"] == 3 and best == trie.tuning()  # all took as long here: the first one stays
+    names = [k for k in _kernels() if k in main.values()]
+    first = next(i for i, k in enumerate(names) if k != "scan_grams")
+    assert 0 < first < 20 and "scan_grams" not in names[first:] and {"scan_tiles", "scan_waves"} <= set(names)
+    assert ran(trie)[0] == "scan_grams"
+
+
+TESTS = [explicit_kernels_run, list_area_refused, first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
 
 
 @pytest.mark.parametrize("name", [t.__name__ for t in TESTS])
