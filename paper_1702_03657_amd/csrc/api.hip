@@ -189,7 +189,8 @@ static int upload_image(pfac_trie *t) {
     size_t o_gfp = align256(o_gram + I.gram.size() * 4);
     size_t o_grec = align256(o_gfp + I.gfp.size() * 2);
     size_t o_gpat = align256(o_grec + I.grec.size() * 4);
-    size_t total = align256(o_gpat + I.gpat.size());
+    size_t o_gper = align256(o_gpat + I.gpat.size());
+    size_t total = align256(o_gper + I.gper.size() * 4);
     auto t0 = std::chrono::steady_clock::now();
     // the new image is built beside the old one, which stays usable if this fails
     DeviceBuf fresh;
@@ -245,6 +246,8 @@ static int upload_image(pfac_trie *t) {
             CP(hipMemcpy(b + o_grec, I.grec.data(), I.grec.size() * 4, hipMemcpyHostToDevice));
         if (!I.gpat.empty())
             CP(hipMemcpy(b + o_gpat, I.gpat.data(), I.gpat.size(), hipMemcpyHostToDevice));
+        if (!I.gper.empty())
+            CP(hipMemcpy(b + o_gper, I.gper.data(), I.gper.size() * 4, hipMemcpyHostToDevice));
         return hipSuccess;
     };
 #undef CP
@@ -297,6 +300,9 @@ static int upload_image(pfac_trie *t) {
     v.gfp = (const uint4 *)(b + o_gfp);
     v.grec = (const uint4 *)(b + o_grec);
     v.gpat = b + o_gpat;
+    v.gper = (const uint32_t *)(b + o_gper);
+    v.gper_lw = I.gper_lw;
+    v.gram_alph = I.gram_alph;
     v.gram_s = I.gram_s;
     v.gram_lw = I.gram_lw;
     v.gram_run = I.gram_run;

@@ -666,6 +666,9 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
             }
         }
     };
+    // bytes: the last gram seen that starts nothing behind the dword pass_y
+    uint32_t pass_x = im.gram_alph, pass_y = pass_x;
+    if (!SYM) asm volatile("" : "+v"(pass_x), "+v"(pass_y));
     // the TL tests of a lane's 16 positions from unit position pos on
     auto tests = [&](const Slot &s, uint32_t pos) {
         const uint32_t w[5] = {s.v.x, s.v.y, s.v.z, s.v.w, s.h};
@@ -704,6 +707,49 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
             }
             queue_bits(m, p0, p1, pos);
             return;
+        }
+        // Where a text repeats up to eight bytes (padding, blanks, tables), a gram
+        // of theirs hits in every lane, though at offset 1 .. S-1 of a pattern
+        // that may start nowhere in it.  In chunks that do (one compare) the hits
+        // count only if a pattern begins with the four bytes from one of the S
+        // starts on: asked once for a pair of dwords, those of one lane that repeats
+        // itself.  (64 MiB
+        // with 64 KiB runs of zeros for a tenth of it, one pattern in a hundred
+        // with four zeros past its first byte: 210 us without this, 30 with; the
+        // prefix filter of the split kernels 51.)
+        if (S > 1 && __builtin_expect(__ballot(w[0] == w[2]) != 0, 0)) {
+            // the dword before the lane's 16 bytes (of lane - 1; lane 0 takes one
+            // that none equals)
+            const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp((int)~pass_y, (int)w[3], 0x138, 0xf, 0xf, false);
+            const ScanArgs &r = again(a);
+            const scalar_u32_t *first = (const scalar_u32_t *)(uintptr_t)r.im.gper;
+            constexpr uint32_t P = 4 / S;  // tests a dword
+#pragma unroll
+            for (uint32_t k = 0; k < 2 * P; k++) {
+                const unsigned long long hits = __ballot(w[0] == w[2] && w[1] == w[3] && test(ent[P + k], h[P + k], x[P + k]) != 0 &&
+                                                         (x[P + k] != pass_x || x[k] != pass_y));
+                if (hits) {
+                    const int l = (int)__builtin_ctzll(hits);
+                    const uint32_t x0 = (uint32_t)__builtin_amdgcn_readlane((int)x[P + k], l);
+                    const uint32_t y0 = (uint32_t)__builtin_amdgcn_readlane((int)x[k], l);
+                    uint32_t any = 0;
+#pragma unroll
+                    for (uint32_t o = 0; o < S; o++) {
+                        const uint32_t f = o == 0 ? x0 : __builtin_amdgcn_alignbyte(x0, y0, 4 - o), g = f * kPfx4Mul;
+                        const uint32_t e = first[g >> (32 - r.im.gper_lw)];
+                        any |= (e >> ((g >> 5) & 31)) & (e >> (f >> 27)) & 1;
+                    }
+                    if (!any) {
+                        pass_x = x0;
+                        pass_y = y0;
+                    }
+                }
+#pragma unroll
+                for (uint32_t j = k; j < TL; j += 2 * P) {
+                    const uint32_t y = j >= P ? x[j - P] : k == 0 ? before : __builtin_amdgcn_alignbyte(w[0], before, k * S);
+                    ent[j] = x[j] == pass_x && y == pass_y ? 0u : ent[j];
+                }
+            }
         }
 #pragma unroll
         for (uint32_t j = 0; j < TL; j++) queue(test(ent[j], h[j], x[j]), x[j], pos + j * S);
@@ -857,6 +903,30 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
                                     om = 1u << (rec.y >> 16 & 3u);
                                 else if (eq)
                                     h = make_uint2(rec.z, rec.y >> 18);
+                            }
+                        }
+                        // Of the starts that a record of several nodes leaves,
+                        // only those whose first four bytes are a pattern's:
+                        // two loads instead of a walk for each (blanks and the
+                        // like: one in 200 patterns with four of them past its
+                        // first byte, runs of 40 bytes for a tenth of 64 MiB, 45
+                        // us, 58 with the walks).
+                        if (SYM == 0 && S > 1 && om && rec.x == kNone) {
+                            // (the gram's dword and the one before; three where
+                            // it need not be aligned)
+                            const uint64_t q = ubase + t + (S - 1), q4 = q & ~3ull;
+                            if (q4 >= 4 && q4 + (S == 4 ? 4 : 8) <= blk_hi + 16) {
+                                const uint32_t *tw = (const uint32_t *)(r.base + q4);
+                                const uint32_t w0 = tw[-1], w1 = tw[0], w2 = S == 4 ? 0u : tw[1];
+                                const uint32_t at = S == 4 ? 0u : (uint32_t)q & 3u;
+                                uint32_t no = 0;
+#pragma unroll
+                                for (uint32_t o = 0; o < S; o++) {
+                                    const uint32_t x = at >= o ? __builtin_amdgcn_alignbyte(w2, w1, at - o) : __builtin_amdgcn_alignbyte(w1, w0, 4 + at - o);
+                                    const uint32_t g = x * kPfx4Mul, w = r.im.gper[g >> (32 - r.im.gper_lw)];
+                                    no |= (~((w >> ((g >> 5) & 31)) & (w >> (x >> 27))) & 1u) << o;
+                                }
+                                om &= ~no;
                             }
                         }
                         for (;;) {

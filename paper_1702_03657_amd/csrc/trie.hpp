@@ -162,6 +162,11 @@ struct DeviceImageHost {
     //    node << 8, the offset in gpat of a pattern below it, the node.
     //    Otherwise kNone and the offsets of the grams as bits 1 << offset;
     //  - gpat: every pattern's bytes, each from a multiple of four on.
+    //  - gper (grams of bytes): for the first four bytes x of every pattern, bits
+    //    (x * kPfx4Mul >> 5) & 31 and x >> 27 of word x * kPfx4Mul >> (32 -
+    //    gper_lw): whether a pattern may begin so, for texts that repeat a few
+    //    bytes (padding, blanks) and grams of several nodes.  gram_alph is a
+    //    dword that no pattern begins with at any byte of its repetition.
     uint32_t gram_s = 0;               // S: 4, 2 or 1 (0 = no gram filter)
     uint32_t gram_lw = 0, gfp_lb = 0;
     uint32_t gram_q = 0, gram_sh = 0, gram_run = 0;  // gram_q 0: grams of four bytes
@@ -169,6 +174,8 @@ struct DeviceImageHost {
     std::vector<uint16_t> gfp;
     std::vector<uint32_t> grec;
     std::vector<uint8_t> gpat;
+    uint32_t gper_lw = 0, gram_alph = 0;
+    std::vector<uint32_t> gper;
 };
 
 // Multiplicative (Fibonacci) hashing, Knuth TAOCP vol. 3, 6.4: odd

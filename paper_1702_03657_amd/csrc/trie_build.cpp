@@ -655,12 +655,18 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
         I.gfp.clear();
         I.grec.clear();
         I.gpat.clear();
+        I.gper.clear();
     };
     I.gram_q = sym ? Q : 0;
     I.gram_run = run;
     I.gram_s = S;
     I.gram_lw = lg - 5;
     I.gram.assign(1u << I.gram_lw, 0);
+    if (!sym) {  // 32 bits a first gram: 0.4% of the others look like one
+        I.gper_lw = 1;
+        while ((1ull << I.gper_lw) < level(4)) I.gper_lw++;
+        I.gper.assign(1u << I.gper_lw, 0);
+    }
     struct Gram {
         uint32_t x, v, o;  // gram, trie node it ends at, offset
     };
@@ -678,7 +684,17 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
             const uint32_t w = (h >> (run ? 2 : kGramShift)) & ((1u << I.gram_lw) - 1u);
             I.gram[w] |= (run ? 0u : 1u << (h & 31)) | (1u << (x & 31));
             if (o < S) grams.push_back(Gram{x, v, o});
+            const uint32_t g = x * kPfx4Mul;
+            if (!sym && o == 0) I.gper[g >> (32 - I.gper_lw)] |= (1u << ((g >> 5) & 31)) | (1u << (x >> 27));
         }
+    auto begins = [&](uint32_t x) {
+        const uint32_t g = x * kPfx4Mul, w = I.gper[g >> (32 - I.gper_lw)];
+        return (w >> ((g >> 5) & 31)) & (w >> (x >> 27)) & 1;
+    };
+    if (!sym)
+        while (begins(I.gram_alph) || begins(I.gram_alph << 8 | I.gram_alph >> 24) ||
+               begins(I.gram_alph << 16 | I.gram_alph >> 16) || begins(I.gram_alph << 24 | I.gram_alph >> 8))
+            I.gram_alph++;
     // buckets of 14 slots: about three grams each, more buckets while one
     // overflows.  The grams in the order of their buckets:
     struct Slot {
