@@ -62,7 +62,7 @@ struct ImageView {
     const uint32_t *gper;     // gram filter: first four bytes of the patterns, hashed (2^gper_lw words)
     uint32_t gram_s, gram_lw, gfp_lb, min_len;
     uint32_t gram_run;        // a position counts when the three after it hit too
-    uint32_t gper_lw, gram_alph;
+    uint32_t gper_lw, gram_alph;  // (grams of symbols: the alphabet's bytes)
     uint32_t gram_q, gram_sh;  // grams of gram_q two-bit symbols, from bit gram_sh of a byte (0: of four bytes)
 };
 

@@ -705,6 +705,24 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
             } else {
                 m >>= 32 - TL;
             }
+            // a lane whose tests all hit: a run of one symbol, or of a byte
+            // outside the alphabet that looks like one (N in place of G); there
+            // only the tests at bytes of the alphabet are left (128 MiB, a tenth of
+            // it N, 20,000 patterns and G x 20: 1,429 us without this, 45 with; the
+            // 16-symbol filter 108)
+            constexpr uint32_t kAll = (1u << TL) - 1u;
+            if (__builtin_expect(__ballot((m & kAll) == kAll) != 0, 0)) {
+                const uint32_t alph = again(a).im.gram_alph;
+                uint32_t other = 0;
+#pragma unroll
+                for (uint32_t q = 0; q < 4; q++) {
+                    const uint32_t d = w[q] ^ __builtin_amdgcn_perm(alph, alph, (w[q] >> sym_sh) & 0x03030303u);
+                    const uint32_t nz = ((d & 0x7f7f7f7fu) + 0x7f7f7f7fu) | d;  // upper bit of each byte of d that is not zero
+#pragma unroll
+                    for (uint32_t b = 0; b < 4; b += S) other |= ((nz >> (8 * b + 7)) & 1u) << ((4 * q + b) / S);
+                }
+                m &= ~other;
+            }
             queue_bits(m, p0, p1, pos);
             return;
         }

@@ -166,7 +166,10 @@ struct DeviceImageHost {
     //    (x * kPfx4Mul >> 5) & 31 and x >> 27 of word x * kPfx4Mul >> (32 -
     //    gper_lw): whether a pattern may begin so, for texts that repeat a few
     //    bytes (padding, blanks) and grams of several nodes.  gram_alph is a
-    //    dword that no pattern begins with at any byte of its repetition.
+    //    dword that no pattern begins with at any byte of its repetition;
+    //  - gram_alph (symbols): the alphabet's byte for each value of the two bits
+    //    (any of its bytes where none has that value): other bytes of a text
+    //    (N) look like one of them.
     uint32_t gram_s = 0;               // S: 4, 2 or 1 (0 = no gram filter)
     uint32_t gram_lw = 0, gfp_lb = 0;
     uint32_t gram_q = 0, gram_sh = 0, gram_run = 0;  // gram_q 0: grams of four bytes

@@ -662,7 +662,12 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
     I.gram_s = S;
     I.gram_lw = lg - 5;
     I.gram.assign(1u << I.gram_lw, 0);
-    if (!sym) {  // 32 bits a first gram: 0.4% of the others look like one
+    if (sym) {
+        uint8_t alph[4];
+        std::memset(alph, T.labels[0], 4);
+        for (const uint8_t c : T.labels) alph[(c >> I.gram_sh) & 3] = c;
+        std::memcpy(&I.gram_alph, alph, 4);
+    } else {  // 32 bits a first gram: 0.4% of the others look like one
         I.gper_lw = 1;
         while ((1ull << I.gper_lw) < level(4)) I.gper_lw++;
         I.gper.assign(1u << I.gper_lw, 0);

@@ -115,6 +115,10 @@ int main() {
                     if (begins(z)) return fail("dword that begins nothing", seed, j, o);
             }
         }
+        if (I.gram_q)
+            for (const char c : data)
+                if ((uint8_t)(I.gram_alph >> (8 * (((uint8_t)c >> I.gram_sh) & 3))) != (uint8_t)c)
+                    return fail("alphabet", seed, 0, 0);
     }
     std::printf("gram sanitizer run: ok, %u sets (%u, %u and %u with S 1, 2 and 4, %u with runs)\n", with, by_s[1], by_s[2],
                 by_s[4], runs);

@@ -1,4 +1,4 @@
-"""Texts that repeat themselves (padding, blank space, tables)
+"""Texts that repeat themselves (padding, blank space, tables, unknown bases)
 against sets that hold what is repeated: record by record against the oracle,
 and the time of a scan, which must not follow the length of the runs when no
 pattern can start in them."""
@@ -72,6 +72,28 @@ def test_runs(lo, more, n, pad):
     assert np.array_equal(counts, oracle.counts(n, want))
 
 
+@pytest.mark.parametrize("lo,hi,k", [(9, 14, 300), (13, 16, 3000), (20, 32, 20_000)])
+def test_symbol_runs(lo, hi, k):
+    rng = np.random.default_rng(lo)
+    a = np.frombuffer(b"ACGT", dtype=np.uint8)
+    n = 4 * MiB + 11
+    pats = [bytes(rng.choice(a, int(m))) for m in rng.integers(lo, hi + 1, k)]
+    pats += [b"G" * lo, b"A" * (lo + 2), b"C" + b"G" * lo, b"G" * lo + b"TC", b"AC" * lo]
+    text = rng.choice(a, n)
+    for at in range(3000, n - 9000, 60_000):
+        c = [b"N", b"G", b"n", b"A", b"\n"][at // 60_000 % 5]
+        m = int(rng.integers(10, 5000))
+        text[at:at + m] = c[0]
+        for q in (at - 1, at + m - 1, at + m // 2):  # a pattern at each end and in the middle
+            p = np.frombuffer(pats[-int(rng.integers(1, 6))], dtype=np.uint8)
+            text[q:q + p.size] = p
+    want = oracle.bucketed(text, pats, threads=8)
+    say(f"gram symbol runs lo={lo}: {want.n} matches")
+    got, counts = gpu_scan(pf.Trie(pats), text, pad_front=3, capacity=want.n)
+    assert_same(got, want)
+    assert np.array_equal(counts, oracle.counts(n, want))
+
+
 def _time(trie, text):
     """Microseconds of a scan, the least of several runs of five."""
     import torch
@@ -92,18 +114,23 @@ def _time(trie, text):
 
 
 # Where every test of a run was checked, a tenth of the text in runs took 3 (4
-# KiB of zeros) or more times the time of the text without them.
+# KiB of zeros) to 13 times (N) the time of the text without them.
 @pytest.mark.parametrize("fill,size,lo", [(b"\0", 1 << 16, 8), (b"\0", 1 << 12, 8), (b"\0", 1 << 16, 5),
-                                          (b"\xff\0", 1 << 16, 8)])
+                                          (b"\xff\0", 1 << 16, 8), (b"N", 1 << 20, 20), (b"N", 1 << 20, 9)])
 def test_time_of_runs(fill, size, lo):
     rng = np.random.default_rng(size + lo)
     n = 64 * MiB
-    pats = [bytearray(rng.integers(1, 255, int(m), dtype=np.uint8).tobytes()) for m in rng.integers(lo, 64, 8000)]
-    for i, p in enumerate(pats[:80]):
-        o = 1 + i % 3 if lo >= 7 else 1
-        p[o:o + 4] = (fill * 4)[:4]
-    pats = [bytes(p) for p in pats]
-    text = rng.integers(0, 256, n, dtype=np.uint8)
+    if fill == b"N":
+        a = np.frombuffer(b"ACGT", dtype=np.uint8)
+        pats = [bytes(rng.choice(a, int(m))) for m in rng.integers(lo, lo + 6, 5000 if lo > 16 else 500)] + [b"G" * lo]
+        text = rng.choice(a, n)
+    else:
+        pats = [bytearray(rng.integers(1, 255, int(m), dtype=np.uint8).tobytes()) for m in rng.integers(lo, 64, 8000)]
+        for i, p in enumerate(pats[:80]):
+            o = 1 + i % 3 if lo >= 7 else 1
+            p[o:o + 4] = (fill * 4)[:4]
+        pats = [bytes(p) for p in pats]
+        text = rng.integers(0, 256, n, dtype=np.uint8)
     trie = pf.Trie(pats)
     plain, found = _time(trie, text)
     for at in rng.integers(0, n - size, max(n // 10 // size, 1)):
