@@ -646,6 +646,21 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
     if (sym && I.qfp_lb && 1024 / S * fp > 60) return;
     // small alphabets: past a quarter of all grams the filter keeps too much
     if (4.0 * (double)n > std::pow((double)I.alphabet, (double)Q)) return;
+    // Before that, where the level index keeps fewer starts: 32 MiB of random
+    // symbols take the gram kernel about 20 + 1.6 us a unit of cost and the fused
+    // kernel 82 + 230 times the share of K-symbol codes in the index, and more
+    // for an index past its place in LDS (us, gram and fused: 6 symbols, 30
+    // patterns 44 and 86, 300 203 and 104; 8, 1,000 209 and 98; 12, 3,000 142 and
+    // 110; 16, 10,000 152 and 176; 20, 30,000 219 and 352).  With two matches
+    // a KiB to expect the fused kernel scans units twice (6 symbols, 100
+    // patterns from four symbols on: 106 and 1,793).
+    if (!sym && I.K) {
+        const double codes = level(I.K);
+        double often = 0;  // matches a KiB
+        for (uint32_t j = 0; j < T.k; j++) often += 1024 * std::pow((double)I.alphabet, -(double)(T.pat_off[j + 1] - T.pat_off[j]));
+        const double fused = 82 + 230 * codes / std::pow((double)I.alphabet, (double)I.K) + (codes > 4096 ? 0.006 * codes : 0.0);
+        if (20 + 1.6 * best > fused && often < 2) return;
+    }
     uint32_t lg = 12;  // bits of the bitmap: 24 a gram, at most 2^20
     while (lg < 20 && (1ull << lg) < (run ? 48 : 24) * n) lg++;
     // without slots of its grams there is no filter

@@ -286,7 +286,23 @@ def explicit_kernels_run():
     assert ran(trie)[0] == "scan_grams"
 
 
-TESTS = [explicit_kernels_run, list_area_refused, first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
+def small_alphabets():
+    """The gram kernel runs the sets over small alphabets that it scans faster
+    than the fused kernel, of random texts: few patterns, or many matches."""
+    for symbols, k, lo, hi, kernel in ((6, 30, 8, 16, "scan_grams"), (6, 300, 8, 16, "scan_waves"),
+                                       (8, 1000, 6, 10, "scan_waves"), (12, 300, 8, 16, "scan_grams"),
+                                       (12, 3000, 8, 16, "scan_waves"), (16, 10_000, 8, 16, "scan_grams"),
+                                       (20, 30_000, 8, 16, "scan_grams"), (26, 30_000, 6, 10, "scan_grams"),
+                                       (6, 100, 4, 8, "scan_grams"), (40, 30_000, 8, 16, "scan_grams")):
+        rng = np.random.default_rng(symbols)
+        a = np.arange(48, 48 + symbols)
+        trie = pf.Trie([bytes(rng.choice(a, int(m)).astype(np.uint8)) for m in rng.integers(lo, hi + 1, k)])
+        _lines()
+        pf.pfac_scan(trie, pf.Workspace(), TEXT, 32 * MiB, OUT, 100, COUNT)
+        assert kernel in _kernels(), (symbols, k, lo)
+
+
+TESTS = [small_alphabets, explicit_kernels_run, list_area_refused, first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
 
 
 @pytest.mark.parametrize("name", [t.__name__ for t in TESTS])
