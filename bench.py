@@ -722,6 +722,7 @@ def placement_ablation(pf, torch, names, steps, warmup, threads):
             res["points"].append({
                 "placement": label, "index_depth": int(s2["index_depth"]),
                 "lds_bytes": int(s2["lds_bytes"]), "scan_kernel": int(s2["scan_kernel"]),
+                "gram_step": trie.launch_gram(n)["step"],
                 "top_lds_bytes": int(s2["bytes_top_nodes"] if tn.get("top_nodes")
                                      else s2["bytes_level_index"]),
                 "image_bytes": int(s2["bytes_device"]), "node_bytes": int(s2["bytes_nodes"]),
@@ -751,28 +752,28 @@ def valu_issue(counts, n_cu, kernel_ms):
             "issue_bound_ms": round(issue_ms, 5), "frac": round(issue_ms / kernel_ms, 4)}
 
 
-def kernel_of(stats, tuning):
-    """(name, split) of the main scan kernel of a launch; `stats` carries
-    "launch_kernel", the kernel a launch of the measured size runs where the
-    gram kernel does not: that takes the launches whose kernel the library
-    chooses (kernel 3) for patterns of four bytes or more."""
-    if tuning["kernel"] == 3 and int(stats["min_len"]) >= 4 and not (tuning["trunc_depth"] or tuning["dag"]):
+def kernel_of(stats):
+    """(name, split) of the main scan kernel of a launch; `stats` carries what
+    the library says of a launch of the measured size: "launch_gram" (the gram
+    kernel's step, 0 where it does not run) and "launch_kernel" (the kernel
+    then)."""
+    if int(stats["launch_gram"]):
         return "scan_grams", False
     k = int(stats["launch_kernel"])
     return ("scan_waves" if k in (1, 2) else "scan_tiles"), k == 2
 
 
-def alg_bytes_of(stats, tuning, text_bytes, n_matches):
+def alg_bytes_of(stats, text_bytes, n_matches):
     """Algorithmic bytes of one launch of the main scan kernel: every text
     byte read once and the CRS trie read once; all but the filter kernel of
     the split path also write the 16-byte match records."""
-    _, split = kernel_of(stats, tuning)
+    _, split = kernel_of(stats)
     return text_bytes + int(stats["bytes_crs"]) + (0 if split else 16 * n_matches)
 
 
 def roofline_entry(stats, workload, tuning, text_bytes, n_matches, kernel_ms, step_ms, probe, n_cu):
-    kernel_name, split = kernel_of(stats, tuning)
-    alg = alg_bytes_of(stats, tuning, text_bytes, n_matches)
+    kernel_name, split = kernel_of(stats)
+    alg = alg_bytes_of(stats, text_bytes, n_matches)
     achieved = alg / (kernel_ms / 1e3) / 1e9
     step_bytes = text_bytes + int(stats["bytes_crs"]) + 16 * n_matches
     counts = profile_counts(kernel_name, workload, tuning)
@@ -861,6 +862,7 @@ def measure_single(pf, torch, name, args, dev_name, threads, steps, headline=Fal
         tuning, tuned_now = trie.tuning(), False
     st = trie.stats()
     st["launch_kernel"] = trie.launch_kernel(n)[0]
+    st["launch_gram"] = trie.launch_gram(n)["step"]
 
     stream = torch.cuda.current_stream()
     cnt = torch.zeros(1, dtype=torch.int64, device="cuda")
@@ -949,6 +951,7 @@ def measure_batch(pf, torch, args, dev_name, threads):
         tuning, tuned_now = trie.tuning(), False
     st = trie.stats()
     st["launch_kernel"] = trie.launch_kernel(total)[0]
+    st["launch_gram"] = trie.launch_gram(total)["step"]
     stream = torch.cuda.Stream()
     cnt = torch.zeros(1, dtype=torch.int64, device="cuda")
     with torch.cuda.stream(stream):

@@ -82,7 +82,8 @@ typedef struct {
     uint32_t symbol_bits;      /* bits per symbol in the level index */
     uint32_t index_depth;      /* K: levels resolved by the level index in LDS */
     uint32_t lds_bytes;        /* dynamic LDS per workgroup of the scan kernel */
-    uint32_t scan_kernel;      /* kernels the current tuning launches: 0 = tile, 1 = fused
+    uint32_t scan_kernel;      /* kernels the current tuning launches where the gram kernel
+                                  does not run (pfac_trie_launch_gram): 0 = tile, 1 = fused
                                   wave kernel, 2 = split filter + walk kernels */
     uint32_t scan_waves;       /* waves per workgroup it launches with (after LDS fitting) */
     uint32_t stage1;           /* wave kernels' first filter: 0 = rolling code over K symbols (or
@@ -235,10 +236,29 @@ int pfac_trie_set_tuning(pfac_trie *t, const pfac_tuning *tuning);
  * batch) runs with the current tuning, with kernel 3 resolved by that size:
  * *kernel = 0 (tile kernel), 1 (fused wave kernel) or 2 (split filter +
  * walk kernels); *tuning (may be NULL) = the tuning that launch uses.  A
- * launch that takes the gram kernel is reported as what it would run without.
+ * launch that takes the gram kernel (pfac_trie_launch_gram) is reported as what
+ * it would run without.
  * Host only.  Errors: PFAC_EINVAL (NULL trie or kernel). */
 int pfac_trie_launch_kernel(const pfac_trie *t, uint64_t total_bytes, uint32_t *kernel,
                             pfac_tuning *tuning);
+
+/* How the gram kernel runs a launch over `total_bytes` bytes (one text, or a
+ * whole batch, at an address divisible by 16) with the current tuning; step = 0
+ * where the kernels of pfac_trie_launch_kernel run it.  (A workspace whose
+ * list area the device cannot hold, and pfac_scan_noalloc where the scratch
+ * does not fit, run those as well.)
+ * Host only.  Errors: PFAC_EINVAL (NULL trie or out). */
+typedef struct {
+    uint32_t step;             /* distance of the positions tested: 4, 2 or 1 */
+    uint32_t symbols;          /* symbols of two bits a gram has (0: four bytes) */
+    uint32_t runs;             /* 1 = a position counts when the three after it hit too */
+    uint32_t bitmap_bytes;     /* size of the filter's bitmap ... */
+    uint32_t bitmap_in_lds;    /* ... and 1 where workgroups copy it to LDS (else read from L2) */
+    uint32_t waves_per_wg, chunks_per_unit;
+    uint32_t unit_matches;     /* matches of a unit that LDS holds */
+    uint32_t lds_bytes;        /* dynamic LDS per workgroup */
+} pfac_gram_launch;
+int pfac_trie_launch_gram(const pfac_trie *t, uint64_t total_bytes, pfac_gram_launch *out);
 
 /* -------------------------------------------------------------- workspace */
 

@@ -69,6 +69,12 @@ class pfac_tuning(ctypes.Structure):
                 ("dag", ctypes.c_uint32)]
 
 
+class pfac_gram_launch(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_uint32) for name in (
+        "step", "symbols", "runs", "bitmap_bytes", "bitmap_in_lds", "waves_per_wg", "chunks_per_unit",
+        "unit_matches", "lds_bytes")]
+
+
 class PfacError(RuntimeError):
     def __init__(self, fn: str, code: int, hip: int = 0):
         self.code = code
@@ -93,6 +99,7 @@ SIGNATURES = [
     ("pfac_trie_free", None, [_vp]),
     ("pfac_trie_get_tuning", ctypes.c_int, [_vp, _p(pfac_tuning)]),
     ("pfac_trie_launch_kernel", ctypes.c_int, [_vp, ctypes.c_uint64, _p(ctypes.c_uint32), _p(pfac_tuning)]),
+    ("pfac_trie_launch_gram", ctypes.c_int, [_vp, ctypes.c_uint64, _p(pfac_gram_launch)]),
     ("pfac_trie_set_tuning", ctypes.c_int, [_vp, _p(pfac_tuning)]),
     ("pfac_workspace_create", ctypes.c_int, [_p(_vp)]),
     ("pfac_workspace_free", None, [_vp]),
@@ -245,13 +252,22 @@ class Trie:
         return {n: getattr(t, n) for n, _ in t._fields_}
 
     def launch_kernel(self, total_bytes: int):
-        """(kernel, tuning) of a launch over total_bytes: 0 = tile kernel,
-        1 = fused wave kernel, 2 = split filter + walk kernels."""
+        """(kernel, tuning) of a launch over total_bytes that the gram kernel
+        does not run (launch_gram): 0 = tile kernel, 1 = fused wave kernel,
+        2 = split filter + walk kernels."""
         k = ctypes.c_uint32()
         t = pfac_tuning()
         check("pfac_trie_launch_kernel", load().pfac_trie_launch_kernel(
             self.handle, int(total_bytes), ctypes.byref(k), ctypes.byref(t)))
         return int(k.value), {n: getattr(t, n) for n, _ in t._fields_}
+
+    def launch_gram(self, total_bytes: int):
+        """How the gram kernel runs a launch over total_bytes (pfac_gram_launch;
+        step 0: it does not, launch_kernel's kernels do)."""
+        g = pfac_gram_launch()
+        check("pfac_trie_launch_gram", load().pfac_trie_launch_gram(
+            self.handle, int(total_bytes), ctypes.byref(g)))
+        return {n: int(getattr(g, n)) for n, _ in g._fields_}
 
     def set_tuning(self, **fields):
         """Change the named fields of the launch tuning (pfac_tuning); the

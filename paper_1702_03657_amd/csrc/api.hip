@@ -934,6 +934,26 @@ static ScanShape scan_shape(const pfac_trie *t, const pfac_tuning &tn, const voi
     return h;
 }
 
+extern "C" int pfac_trie_launch_gram(const pfac_trie *t, uint64_t total_bytes, pfac_gram_launch *o) {
+    if (!t || !o) return PFAC_EINVAL;
+    std::memset(o, 0, sizeof(*o));
+    if (!use_gram_kernel(t)) return PFAC_OK;
+    const ScanShape h = scan_shape(t, launch_tuning(t, total_bytes), nullptr, total_bytes, true);
+    ScanArgs a{};
+    a.im.gram_lw = t->img.gram_lw;
+    gram_lds_layout(a, h.waves, h.gram_lds, t->lds_limit);
+    o->step = t->img.gram_s;
+    o->symbols = t->img.gram_q;
+    o->runs = t->img.gram_run;
+    o->bitmap_bytes = 4u << t->img.gram_lw;
+    o->bitmap_in_lds = h.gram_lds;
+    o->waves_per_wg = h.waves;
+    o->chunks_per_unit = h.group;
+    o->unit_matches = a.gm;
+    o->lds_bytes = a.lds_total;
+    return PFAC_OK;
+}
+
 // gram: by the gram kernel (use_gram_kernel)
 static int enqueue_scan(const Launch &L, bool reserve, bool gram) {
     const pfac_trie *t = L.t;

@@ -302,7 +302,45 @@ def small_alphabets():
         assert kernel in _kernels(), (symbols, k, lo)
 
 
-TESTS = [small_alphabets, explicit_kernels_run, list_area_refused, first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
+def launch_gram_tells():
+    """pfac_trie_launch_gram says of every launch whether the gram kernel runs
+    it, and how; the bench names the main kernel by it."""
+    import bench
+
+    rng = np.random.default_rng(5)
+    dna = np.frombuffer(b"ACGT", dtype=np.uint8)
+    sets = [_bytes_set(300), _bytes_set(20_000), _bytes_set(300, lo=3), _bytes_set(9000, lo=4), _bytes_set(6000, lo=5),
+            [bytes(rng.choice(dna, 9)) for _ in range(100)], [bytes(rng.choice(dna, 20)) for _ in range(40_000)],
+            [bytes(rng.choice(dna, int(m))) for m in rng.integers(20, 33, 200_000)],  # beyond the filter
+            [bytes(rng.choice(np.arange(97, 107), 9).astype(np.uint8)) for _ in range(300)]]
+    seen = set()
+    for pats in sets:
+        trie = pf.Trie(pats)
+        for tuning in ({}, dict(kernel=1), dict(kernel=3), dict(kernel=3, trunc_depth=8), dict(kernel=3, dag=1, trunc_depth=0)):
+            if tuning:
+                if len(pats) > 50_000:
+                    continue
+                trie.set_tuning(**tuning)
+            for n in (1460, 2 * MiB, 2 * MiB + MiB // 2 + KiB, 40 * MiB):
+                told = trie.launch_gram(n)
+                _lines()
+                pf.pfac_scan(trie, pf.Workspace(), TEXT, n, OUT, 100, COUNT)
+                (name, grid, block, lds), = [x for x in _launches() if x[0] in ("scan_grams", "scan_waves", "scan_tiles")]
+                assert (told["step"] != 0) == (name == "scan_grams"), (len(pats), tuning, n)
+                st = dict(launch_gram=told["step"], launch_kernel=trie.launch_kernel(n)[0])
+                assert bench.kernel_of(st)[0] == name
+                if told["step"]:
+                    assert block == 64 * told["waves_per_wg"] and lds == told["lds_bytes"]
+                    assert lds > told["bitmap_bytes"] or not told["bitmap_in_lds"]
+                    units = -(-n // (KiB * told["chunks_per_unit"]))
+                    assert grid == min(-(-units // told["waves_per_wg"]), 256 if told["bitmap_in_lds"] else 1 << 30)
+                    seen.add((told["step"], bool(told["symbols"]), told["runs"], told["bitmap_in_lds"]))
+    assert {(s, False, 0, b) for s in (1, 2, 4) for b in (0, 1)} <= seen and {(1, True, 1, 0), (1, True, 1, 1)} <= seen
+    assert pf.load().pfac_trie_launch_gram(None, 1, None) == pf.PFAC_EINVAL
+    assert pf.load().pfac_trie_launch_gram(trie.handle, 1, None) == pf.PFAC_EINVAL
+
+
+TESTS = [launch_gram_tells, small_alphabets, explicit_kernels_run, list_area_refused, first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
 
 
 @pytest.mark.parametrize("name", [t.__name__ for t in TESTS])
