@@ -340,7 +340,23 @@ def launch_gram_tells():
     assert pf.load().pfac_trie_launch_gram(trie.handle, 1, None) == pf.PFAC_EINVAL
 
 
-TESTS = [launch_gram_tells, small_alphabets, explicit_kernels_run, list_area_refused, first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
+def noalloc_routes():
+    """pfac_scan_noalloc takes the gram kernel while its list area fits in the
+    64 MiB beside the records, then the kernels that need less; what fits
+    neither is refused before anything is launched."""
+    trie = pf.Trie(_bytes_set(3000))
+    n = 7 * MiB + 5
+    for cap, kernel in ((1000, "scan_grams"), ((58 * MiB) // 16, "scan_grams"), ((62 * MiB) // 16, "scan_tiles")):
+        _lines()
+        pf.pfac_scan_noalloc(trie, TEXT, n, OUT, cap, COUNT)
+        lines = _lines()
+        assert kernel in _kernels(lines) and not _areas(lines)
+    with pytest.raises(pf.PfacError) as e:
+        pf.pfac_scan_noalloc(trie, TEXT, n, OUT, 4 * MiB, COUNT)
+    assert e.value.code == pf.PFAC_EINVAL and not _lines()
+
+
+TESTS = [noalloc_routes, launch_gram_tells, small_alphabets, explicit_kernels_run, list_area_refused, first_scan_allocates_what_it_reads, lists_aligned, cursor_cleared, graph_cursor_cleared, reserved_scans_allocate_nothing]
 
 
 @pytest.mark.parametrize("name", [t.__name__ for t in TESTS])
