@@ -317,8 +317,8 @@ int pfac_scan(const pfac_trie *t, pfac_workspace *w, const uint8_t *text_dev, ui
  * PFAC_EINVAL before touching the device.  Every call on a device uses the
  * same array: calls that may overlap on one device (different streams or
  * threads) race and must be ordered by the caller; a call on one stream
- * after another is safe.  The array keeps the previous call's contents;
- * the scan clears what it needs cleared.
+ * after another is safe.  The array keeps the previous call's contents; a
+ * scan leaves cleared what the next one needs so.
  */
 int pfac_scan_noalloc(const pfac_trie *t, const uint8_t *text_dev, uint64_t n,
                       pfac_match *out_dev, uint64_t capacity, uint64_t *n_matches_dev,

@@ -867,13 +867,13 @@ static bool uses_split(const pfac_trie *t, const pfac_tuning &tn) {
     return tn.kernel == 2 && use_wave_kernel(t, tn, nullptr);
 }
 
-// How a scan of `total` bytes at `text` is cut with the trie's tuning:
-// output units (tiles, or units of G chunks), batch-plan units (1 KiB chunks
-// of the wave kernels, else tiles), and which kernels run.
 // Up to this many units a finisher workgroup takes 16 of them, past it 32 (16
 // MiB of words: 38 us a scan with 16, 40 with 32).
 constexpr uint64_t kFinishWide = 8192;
 
+// How a scan of `total` bytes at `text` is cut with the trie's tuning:
+// output units (tiles, or units of G chunks), batch-plan units (1 KiB chunks
+// of the wave kernels, else tiles), and which kernels run.
 struct ScanShape {
     bool wave_kernel, split, gram;
     bool gram_lds;                    // gram kernel: its bitmap in LDS

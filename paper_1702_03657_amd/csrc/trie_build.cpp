@@ -656,10 +656,13 @@ static void build_grams(const CrsTrie &T, DeviceImageHost &I) {
     // patterns from four symbols on: 106 and 1,793).
     if (!sym && I.K) {
         const double codes = level(I.K);
-        double often = 0;  // matches a KiB
-        for (uint32_t j = 0; j < T.k; j++) often += 1024 * std::pow((double)I.alphabet, -(double)(T.pat_off[j + 1] - T.pat_off[j]));
         const double fused = 82 + 230 * codes / std::pow((double)I.alphabet, (double)I.K) + (codes > 4096 ? 0.006 * codes : 0.0);
-        if (20 + 1.6 * best > fused && often < 2) return;
+        if (20 + 1.6 * best > fused) {
+            double often = 0;  // matches a KiB
+            for (uint32_t j = 0; j < T.k; j++)
+                often += 1024 * std::pow((double)I.alphabet, -(double)(T.pat_off[j + 1] - T.pat_off[j]));
+            if (often < 2) return;
+        }
     }
     uint32_t lg = 12;  // bits of the bitmap: 24 a gram, at most 2^20
     while (lg < 20 && (1ull << lg) < (run ? 48 : 24) * n) lg++;
