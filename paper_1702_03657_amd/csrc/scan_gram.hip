@@ -18,10 +18,11 @@
 // one after another, so there every position is tested against the grams at
 // offsets 0 .. 3, one bit each, and four hits in a row are wanted: 1% for
 // 100,000 patterns, where two bits a gram leave 11% of every second position or
-// 29% of every fourth.  1 GiB, 100,000 patterns of 20 to 32: 329 us, VALU busy
-// for 278 of it (a hash per position and a second stage of walks 830, every
-// second position 571, pairs of two-bit hits 343); 32 MiB, 500 patterns of 9 to
-// 14, where the generic filter kept every 25th position: 26 us (90).
+// 29% of every fourth.  1 GiB, 100,000 patterns of 20 to 32: 333 us a call, of
+// which VALU issue takes 280 (164 instructions a KiB; a hash per position and a
+// second stage of walks 830, every second position 571, pairs of two-bit hits
+// 343); 32 MiB, 500 patterns of 9 to 14, where the generic filter kept every
+// 25th position: 26 us (90).
 //
 //   * a workgroup loads the bitmap (two hashed bits per gram, at most 128 KiB)
 //     into LDS; each wave owns units of G consecutive 1 KiB chunks of test
@@ -601,8 +602,8 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
     // Queue a lane's grams that hit (bit j of m: at unit position pos + j * S),
     // one of every lane at a time: symbols, whose grams are one shift away.  (32
     // MiB against 500 motifs: 26 us, 30 with a ballot per test.  Bytes, whose
-    // gram is chosen among five registers: 2.1 GB of packets and files 718, 515 with a
-    // ballot per test.)
+    // gram is chosen among five registers: 2.1 GB of packets and files 718, 515
+    // with a ballot per test.)
     auto queue_bits = [&](uint32_t m, uint32_t p0, uint32_t p1, uint32_t pos) {
         for (;;) {
             const unsigned long long mk = __ballot(m != 0);
