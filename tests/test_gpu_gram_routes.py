@@ -245,3 +245,48 @@ def test_noalloc_on_both_sides_of_the_scratch():
             assert int(cnt.item()) == want.n
             assert_same(pf.matches_to_numpy(out, want.n), want)
             assert np.array_equal(counts.cpu().numpy().view(np.uint32), oracle.counts(n, want))
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_scans_captured_by_the_caller(noalloc):
+    """A scan captured on the caller's stream as a workspace's first one, then
+    replayed, with eager scans of other sizes on the same workspace between."""
+    import torch
+    rng = np.random.default_rng(5)
+    pats = _patterns(rng, BYTES, 500, 5, 30)
+    trie = pf.Trie(pats)
+    n = 300_000
+    texts = [_text(rng, BYTES, n, pats) for _ in range(3)]
+    wants = [oracle.bucketed(t, pats, threads=8) for t in texts]
+    cap = max(w.n for w in wants)
+    dev = torch.from_numpy(texts[0]).cuda()
+    out = torch.empty(cap * 16, dtype=torch.uint8, device="cuda")
+    cnt = torch.zeros(1, dtype=torch.int64, device="cuda")
+    ws = pf.Workspace()
+    ws.reserve(n, 1, cap)
+    side = torch.cuda.Stream()
+
+    def scan(stream):
+        if noalloc:
+            pf.pfac_scan_noalloc(trie, dev, n, out, cap, cnt, None, stream)
+        else:
+            pf.pfac_scan(trie, ws, dev, n, out, cap, cnt, None, stream)
+
+    if noalloc:  # (the first call on a device looks its array up)
+        scan(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="thread_local"):
+        scan(side)
+    for i in (1, 2, 0, 1):
+        # an eager scan of the same workspace first: nothing was cleared by the capture
+        if not noalloc:
+            got, _ = gpu_scan(trie, texts[i][:90_000 + i], ws=ws, counts=False)
+            assert_same(got, oracle.bucketed(texts[i][:90_000 + i], pats, threads=8))
+        dev.copy_(torch.from_numpy(texts[i]))
+        out.fill_(0xAB)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(cnt.item()) == wants[i].n
+        assert_same(pf.matches_to_numpy(out, wants[i].n), wants[i])
