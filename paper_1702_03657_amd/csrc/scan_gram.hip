@@ -683,15 +683,14 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
         // of theirs hits in every lane, though at offset 1 .. S-1 of a pattern
         // that may start nowhere in it.  In chunks that do (one compare) the hits
         // count only if a pattern begins with the four bytes from one of the S
-        // starts on: asked once for a pair of dwords, those of one lane that repeats
-        // itself.  (64 MiB
-        // with 64 KiB runs of zeros for a tenth of it, one pattern in a hundred
-        // with four zeros past its first byte: 210 us without this, 30 with; the
-        // prefix filter of the split kernels 51.)
+        // starts on: asked once for a pair of dwords, those of one lane that
+        // repeats itself.  (64 MiB with 64 KiB runs of zeros for a tenth of it, one
+        // pattern in a hundred with four zeros past its first byte: 210 us without
+        // this, 30 with; the prefix filter of the split kernels 51.)
         if (S > 1 && __builtin_expect(__ballot(w[0] == w[2]) != 0, 0)) {
-            // the dword before the lane's 16 bytes (of lane - 1; lane 0 takes one
-            // that none equals)
-            const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp((int)~pass_y, (int)w[3], 0x138, 0xf, 0xf, false);
+            // the dword before the lane's 16 bytes: of lane - 1; lane 0, which has
+            // none, keeps its tests there
+            const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[3], 0x138, 0xf, 0xf, false);
             const ScanArgs &r = again(a);
             const scalar_u32_t *first = (const scalar_u32_t *)(uintptr_t)r.im.gper;
             constexpr uint32_t P = 4 / S;  // tests a dword
@@ -718,7 +717,7 @@ __global__ __launch_bounds__(1024) void scan_grams(const ScanArgs a) {
 #pragma unroll
                 for (uint32_t j = k; j < TL; j += 2 * P) {
                     const uint32_t y = j >= P ? x[j - P] : k == 0 ? before : __builtin_amdgcn_alignbyte(w[0], before, k * S);
-                    ent[j] = x[j] == pass_x && y == pass_y ? 0u : ent[j];
+                    ent[j] = x[j] == pass_x && y == pass_y && (j >= P || lane != 0) ? 0u : ent[j];
                 }
             }
         }

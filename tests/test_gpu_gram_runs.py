@@ -72,6 +72,40 @@ def test_runs(lo, more, n, pad):
     assert np.array_equal(counts, oracle.counts(n, want))
 
 
+@pytest.mark.parametrize("lo", [5, 8])
+@pytest.mark.parametrize("more", [150, 20_000])
+@pytest.mark.parametrize("kib", [600, 9000])
+def test_runs_from_a_chunk_s_first_byte(lo, more, kib):
+    """Runs that begin where a KiB of the text's frame does, behind the first
+    bytes of a pattern that goes on with them, after runs of other bytes: what
+    lies before the chunk is not what a run inside it suggests."""
+    rng = np.random.default_rng(lo + more)
+    fills = [b"\xff", b"\0", b"\0\0\xff\xff", b"\xff\xff\0\0", b"\0\xff", b"\x01\x02\x03\x04\x05\x06\x07\x08"]
+    heads = [b"M", b"MZ", b"M\0Z"]
+    # a pattern for each head and phase of a fill, none that begins in one
+    pats = [h + ((f[q:] + f[:q]) * 8)[:m] for f in fills for h in heads for q in range(len(f)) for m in (lo, lo + 1, 20)]
+    pats += [bytes(rng.integers(1, 255, 1, dtype=np.uint8)) + rng.integers(0, 256, int(rng.integers(lo, 24)), dtype=np.uint8).tobytes()
+             for _ in range(more)]
+    pad = 5
+    n = kib * 1024 + 77
+    text = rng.integers(0, 256, n, dtype=np.uint8)
+    for c in range(2, kib - 10):
+        at = c * 1024 - pad
+        f = fills[c % len(fills)]
+        q = int(rng.integers(0, len(f)))
+        h = np.frombuffer(heads[c // len(fills) % len(heads)] if c % 4 else f[-1:], dtype=np.uint8)
+        text[at:at + 200] = np.resize(np.frombuffer(f[q:] + f[:q], dtype=np.uint8), 200)
+        text[at - h.size:at] = h
+        # another run before, so that a wave has seen one
+        g = np.frombuffer(fills[(c + 1) % len(fills)], dtype=np.uint8)
+        text[at - 300:at - 100] = np.resize(g, 200)
+    want = oracle.bucketed(text, pats, threads=8)
+    say(f"gram runs at chunks lo={lo} more={more} kib={kib}: {want.n} matches")
+    got, counts = gpu_scan(pf.Trie(pats), text, pad_front=pad, capacity=want.n)
+    assert_same(got, want)
+    assert np.array_equal(counts, oracle.counts(n, want))
+
+
 @pytest.mark.parametrize("lo,hi,k", [(9, 14, 300), (13, 16, 3000), (20, 32, 20_000)])
 def test_symbol_runs(lo, hi, k):
     rng = np.random.default_rng(lo)
