@@ -66,12 +66,11 @@ __device__ __forceinline__ bool chain_equal_g(const uint8_t *base, uint64_t g, c
     return diff == 0;
 }
 
-// Walk for the start position at frame position p from node v at depth d; the
-// text ends lim bytes after p, and byte_at(i) is its byte at p + i.  Returns the
-// pattern list of the deepest terminal node passed.
-template <class ByteAt>
-__device__ __forceinline__ uint2 walk_nodes(const ImageView &im, const uint8_t *base, uint64_t p, uint32_t lim,
-                                            uint32_t v, uint32_t d, uint64_t hi_valid, ByteAt byte_at) {
+// Walk for the start position at frame position p from node v at depth d,
+// reading the text from global memory; the text ends lim bytes after p.
+// Returns the pattern list of the deepest terminal node passed.
+__device__ __forceinline__ uint2 walk_g(const ImageView &im, const uint8_t *base, uint64_t p,
+                                        uint32_t lim, uint32_t v, uint32_t d, uint64_t hi_valid) {
     uint2 hit = make_uint2(0, 0);
     for (;;) {
         const uint4 r = im.node[v];
@@ -97,7 +96,7 @@ __device__ __forceinline__ uint2 walk_nodes(const ImageView &im, const uint8_t *
                 continue;
             }
         }
-        const uint32_t c = byte_at(d);
+        const uint32_t c = base[p + d];
         uint32_t j;
         if (skip) {
             if (c != im.label[r.y - 1]) break;
@@ -122,12 +121,6 @@ __device__ __forceinline__ uint2 walk_nodes(const ImageView &im, const uint8_t *
         d++;
     }
     return hit;
-}
-
-// walk_nodes reading the text from global memory
-__device__ __forceinline__ uint2 walk_g(const ImageView &im, const uint8_t *base, uint64_t p,
-                                        uint32_t lim, uint32_t v, uint32_t d, uint64_t hi_valid) {
-    return walk_nodes(im, base, p, lim, v, d, hi_valid, [&](uint32_t i) -> uint32_t { return base[p + i]; });
 }
 
 // Stage the matches of unit u in (pos, id) order.  wm[i] = (unit position |
