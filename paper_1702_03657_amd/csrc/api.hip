@@ -955,7 +955,7 @@ extern "C" int pfac_trie_launch_gram(const pfac_trie *t, uint64_t total_bytes, p
 }
 
 // gram: by the gram kernel (use_gram_kernel)
-static int enqueue_scan(const Launch &L, bool reserve, bool gram) {
+static int enqueue_kernels(const Launch &L, bool reserve, bool gram) {
     const pfac_trie *t = L.t;
     const pfac_tuning tn = launch_tuning(t, L.total);
     ScanShape h = scan_shape(t, tn, L.text, L.total, gram);
@@ -1105,6 +1105,17 @@ static int enqueue_scan(const Launch &L, bool reserve, bool gram) {
     HIP_TRY(launch_finish(f, L.s));
     w->cursor_stale = capture != hipStreamCaptureStatusNone;  // captured: nothing ran
     return PFAC_OK;
+}
+
+static int enqueue_scan(const Launch &L, bool reserve, bool gram) {
+    const bool stale = L.w->cursor_stale;
+    const int rc = enqueue_kernels(L, reserve, gram);
+    // A launch failed on the way: the cursor is cleared behind what was queued,
+    // if that can be queued (replays of scans that were captured while it was
+    // known to be clear do not clear it).
+    if (rc != PFAC_OK && !stale && L.w->cursor_stale && launch_reset(L.w->cursor(), nullptr, 0, L.s) != hipSuccess)
+        (void)hipGetLastError();
+    return rc;
 }
 
 static int check_scan_args(const pfac_trie *t, pfac_workspace *w, const void *text, uint64_t n,

@@ -116,11 +116,13 @@ def cursor_cleared():
     for call in (lambda: scan(ws), noalloc):
         call()
         hip.host_hip_refuse(b"finish_tiles")
+        _lines()
         with pytest.raises(pf.PfacError) as e:
             call()
         assert e.value.code == pf.PFAC_EDEVICE
+        # at once, for replays of scans captured before, and again with the next
+        assert _kernels() == ["scan_grams", "reset_kernel"]
         hip.host_hip_refuse(b"")
-        _lines()
         call()
         assert _kernels() == ["reset_kernel", "scan_grams", "finish_tiles"]
         call()
